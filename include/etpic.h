@@ -309,10 +309,12 @@ int etpic_gather_push_deposit(etpic_ctx *ctx, const etpic_particles *p, int prec
 
 /* nsteps consecutive steps (times (step0 + j) dt, j = 0..nsteps-1) with the same
  * field DoFs: the same result as nsteps calls of etpic_gather_push_deposit,
- * with rho (if not NULL) deposited after the last step only.  Between two
- * steps the walk of one and the coefficient pass of the next run in one
- * kernel launch.  With ETPIC_STEP_TIMING, etpic_kernel_time books that shared
- * launch as walk time (the coefficient time of all but the first step is 0).
+ * with rho (if not NULL) deposited after the last step only.  Up to 16 steps
+ * share one particle-kernel launch, in which the particle state stays in
+ * registers (one step per launch where a flag forces the slices per
+ * wavefront); the field coefficients are prepared once per call.  With
+ * ETPIC_STEP_TIMING, etpic_kernel_time books a launch's time evenly over its
+ * steps.
  * Asynchronous on `stream`.  Errors as etpic_gather_push_deposit. */
 int etpic_run_steps(etpic_ctx *ctx, const etpic_particles *p, int precision, const etpic_species *sp,
                     const etpic_fields *f, int64_t step0, int nsteps, double dt, double omega, double *dG,
@@ -378,7 +380,7 @@ int etpic_gauss_residual(etpic_ctx *ctx, const double *dG, const double *rho_new
                          double out_host[2], void *stream);
 
 /* Slices of 64 particles per wavefront that the last particle-kernel launch of
- * a step call used (1: k_push; 2: k_push_pipe, two pipelined slices; 4 or 16:
+ * a step call used (1: k_push, k_push_multi; 2: k_push_pipe, two pipelined slices; 4 or 16:
  * k_push_slices<S>; 0 before any step).  Host only. */
 int etpic_last_push_slices(const etpic_ctx *ctx, int *slices);
 
@@ -825,11 +827,11 @@ int etpic_cotree_step(etpic_cotree *z, etpic_qh *qh, double dt, double omega, do
 /* Kernel times of the steps launched with ETPIC_STEP_TIMING since the last
  * reset, from HIP start and stop events bound to each kernel's own dispatch
  * on the launch stream (hipExtLaunchKernel: no marker packets between the
- * kernels, so the timing does not stretch the step), summed over the steps:
+ * kernels, so the timing does not stretch the step), summed over the steps (a
+ * launch that takes several steps books its time evenly over them):
  * ms_out[0] = particle kernel (gather, push, in-tet deposit) of the steps
  * that update the particles in place, ms_out[1] = per-tet coefficient kernel
- * where it runs alone, ms_out[2] = walk kernel (with the next step's
- * coefficient pass where the two share a launch, and the gather of the
+ * (once per multi-step call), ms_out[2] = walk kernel (with the gather of the
  * per-tet current sums onto the edges at the end of a call), ms_out[3] =
  * particle kernel of the steps that also sort (the first step of
  * etpic_sort_run_steps); [1] and [2] only for steps run with

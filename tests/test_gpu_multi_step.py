@@ -1,0 +1,117 @@
+"""Several steps per launch (etpic_run_steps, etpic_sort_run_steps,
+etpic_coarse_step) at the sizes where the split of the work can go wrong:
+one particle, wavefronts and blocks that end on a ragged slice, wavefronts
+whose particles sit in more tets than are staged at a time, more steps than
+one launch takes, particles that leave their tet at every step of a launch."""
+import numpy as np
+import pytest
+
+from paper_2208_12795_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_2208_12795_amd import etpic
+    return etpic
+
+
+def problem(E, torch, n, precision, ordered):
+    w = synth.make_workload(1, n_particles=n)
+    if ordered:
+        o = np.argsort(w.tet, kind="stable")
+        w.tet, w.lam, w.vel, w.ids = w.tet[o], w.lam[o], w.vel[o], w.ids[o]
+    ctx = E.Context(0)
+    ctx.upload_mesh(w.xyz, w.tet_vert)
+    f = E.Fields.from_numpy(w.e_env, w.b_env, None, w.b_dc)
+    return w, ctx, f, E.Species(w.q, w.m, w.w), E.Particles.from_numpy(w.tet, w.lam, w.vel, w.ids, precision=precision)
+
+
+def same_state(a, b):
+    for x, y in zip(a[:3], b[:3]):
+        assert np.array_equal(x, y)
+
+
+# 32768 and 32769: the last size with 16 particles to a wavefront and the first with 64
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("n,ordered,nsteps,dt_scale,by_slice", [
+    (1, True, 2, 1.0, False), (63, False, 16, 1.0, False), (65, False, 17, 300.0, False),
+    (1000, False, 33, 1000.0, False), (1000, True, 16, 1000.0, True), (32768, False, 3, 300.0, False),
+    (32769, False, 3, 300.0, False), (32769, True, 16, 300.0, True), (100_003, True, 10, 1.0, False)])
+def test_multi_equals_single_steps(E, torch_cuda, n, ordered, nsteps, dt_scale, by_slice, precision):
+    """One call of nsteps against nsteps calls of one step: identical particles;
+    currents and charge to the rounding of their sums (1e-13 of the largest,
+    the tolerance of the other tests of this identity)."""
+    torch = torch_cuda
+    w, ctx, f, sp, p1 = problem(E, torch, n, precision, ordered)
+    p2 = p1.clone()
+    dt = w.dt * dt_scale
+    flags = E.STEP_XCD_REMAP | (E.STEP_WALK_BY_SLICE if by_slice else 0)
+    g1 = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    g2 = torch.zeros_like(g1)
+    rho1 = torch.zeros(ctx.n_vert, dtype=torch.float64, device="cuda")
+    rho2 = torch.zeros_like(rho1)
+    ctx.run_steps(p1, sp, f, 7, nsteps, dt, w.omega, g1, rho=rho1, flags=flags)
+    for j in range(nsteps):
+        ctx.gather_push_deposit(p2, sp, f, 7 + j, dt, w.omega, g2, rho=rho2 if j == nsteps - 1 else None, flags=flags)
+    ctx.check()
+    same_state(p1.to_numpy(), p2.to_numpy())
+    if dt_scale > 1:
+        moved = (p1.tet.cpu().numpy() != w.tet).mean()
+        print(f"[multi] moved to another tet: {moved:.3f}", flush=True)
+        assert moved > 0.01
+    assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    assert torch.allclose(rho1, rho2, rtol=0, atol=1e-13 * rho2.abs().max().item())
+    ctx.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("n,ordered,nsteps,dt_scale", [(1, True, 2, 1.0), (1000, False, 18, 300.0),
+                                                       (40_001, True, 10, 300.0)])
+def test_sorting_multi_equals_sort_then_single_steps(E, torch_cuda, n, ordered, nsteps, dt_scale, precision):
+    torch = torch_cuda
+    w, ctx, f, sp, src = problem(E, torch, n, precision, ordered)
+    dt = w.dt * dt_scale
+    d1, d2 = src.empty_like(), src.empty_like()
+    g1 = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    g2 = torch.zeros_like(g1)
+    ctx.sort_run_steps(src, d1, sp, f, 0, nsteps, dt, w.omega, g1)
+    ctx.sort(src, d2)
+    for j in range(nsteps):
+        ctx.gather_push_deposit(d2, sp, f, j, dt, w.omega, g2)
+    ctx.check()
+    a, b = d1.to_numpy(), d2.to_numpy()
+    oa, ob = np.argsort(a[3]), np.argsort(b[3])
+    same_state([x[oa] for x in a], [x[ob] for x in b])
+    assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    ctx.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("n,ordered", [(65, False), (40_001, True)])
+def test_coarse_launch_split_changes_nothing(E, torch_cuda, n, ordered, precision):
+    """Twenty fine steps with three different snapshots (two launches) against
+    the same call with its slices forced to one, which takes one step per
+    launch."""
+    torch = torch_cuda
+    w, ctx, f, sp, p1 = problem(E, torch, n, precision, ordered)
+    snaps = [E.Fields.from_numpy(e, b, None, w.b_dc) for e, b in synth.envelope_snapshots(w, seed=3)]
+    p2 = p1.clone()
+    g1 = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    g2 = torch.zeros_like(g1)
+    dtc = 20 * 300.0 * w.dt
+    ctx.coarse_step(p1, sp, snaps, 3 * dtc, dtc, 20, w.omega, g1)
+    ctx.coarse_step(p2, sp, snaps, 3 * dtc, dtc, 20, w.omega, g2, flags=E.STEP_XCD_REMAP | E.STEP_SLICES_1)
+    ctx.check()
+    same_state(p1.to_numpy(), p2.to_numpy())
+    assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    ctx.close()
