@@ -953,49 +953,112 @@ __global__ void __launch_bounds__(kBlock) k_slots_to_edges(int64_t ne, const int
 }
 
 
-// Fields at the barycentrics l of a tet and the Boris update of v:
-// E = A_0 + beta x u, B = C_0 + b u at u = x - r_0 = sum_{k>0} l_k (r_k - r_0),
-// half kick, rotation (implicit midpoint in v x B), half kick.
-template <typename Real>
-__device__ __forceinline__ void gather_boris(const Real *cf, const Real *gm, const double l[4], Real h, Real v[3]) {
-    const Real x1 = (Real)l[1], x2 = (Real)l[2], x3 = (Real)l[3];
-    Real u[3];
+// 2 / d for d >= 1 or NaN: the reciprocal refined, without the operand scaling
+// a general division starts with.  float32: the steps of the general division,
+// hence its (correctly rounded) result.  float64: one cubic step from the
+// hardware's reciprocal (relative error below 2^-20, so the step's own is
+// below 2^-60).  The fix-up gives 0 at d = inf.
+__device__ __forceinline__ float two_over(float d) {
+    float y = __builtin_amdgcn_rcpf(d);
+    y = fmaf(fmaf(-d, y, 1.0f), y, y);
+    float q = 2.0f * y;
+    q = fmaf(fmaf(-d, q, 2.0f), y, q);
+    q = fmaf(fmaf(-d, q, 2.0f), y, q);
+    return __builtin_amdgcn_div_fixupf(q, d, 2.0f);
+}
+__device__ __forceinline__ double two_over(double d) {
+    const double y = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, y, 1.0), y2 = y + y;
+    return __builtin_amdgcn_div_fixup(fma(y2, fma(e, e, e), y2), d, 2.0);
+}
+
+// Fields at the barycentrics x_1..3 of a tet and the Boris update of v:
+// E = A_0 + beta x u, B = C_0 + b u at u = x - r_0 = sum_{k>0} x_k (r_k - r_0),
+// half kick, rotation (implicit midpoint in v x B), half kick.  Shared by the
+// one-step and the multi-step kernels, which thereby round alike.
+__device__ __forceinline__ void gather_boris(const float *cf, const float *gm, const float x[3], float h, float v[3]) {
+    float u[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) u[d] = x1 * gm[d] + x2 * gm[3 + d] + x3 * gm[6 + d];
-    Real E[3], B[3];
+    for (int d = 0; d < 3; ++d) u[d] = x[0] * gm[d] + x[1] * gm[3 + d] + x[2] * gm[6 + d];
+    float E[3], B[3];
     E[0] = cf[0] + (cf[4] * u[2] - cf[5] * u[1]);
     E[1] = cf[1] + (cf[5] * u[0] - cf[3] * u[2]);
     E[2] = cf[2] + (cf[3] * u[1] - cf[4] * u[0]);
 #pragma unroll
     for (int d = 0; d < 3; ++d) B[d] = cf[6 + d] + cf[9] * u[d];
-    Real vm[3], tau[3];
+    float vm[3], tau[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         vm[d] = v[d] + h * E[d];
         tau[d] = h * B[d];
     }
-    const Real t2 = tau[0] * tau[0] + tau[1] * tau[1] + tau[2] * tau[2];
-    const Real sg = (Real)2 / ((Real)1 + t2);
-    const Real vr[3] = {vm[0] + (vm[1] * tau[2] - vm[2] * tau[1]), vm[1] + (vm[2] * tau[0] - vm[0] * tau[2]),
-                        vm[2] + (vm[0] * tau[1] - vm[1] * tau[0])};
+    const float t2 = tau[0] * tau[0] + tau[1] * tau[1] + tau[2] * tau[2];
+    const float sg = two_over(1.0f + t2);
+    const float vr[3] = {vm[0] + (vm[1] * tau[2] - vm[2] * tau[1]), vm[1] + (vm[2] * tau[0] - vm[0] * tau[2]),
+                         vm[2] + (vm[0] * tau[1] - vm[1] * tau[0])};
     v[0] = vm[0] + sg * (vr[1] * tau[2] - vr[2] * tau[1]) + h * E[0];
     v[1] = vm[1] + sg * (vr[2] * tau[0] - vr[0] * tau[2]) + h * E[1];
     v[2] = vm[2] + sg * (vr[0] * tau[1] - vr[1] * tau[0]) + h * E[2];
 }
+// (float64: each sum one chain of fma)
+__device__ __forceinline__ void gather_boris(const double *cf, const double *gm, const double x[3], double h,
+                                             double v[3]) {
+    double u[3], E[3], vm[3], tau[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) u[d] = fma(x[2], gm[6 + d], fma(x[1], gm[3 + d], x[0] * gm[d]));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        E[d] = fma(cf[3 + p], u[q], fma(-cf[3 + q], u[p], cf[d]));
+        tau[d] = h * fma(cf[9], u[d], cf[6 + d]);
+        vm[d] = fma(h, E[d], v[d]);
+    }
+    const double sg = two_over(fma(tau[0], tau[0], fma(tau[1], tau[1], fma(tau[2], tau[2], 1.0))));
+    double vr[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        vr[d] = fma(vm[p], tau[q], fma(-vm[q], tau[p], vm[d]));
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        v[d] = fma(sg, fma(vr[p], tau[q], -(vr[q] * tau[p])), fma(h, E[d], vm[d]));
+    }
+}
 
-// Barycentric increments of the displacement dt v and whether the particle
-// stays in its tet.  lam0 is stored implicitly (1 - lam1 - lam2 - lam3), so its
-// increment is minus the sum of the other three, in float64: deposit and
-// stored end point see the same four increments (continuity to float64
-// rounding).
+// Barycentric increments dl_1..3 of the displacement dt v and the end point t,
+// in units of 1 / one (t_0 = one - t_1 - t_2 - t_3: lam0 is stored implicitly);
+// true if the particle stays in its tet.  A non-finite velocity never stays:
+// it makes every increment non-finite, hence some t negative or NaN.
 template <typename Real>
-__device__ __forceinline__ bool increments(const Real *gr, const Real v[3], Real dt, const double l[4], double dl[4]) {
+__device__ __forceinline__ bool increments(const Real *gr, const Real v[3], Real dt, double one, const double l[4],
+                                           double dl[4], double t[4]) {
     const Real dx[3] = {dt * v[0], dt * v[1], dt * v[2]};
 #pragma unroll
-    for (int k = 1; k < 4; ++k)
-        dl[k] = (double)(gr[3 * k - 3] * dx[0] + gr[3 * k - 2] * dx[1] + gr[3 * k - 1] * dx[2]);
-    dl[0] = -(dl[1] + dl[2] + dl[3]);
-    return (l[0] + dl[0] >= 0.0) && (l[1] + dl[1] >= 0.0) && (l[2] + dl[2] >= 0.0) && (l[3] + dl[3] >= 0.0);
+    for (int k = 1; k < 4; ++k) {
+        if constexpr (std::is_same<Real, float>::value)
+            dl[k] = (double)(gr[3 * k - 3] * dx[0] + gr[3 * k - 2] * dx[1] + gr[3 * k - 1] * dx[2]);
+        else
+            dl[k] = fma(gr[3 * k - 1], dx[2], fma(gr[3 * k - 2], dx[1], gr[3 * k - 3] * dx[0]));
+    }
+#pragma unroll
+    for (int k = 1; k < 4; ++k) t[k] = l[k] + dl[k];
+    t[0] = one - t[1] - t[2] - t[3];
+    return t[0] >= 0.0 && t[1] >= 0.0 && t[2] >= 0.0 && t[3] >= 0.0;
+}
+
+// Path integrals of the six edge functions from the sums over straight in-tet
+// pieces of dl_1..3 and a_12, a_13, a_23, a_kj = l_k dl_j - l_j dl_k: with m the
+// midpoint of a piece, m_k dl_j - m_j dl_k = a_kj, and m_0 dl_j - m_j dl_0 =
+// dl_j - sum_k a_kj (the barycentrics sum to one, the increments to zero).
+__device__ __forceinline__ void edge_sums(const double s[6], double g6[6]) {
+    g6[0] = s[0] + s[3] + s[4];
+    g6[1] = s[1] - s[3] + s[5];
+    g6[2] = s[2] - s[4] - s[5];
+    g6[3] = s[3];
+    g6[4] = s[4];
+    g6[5] = s[5];
 }
 
 // ------------------------------------------------------------------ particle step
@@ -1182,11 +1245,13 @@ __device__ __forceinline__ void push_slices(const StepArgs<Real> &a, int remap) 
             l[3] = sl3;
             l[0] = 1.0 - l[1] - l[2] - l[3];
             Real v[3] = {sv0, sv1, sv2};
-            gather_boris<Real>(a.coef + (int64_t)T * CoefRow<Real>::kStride, a.geo + (int64_t)T * GeoRow<Real>::kStride,
-                               l, a.h, v);
-            if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]))) atomicOr(a.status, (unsigned)ETPIC_DEV_NAN);
-            double dl[4];
-            const bool stays = increments<Real>(a.gpush + (int64_t)T * PushRow<Real>::kStride, v, a.dt_r, l, dl);
+            const Real x[3] = {(Real)l[1], (Real)l[2], (Real)l[3]};
+            gather_boris(a.coef + (int64_t)T * CoefRow<Real>::kStride, a.geo + (int64_t)T * GeoRow<Real>::kStride, x,
+                         a.h, v);
+            double dl[4], end[4];
+            const bool stays = increments(a.gpush + (int64_t)T * PushRow<Real>::kStride, v, a.dt_r, 1.0, l, dl, end);
+            if (!stays && !(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2])))
+                atomicOr(a.status, (unsigned)ETPIC_DEV_NAN);
             if (stays) {
                 // compact form: the end point rounded to the fixed-point grid, and
                 // the piece taken to that point, so that deposit and stored end
@@ -1197,18 +1262,18 @@ __device__ __forceinline__ void push_slices(const StepArgs<Real> &a, int remap) 
                     dl[1] = ((double)un[0] - (double)su1) * kFix;
                     dl[2] = ((double)un[1] - (double)su2) * kFix;
                     dl[3] = ((double)un[2] - (double)su3) * kFix;
-                    dl[0] = -(dl[1] + dl[2] + dl[3]);
+                    end[1] = l[1] + dl[1];
+                    end[2] = l[2] + dl[2];
+                    end[3] = l[3] + dl[3];
                 }
-                // path integral of W1_ij along the straight piece: m_i dl_j - m_j dl_i,
-                // m the midpoint barycentrics (exact: the integrand is affine on the piece)
-                double m[4];
+                // path integrals of the six W1_ij along the straight piece
+                // (edge_sums): deposit and stored end point see the same
+                // increments (continuity to float64 rounding)
+                const double ps[6] = {dl[1], dl[2], dl[3], fma(l[1], dl[2], -(l[2] * dl[1])),
+                                      fma(l[1], dl[3], -(l[3] * dl[1])), fma(l[2], dl[3], -(l[3] * dl[2]))};
+                edge_sums(ps, g6);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) m[k] = l[k] + 0.5 * dl[k];
-                constexpr int le[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
-#pragma unroll
-                for (int e = 0; e < 6; ++e) g6[e] = m[le[e][0]] * dl[le[e][1]] - m[le[e][1]] * dl[le[e][0]];
-#pragma unroll
-                for (int k = 1; k < 4; ++k) l[k] += dl[k];
+                for (int k = 1; k < 4; ++k) l[k] = end[k];
                 if (kScatter) {
                     if (fx) {
                         __builtin_nontemporal_store(un[0], reinterpret_cast<uint32_t *>(a.o_lam1) + dq);
@@ -1407,7 +1472,7 @@ k_push_sort_slices(StepArgs<Real> a, int remap) {
 // reads are HBM round trips: there the state loads of one slice overlap the
 // row round trip of the other.
 template <bool kFixed>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
 k_push_pipe(StepArgs<float> a, int remap) {
     push_slices<float, 2, false, false, kFixed, true>(a, remap);
 }
@@ -1562,10 +1627,6 @@ __global__ void __launch_bounds__(kBlock) k_walk(StepArgs<Real> a) {
 // A particle that leaves its tet at step j stops there (its start point of
 // that step, its new velocity and j are kept: tet = -(T + j nt + 2)) and is
 // queued; k_walk_multi walks it and takes it through the remaining steps.
-//
-// The path integrals of the three edges at vertex 0 follow from the sums of
-// dl_j and of a_kj = l_k dl_j - l_j dl_k over the steps: with m the midpoint,
-// m_k dl_j - m_j dl_k = a_kj, and m_0 dl_j - m_j dl_0 = dl_j - sum_k a_kj.
 constexpr int kMaxFused = 16;
 constexpr int kCoefDoubles = kRowParts<3> * kRowReals;   // per tet: the largest of the coefficient forms
 
@@ -1579,29 +1640,41 @@ struct MultiArgs {
 
 __device__ __forceinline__ int leaver_mark(int T, int j, int64_t nt) { return -(T + j * (int)nt + 2); }
 
-// the six edge sums from the sums over dl_1..3 and a_12, a_13, a_23
-__device__ __forceinline__ void edge_sums(const double s[6], double g6[6]) {
-    g6[0] = s[0] + s[3] + s[4];
-    g6[1] = s[1] - s[3] + s[5];
-    g6[2] = s[2] - s[4] - s[5];
-    g6[3] = s[3];
-    g6[4] = s[4];
-    g6[5] = s[5];
+// The multi-step kernels keep the barycentrics in units of 1 / kOne: 1, or
+// 2^32 in the compact form, whose stored numbers are then whole doubles and
+// every step's scalings by 2^32 drop out (the geometry and gradient rows take
+// them once per launch; a power of two changes no rounding).
+template <bool kFixed>
+constexpr double kOne = kFixed ? kFixScale : 1.0;
+
+// A tet's geometry and gradient rows in those units.
+template <typename Real, bool kFixed>
+__device__ __forceinline__ void load_rows(const StepArgs<Real> &a, int T, Real gm[9], Real gr[9]) {
+    const Real *gmp = a.geo + (int64_t)T * GeoRow<Real>::kStride;
+    const Real *grp = a.gpush + (int64_t)T * PushRow<Real>::kStride;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        gm[k] = kFixed ? gmp[k] * (Real)kFix : gmp[k];
+        gr[k] = kFixed ? grp[k] * (Real)kFixScale : grp[k];
+    }
 }
 
 // One in-tet step's contribution to those sums, and the new barycentrics; in
-// the compact form the end point goes to the fixed-point grid first and the
-// piece runs to it (u: the barycentrics on the grid).
+// the compact form the end point goes to the fixed-point grid first (as
+// fix_round3) and the piece runs to it.
 template <bool kFixed>
-__device__ __forceinline__ void stay_step(double l[4], double dl[4], uint32_t u[3], double s[6]) {
+__device__ __forceinline__ void stay_step(double l[4], double dl[4], double t[4], double s[6]) {
     if (kFixed) {
-        uint32_t un[3];
-        fix_round3(l[1] + dl[1], l[2] + dl[2], l[3] + dl[3], un);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            dl[k + 1] = ((double)un[k] - (double)u[k]) * kFix;
-            u[k] = un[k];
+        for (int k = 1; k < 4; ++k) t[k] = fmin(rint(t[k]), kFixScale - 1.0);
+        if (t[1] + t[2] + t[3] > kFixScale) {
+            uint32_t un[3];
+            fix_round3(t[1] * kFix, t[2] * kFix, t[3] * kFix, un);
+#pragma unroll
+            for (int k = 1; k < 4; ++k) t[k] = (double)un[k - 1];
         }
+#pragma unroll
+        for (int k = 1; k < 4; ++k) dl[k] = t[k] - l[k];
     }
     s[0] += dl[1];
     s[1] += dl[2];
@@ -1610,8 +1683,18 @@ __device__ __forceinline__ void stay_step(double l[4], double dl[4], uint32_t u[
     s[4] = fma(l[1], dl[3], fma(-l[3], dl[1], s[4]));
     s[5] = fma(l[2], dl[3], fma(-l[3], dl[2], s[5]));
 #pragma unroll
-    for (int k = 1; k < 4; ++k) l[k] += dl[k];
-    l[0] = 1.0 - l[1] - l[2] - l[3];
+    for (int k = 1; k < 4; ++k) l[k] = t[k];
+}
+
+// The sums in barycentric units.
+template <bool kFixed>
+__device__ __forceinline__ void unscale_sums(double s[6]) {
+    if (kFixed)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            s[k] *= kFix;
+            s[3 + k] *= kFix * kFix;
+        }
 }
 
 template <typename Real, int kSnap, bool kRho, bool kScatter, bool kFixed>
@@ -1635,7 +1718,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     if (b0 >= a.n) return;   // the whole wavefront; no block barrier below
     const int64_t p = b0 + ln;
     int T = -1;
-    double l[4] = {1.0, 0.0, 0.0, 0.0};
+    double l[4] = {0.0, 0.0, 0.0, 0.0};   // l[0] unused: lam0 is implicit
     uint32_t u[3] = {0, 0, 0};
     Real v[3] = {0, 0, 0};
     if (p < a.n && (int)ln < ma.width) {
@@ -1658,11 +1741,9 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         }
     }
     if (kFixed) {
-        l[1] = fix_to_real(u[0]);
-        l[2] = fix_to_real(u[1]);
-        l[3] = fix_to_real(u[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) l[k + 1] = (double)u[k];
     }
-    l[0] = 1.0 - l[1] - l[2] - l[3];
     const bool act = T >= 0;
     const WaveRuns runs = wave_runs(T, ln);
     unsigned dq = 0;   // scatter form: the sorted position, one cursor atomic per run
@@ -1677,15 +1758,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     const int run = __popcll(heads & (ln == 63 ? ~0ull : ((2ull << ln) - 1ull))) - 1;
     if (runs.head) s_tet[run] = T;
     Real gm[9], gr[9];
-    {
-        const Real *gmp = a.geo + (int64_t)max(T, 0) * GeoRow<Real>::kStride;
-        const Real *grp = a.gpush + (int64_t)max(T, 0) * PushRow<Real>::kStride;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            gm[k] = gmp[k];
-            gr[k] = grp[k];
-        }
-    }
+    load_rows<Real, kFixed>(a, max(T, 0), gm, gr);
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int leave = -1;   // step at which the particle left its tet
 #pragma unroll 1
@@ -1712,11 +1785,17 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
                 ws[k] = ma.ws[j][k];
             }
         };
+        // this lane's entry of the first 64 keeps its parts in registers
+        const int entries = nr * kRowReals;
+        double mine[kParts];
         auto form_rows = [&](Real *row) {
-            for (int e = ln; e < nr * kRowReals; e += 64) row[e] = (Real)row_entry<kSnap>(part + e, kEnt, wc, ws);
+            if ((int)ln < entries) row[ln] = (Real)row_entry<kSnap>(mine, 1, wc, ws);
+            for (int e = ln + 64; e < entries; e += 64) row[e] = (Real)row_entry<kSnap>(part + e, kEnt, wc, ws);
         };
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < kParts; ++q) mine[q] = part[q * kEnt + ln];
         weights(0);
         form_rows(rows);
         weights(1);
@@ -1732,20 +1811,27 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
                 weights(j + 2 <= kMaxFused ? j + 2 : kMaxFused);
             }
             if (live) {
-                gather_boris<Real>(cj, gm, l, a.h, v);
-                double dl[4];
-                if (increments<Real>(gr, v, a.dt_r, l, dl)) {
-                    stay_step<kFixed>(l, dl, u, s);
+                const Real x[3] = {(Real)l[1], (Real)l[2], (Real)l[3]};
+                gather_boris(cj, gm, x, a.h, v);
+                double dl[4], t[4];
+                if (increments(gr, v, a.dt_r, kOne<kFixed>, l, dl, t)) {
+                    stay_step<kFixed>(l, dl, t, s);
                 } else {
-                    // a non-finite velocity makes every increment non-finite,
-                    // which never stays: its flag needs a look here only
                     if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2])))
                         atomicOr(a.status, (unsigned)ETPIC_DEV_NAN);
                     leave = j;
                     live = false;
                 }
             }
-            if (!__ballot(live)) break;
+            if (!__builtin_amdgcn_ballot_w64(live)) break;
+        }
+    }
+    unscale_sums<kFixed>(s);
+    if (kFixed) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            u[k] = (uint32_t)l[k + 1];
+            l[k + 1] *= kFix;
         }
     }
     const bool left = leave >= 0;
@@ -1791,7 +1877,11 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     if (kRho) {
         double r4[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) r4[k] = run_total(act && !left ? l[k] : 0.0, runs);
+        for (int k = 1; k < 4; ++k) r4[k] = run_total(act && !left ? l[k] : 0.0, runs);
+        // lam_0 sums to the number of the run's particles that stayed less the rest
+        const unsigned long long here = __ballot(act && !left);
+        const unsigned long long upto = ln == 63 ? ~0ull : ((2ull << ln) - 1ull);
+        r4[0] = (double)__popcll(here & upto & ~((1ull << runs.head_lane) - 1ull)) - r4[1] - r4[2] - r4[3];
         if (flush) {
             const TetTopo *tp = a.topo + T;
 #pragma unroll
@@ -1825,28 +1915,20 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
     int j = code / (int)a.nt;
     int T = code - j * (int)a.nt;
     if (j >= ma.nsteps) return;
+    double *lam[3] = {a.lam1, a.lam2, a.lam3};
     uint32_t *fl[3] = {reinterpret_cast<uint32_t *>(a.lam1), reinterpret_cast<uint32_t *>(a.lam2),
                        reinterpret_cast<uint32_t *>(a.lam3)};
     double l[4];
-    uint32_t u[3] = {0, 0, 0};
-    if (kFixed) {
+    l[0] = 0.0;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            u[k] = fl[k][p];
-            l[k + 1] = fix_to_real(u[k]);
-        }
-    } else {
-        l[1] = a.lam1[p];
-        l[2] = a.lam2[p];
-        l[3] = a.lam3[p];
-    }
-    l[0] = 1.0 - l[1] - l[2] - l[3];
+    for (int k = 0; k < 3; ++k) l[k + 1] = kFixed ? (double)fl[k][p] : lam[k][p];
     Real v[3] = {a.v0[p], a.v1[p], a.v2[p]};
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     bool some = false;
     auto flush = [&]() {
         if (!some) return;
         double g6[6];
+        unscale_sums<kFixed>(s);
         edge_sums(s, g6);
         double *slot = a.tetG + (int64_t)T * 8;
 #pragma unroll
@@ -1863,43 +1945,52 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
             flush();
             const Real dx[3] = {a.dt_r * v[0], a.dt_r * v[1], a.dt_r * v[2]};
             double d[3] = {(double)dx[0], (double)dx[1], (double)dx[2]};
+            if (kFixed)
+#pragma unroll
+                for (int k = 1; k < 4; ++k) l[k] *= kFix;
             T = walk<Real, false>(a, T, l, d, v, nullptr, nullptr, kFixed);
             if (kFixed) {
+                uint32_t u[3];
                 fix_round3(l[1], l[2], l[3], u);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) l[k + 1] = fix_to_real(u[k]);
+                for (int k = 0; k < 3; ++k) l[k + 1] = (double)u[k];
             }
-            l[0] = 1.0 - l[1] - l[2] - l[3];
         }
         if (++j >= ma.nsteps) break;
         Real cf[kRowReals];
         const double *pr = ma.parts + (int64_t)T * (kRowParts<kSnap> * kRowReals);
 #pragma unroll
         for (int c = 0; c < kRowReals; ++c) cf[c] = (Real)row_entry<kSnap>(pr + c, kRowReals, ma.wc[j], ma.ws[j]);
-        gather_boris<Real>(cf, a.geo + (int64_t)T * GeoRow<Real>::kStride, l, a.h, v);
-        if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]))) atomicOr(a.status, (unsigned)ETPIC_DEV_NAN);
-        double dl[4];
-        walks = !increments<Real>(a.gpush + (int64_t)T * PushRow<Real>::kStride, v, a.dt_r, l, dl);
+        Real gm[9], gr[9];
+        load_rows<Real, kFixed>(a, T, gm, gr);
+        const Real x[3] = {(Real)l[1], (Real)l[2], (Real)l[3]};
+        gather_boris(cf, gm, x, a.h, v);
+        double dl[4], t[4];
+        walks = !increments(gr, v, a.dt_r, kOne<kFixed>, l, dl, t);
         if (!walks) {
-            stay_step<kFixed>(l, dl, u, s);
+            stay_step<kFixed>(l, dl, t, s);
             some = true;
+        } else if (!(isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]))) {
+            atomicOr(a.status, (unsigned)ETPIC_DEV_NAN);
         }
     }
     flush();
     a.tet[p] = T;
-    if (kFixed) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) fl[k][p] = u[k];
-    } else {
-        a.lam1[p] = l[1];
-        a.lam2[p] = l[2];
-        a.lam3[p] = l[3];
+    for (int k = 0; k < 3; ++k) {
+        if (kFixed) {
+            fl[k][p] = (uint32_t)l[k + 1];
+            l[k + 1] *= kFix;
+        } else {
+            lam[k][p] = l[k + 1];
+        }
     }
     a.v0[p] = v[0];
     a.v1[p] = v[1];
     a.v2[p] = v[2];
     if (a.rho) {
         const TetTopo tp = a.topo[T];
+        l[0] = 1.0 - l[1] - l[2] - l[3];
 #pragma unroll
         for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&a.rho[tp.v[k]], a.qw * l[k]);
     }
