@@ -115,3 +115,34 @@ def test_coarse_launch_split_changes_nothing(E, torch_cuda, n, ordered, precisio
     same_state(p1.to_numpy(), p2.to_numpy())
     assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,ordered,nsteps,dt_scale,edc,by_slice", [
+    (1, True, 5, 1.0, False, False), (65, False, 20, 300.0, True, False), (1000, False, 21, 300.0, False, True),
+    (40_001, True, 13, 300.0, True, False)])
+def test_downshifted_launch_split_changes_nothing(E, torch_cuda, n, ordered, nsteps, dt_scale, edc, by_slice, precision):
+    """One call from an empty history (three one-step launches, then up to 16
+    steps each) against one call per step: identical particles and history,
+    currents and charge to the rounding of their sums."""
+    torch = torch_cuda
+    w, ctx, f, sp, p1 = problem(E, torch, n, precision, ordered)
+    if edc:
+        f = E.Fields.from_numpy(w.e_env, w.b_env, 0.3 * w.e_env.real, w.b_dc)
+    p2 = p1.clone()
+    h1, h2 = ctx.ds_history(p1), ctx.ds_history(p2)
+    dt = w.dt * dt_scale
+    flags = E.STEP_XCD_REMAP | (E.STEP_WALK_BY_SLICE if by_slice else 0)
+    g1 = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    g2 = torch.zeros_like(g1)
+    rho1 = torch.zeros(ctx.n_vert, dtype=torch.float64, device="cuda")
+    rho2 = torch.zeros_like(rho1)
+    ctx.ds_steps(p1, h1, sp, f, 6, nsteps, 0, dt, w.omega, g1, rho=rho1, flags=flags)
+    for j in range(nsteps):
+        ctx.ds_steps(p2, h2, sp, f, 6 + j, 1, j, dt, w.omega, g2, rho=rho2 if j == nsteps - 1 else None, flags=flags)
+    ctx.check()
+    same_state(p1.to_numpy(), p2.to_numpy())
+    assert torch.equal(h1, h2)
+    assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    assert torch.allclose(rho1, rho2, rtol=0, atol=1e-13 * rho2.abs().max().item())
+    ctx.close()
