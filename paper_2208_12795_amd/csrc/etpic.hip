@@ -100,7 +100,9 @@ constexpr unsigned kWalkBlocks = 64;
 // launch's steps
 constexpr unsigned kLeaverBlocks = 512;
 constexpr int64_t kFewParticles = 2 * 1024 * 16;   // two 16-particle wavefronts on each of 256 CUs x 4 SIMDs
-constexpr unsigned kCtrStride = 64;           // walk-counter sets on lines of their own
+// walk-counter sets, on lines of their own: 0 one step per launch, 1 and 2
+// alternating several, 3 and 4 alternating the reverse sweep
+constexpr unsigned kCtrSets = 5, kCtrStride = 64;
 constexpr int64_t kMinPushWaves = 16384;      // 256 CUs x 64 wavefronts
 constexpr int64_t kInfinityCacheBytes = (int64_t)256 << 20;
 constexpr int64_t kFloatRowBytes = 48 + 64 + 48;   // float coefficient, push and geometry rows per tet
@@ -378,11 +380,10 @@ __device__ __forceinline__ void half_row(int face, const double z[6], const doub
     }
 }
 
-// What a coefficient pass writes per tet: the reverse sweep's 24 reals (A_0..3,
-// C_0..3 of one step), the particle step's 10 reals of one step (CoefRow), or
-// the parts of the 10-real row (kRowParts * 10 float64) from which a
-// multi-step launch forms the row of each of its steps.
-enum CoefMode { kCoefFull, kCoefStep, kCoefParts };
+// What a coefficient pass writes per tet: the particle step's 10 reals of one
+// step (CoefRow), or the parts of the 10-real row (kRowParts * 10 float64)
+// from which a multi-step launch forms the row of each of its steps.
+enum CoefMode { kCoefStep, kCoefParts };
 
 template <typename Real, int kSnap, int kMode>
 __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ prow,
@@ -398,9 +399,9 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
     // lanes' rows start in different banks.
     constexpr int kTets = kBlock / 2;
     constexpr int kRow = PushRow<double>::kStride + 1;   // staged push row, doubles
-    constexpr int kOut = kMode == kCoefFull ? 25 : 11;   // staged coefficient row, Reals
-    constexpr int kPart0 = kMode == kCoefFull ? 12 : 6, kPart1 = kMode == kCoefFull ? 12 : 4;   // reals of each half
-    constexpr int kOutRow = kMode == kCoefFull ? 24 : CoefRow<Real>::kStride;   // row in memory, Reals
+    constexpr int kOut = 11;                             // staged coefficient row, Reals
+    constexpr int kPart0 = 6, kPart1 = 4;                // reals of each half
+    constexpr int kOutRow = CoefRow<Real>::kStride;      // row in memory, Reals
     constexpr int kIn = kTets * kRow + kTets * 4 / 2;    // rows + face ids, in doubles
     constexpr int kOutD = (kTets * kOut * (int)sizeof(Real) + 7) / 8;
     __shared__ double lds[kIn > kOutD ? kIn : kOutD];
@@ -444,71 +445,7 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
         id[4] = re[4];
         id[5] = re[5];
     }
-    if constexpr (kMode == kCoefFull) {
-        double o[12];
-        // the DoFs first, all gathers in flight together (each edge serves
-        // two of the A_k, each face three of the C_k), then the sums in the
-        // order and with the operations of coef_A / coef_C
-        if (act && part == 0) {
-            double ev[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                const double2 z = F.e_env[0][id[k]];
-                ev[k] = z.x * F.c - z.y * F.s;
-            }
-            if (F.e_dc)
-#pragma unroll
-                for (int k = 0; k < 6; ++k) ev[k] += F.e_dc[id[k]];
-#pragma unroll
-            for (int K = 0; K < 4; ++K) {
-                double *A = o + 3 * K;
-                A[0] = A[1] = A[2] = 0.0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j == K) continue;
-                    double eps = ev[local_edge(j < K ? j : K, j < K ? K : j)];
-                    if (j < K) eps = -eps;
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) A[d] += eps * g[j][d];
-                }
-            }
-        } else if (act) {
-            double bv[4];
-#pragma unroll
-            for (int f = 0; f < 4; ++f) {
-                const double2 z = F.b_env[0][id[f]];
-                bv[f] = z.x * F.c - z.y * F.s;
-            }
-            if (F.b_dc)
-#pragma unroll
-                for (int f = 0; f < 4; ++f) bv[f] += F.b_dc[id[f]];
-            constexpr int lf[4][3] = {{1, 2, 3}, {0, 2, 3}, {0, 1, 3}, {0, 1, 2}};
-#pragma unroll
-            for (int K = 0; K < 4; ++K) {
-                double *Cv = o + 3 * K;
-                Cv[0] = Cv[1] = Cv[2] = 0.0;
-#pragma unroll
-                for (int f = 0; f < 4; ++f) {
-                    if (f == K) continue;
-                    const int a = lf[f][0] == K ? lf[f][1] : (lf[f][1] == K ? lf[f][2] : lf[f][0]);
-                    const int b = lf[f][0] == K ? lf[f][2] : (lf[f][1] == K ? lf[f][0] : lf[f][1]);
-                    const double beta = bv[f] * 2.0;
-                    Cv[0] += beta * (g[a][1] * g[b][2] - g[a][2] * g[b][1]);
-                    Cv[1] += beta * (g[a][2] * g[b][0] - g[a][0] * g[b][2]);
-                    Cv[2] += beta * (g[a][0] * g[b][1] - g[a][1] * g[b][0]);
-                }
-            }
-        }
-        __syncthreads();   // every staged row read: the space takes the output
-        Real *sout = reinterpret_cast<Real *>(lds);
-        if (act) {
-#pragma unroll
-            for (int d = 0; d < 12; ++d) sout[t * kOut + 12 * part + d] = (Real)o[d];
-        }
-        __syncthreads();
-        Real *dst = coef + T0 * kOutRow;
-        for (int i = threadIdx.x; i < nloc * kOutRow; i += kBlock) dst[i] = sout[i / kOutRow * kOut + i % kOutRow];
-    } else {
+    {
         // parts of the row, one after the other: real and imaginary part of
         // each snapshot, then dc
         constexpr int kParts = kRowParts<kSnap>;
@@ -1718,12 +1655,13 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     const int64_t b0 = ((int64_t)blk * kWaves + wv) * ma.width;
     if (b0 >= a.n) return;   // the whole wavefront; no block barrier below
     const int64_t p = b0 + ln;
-    int T = -1;
+    int T = -1, stored = -1;
     double l[4] = {0.0, 0.0, 0.0, 0.0};   // l[0] unused: lam0 is implicit
     uint32_t u[3] = {0, 0, 0};
     Real v[3] = {0, 0, 0};
-    if (p < a.n && (int)ln < ma.width) {
-        T = __builtin_nontemporal_load(lane_at(a.tet + b0, ln));
+    const bool here = p < a.n && (int)ln < ma.width;
+    if (here) {
+        T = stored = __builtin_nontemporal_load(lane_at(a.tet + b0, ln));
         if (kFixed) {
             u[0] = __builtin_nontemporal_load(lane_at(reinterpret_cast<uint32_t *>(a.lam1) + b0, ln));
             u[1] = __builtin_nontemporal_load(lane_at(reinterpret_cast<uint32_t *>(a.lam2) + b0, ln));
@@ -1747,8 +1685,10 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     }
     const bool act = T >= 0;
     const WaveRuns runs = wave_runs(T, ln);
-    unsigned dq = 0;   // scatter form: the sorted position, one cursor atomic per run
-    if (kScatter) {
+    // scatter form: the sorted position, one cursor atomic per run; without
+    // cursors the particles keep their places in the other arrays
+    unsigned dq = (unsigned)p;
+    if (kScatter && a.cursor) {
         unsigned base = 0;
         if (runs.head && act) base = atomicAdd(&a.cursor[T], (unsigned)(runs.run_end - runs.lane + 1));
         base = __shfl(base, runs.head_lane);
@@ -1836,7 +1776,9 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         }
     }
     const bool left = leave >= 0;
-    if (act) {
+    // (a particle without a valid tet has no sorted place; one that keeps its
+    // place is copied as it is)
+    if (act || (kScatter && !a.cursor && here)) {
         const int64_t q = kScatter ? (int64_t)dq : p;
         if (kScatter) {
             if (kFixed) {
@@ -1851,7 +1793,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
             __builtin_nontemporal_store(v[0], &a.o_v0[q]);
             __builtin_nontemporal_store(v[1], &a.o_v1[q]);
             __builtin_nontemporal_store(v[2], &a.o_v2[q]);
-            a.o_tet[q] = left ? leaver_mark(T, leave, a.nt) : T;
+            a.o_tet[q] = left ? leaver_mark(T, leave, a.nt) : stored;
             if (a.id) __builtin_nontemporal_store(__builtin_nontemporal_load(&a.id[p]), &a.o_id[q]);
         } else {
             if (kFixed) {
@@ -1880,9 +1822,9 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
 #pragma unroll
         for (int k = 1; k < 4; ++k) r4[k] = run_total(act && !left ? l[k] : 0.0, runs);
         // lam_0 sums to the number of the run's particles that stayed less the rest
-        const unsigned long long here = __ballot(act && !left);
+        const unsigned long long stayed = __ballot(act && !left);
         const unsigned long long upto = ln == 63 ? ~0ull : ((2ull << ln) - 1ull);
-        r4[0] = (double)__popcll(here & upto & ~((1ull << runs.head_lane) - 1ull)) - r4[1] - r4[2] - r4[3];
+        r4[0] = (double)__popcll(stayed & upto & ~((1ull << runs.head_lane) - 1ull)) - r4[1] - r4[2] - r4[3];
         if (flush) {
             const TetTopo *tp = a.topo + T;
 #pragma unroll
@@ -2553,165 +2495,343 @@ __global__ void __launch_bounds__(kBlock) k_walk_ds(StepArgs<Real> a, DsArgs<Rea
 }
 
 // ------------------------------------------------------------------ adjoint step
-// Reverse of one float64 step for every particle, given the state before the
-// step (recomputed from a checkpoint) and the adjoints of the state after it.
+// Reverse of float64 steps for every particle, given the state before the
+// first of them (a checkpoint) and the adjoints of the state after the last.
 // Recomputes gather, Boris and the walk's reflections, then back-propagates:
 //   x_{k+1} = R (x_k + dt v+) + const, v_{k+1} = R v+         (walk, reflections R)
 //   v+ = Boris(v_k, E, B)                                        (vjp written out)
-//   E = sum_i l_i(x) A_i, B = sum_i l_i(x) C_i                  (affine in x)
+//   E = A_0 + beta x u, B = C_0 + b u, u = x - r_0
 // and accumulates the gradient with respect to the complex edge envelope,
 // dL/dRe e_e + j dL/dIm e_e = (Ebar . W1_e(x_k)) e^{-j w t_k}, reduced over runs
 // of equal tet before the float64 atomics.
+constexpr int kMaxAdj = 5;   // steps reversed per launch: their states fill the LDS left beside the rows
+
+__global__ void __launch_bounds__(kBlock) k_copy_state(etpic_particles src, etpic_particles dst) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= src.n) return;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        dst.lam[k][p] = src.lam[k][p];
+        static_cast<double *>(dst.vel[k])[p] = static_cast<const double *>(src.vel[k])[p];
+    }
+    dst.tet[p] = src.tet[p];
+}
+
 struct AdjArgs {
-    const double *lam1, *lam2, *lam3;
-    const double *v0, *v1, *v2;
+    const double *parts;             // row parts (k_tet_coef, kCoefParts)
+    const double *lam[3], *v[3];     // the state before the launch's first step
     const int32_t *tet;
-    double *vb0, *vb1, *vb2;
-    double *xb0, *xb1, *xb2;
+    double *vb[3], *xb[3];
     double *grad_e;
-    double c, s, dt;
+    int64_t first, end;              // particles [first, end) of this launch
+    int nsteps;                      // at most kMaxAdj
+    double c[kMaxAdj], s[kMaxAdj];   // cos, sin of the carrier phase of each step
+    // per-step states of the particles that leave their tet (k_adjoint_leavers)
+    double *s_lam[kMaxAdj][3], *s_v[kMaxAdj][3];
+    int32_t *s_tet[kMaxAdj];
 };
 
-__global__ void __launch_bounds__(kBlock) k_adjoint(StepArgs<double> a, AdjArgs b) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Reverse of one step from the state (l, v) before it: xb, vb in: adjoints of
+// the end point and velocity, out: of the start point and velocity.  R: the
+// step's reflections (null: none).  w: the envelope gradient's six sums, w[0..2]
+// = Eb . grad l_k, w[3..5] = l_i Eb . grad l_k - l_k Eb . grad l_i for (i,k) =
+// (1,2), (1,3), (2,3) (edge_sums turns them into Eb . W1_e).
+__device__ __forceinline__ void adjoint_step(const double *cf, const double *gm, const double *gr, const double l[4],
+                                             const double v[3], double h, double dt, const double *R, double xb[3],
+                                             double vb[3], double w[6]) {
+    double u[3], E[3], vm[3], tau[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) u[d] = fma(l[3], gm[6 + d], fma(l[2], gm[3 + d], l[1] * gm[d]));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        E[d] = fma(cf[3 + p], u[q], fma(-cf[3 + q], u[p], cf[d]));
+        tau[d] = h * fma(cf[9], u[d], cf[6 + d]);
+        vm[d] = fma(h, E[d], v[d]);
+    }
+    const double sg = two_over(fma(tau[0], tau[0], fma(tau[1], tau[1], fma(tau[2], tau[2], 1.0))));
+    double vr[3], sig[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        vr[d] = fma(vm[p], tau[q], fma(-vm[q], tau[p], vm[d]));
+        sig[d] = sg * tau[d];
+    }
+    double ob[3];
+    if (R) {
+        double xr[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            ob[i] = xr[i] = 0.0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                ob[i] = fma(R[3 * j + i], fma(dt, xb[j], vb[j]), ob[i]);
+                xr[i] = fma(R[3 * j + i], xb[j], xr[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) xb[i] = xr[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) ob[i] = fma(dt, xb[i], vb[i]);
+    }
+    // out = vm + vr x sig + h E, vr = vm + vm x tau, sig = 2 tau / (1 + |tau|^2)
+    double vrb[3], sigb[3], vmb[3], taub[3], Eb[3], Bb[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        vrb[d] = fma(sig[p], ob[q], -(sig[q] * ob[p]));
+        sigb[d] = fma(ob[p], vr[q], -(ob[q] * vr[p]));
+    }
+    const double st = fma(sigb[0], tau[0], fma(sigb[1], tau[1], sigb[2] * tau[2]));
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        vmb[d] = ob[d] + fma(tau[p], vrb[q], fma(-tau[q], vrb[p], vrb[d]));
+        // d sig / d tau: sg I - sg^2 tau tau^T
+        taub[d] = fma(vrb[p], vm[q], fma(-vrb[q], vm[p], sg * fma(-st * sg, tau[d], sigb[d])));
+        Eb[d] = h * (ob[d] + vmb[d]);
+        Bb[d] = h * taub[d];
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const int p = (d + 1) % 3, q = (d + 2) % 3;
+        vb[d] = vmb[d];
+        // E = A_0 + beta x u, B = C_0 + b u
+        xb[d] += fma(cf[9], Bb[d], fma(Eb[p], cf[3 + q], -(Eb[q] * cf[3 + p])));
+    }
+    double eg[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        eg[k] = fma(Eb[2], gr[3 * k + 2], fma(Eb[1], gr[3 * k + 1], Eb[0] * gr[3 * k]));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = eg[k];
+    w[3] = fma(l[1], eg[1], -(l[2] * eg[0]));
+    w[4] = fma(l[1], eg[2], -(l[3] * eg[0]));
+    w[5] = fma(l[2], eg[2], -(l[3] * eg[1]));
+}
+
+// The reverse of up to kMaxAdj steps per launch, one lane per particle, one
+// wavefront per block: the steps are first taken forward from the state before
+// them (bit for bit as the run took them), each step's start kept in LDS, then
+// reversed with the adjoints in registers; the gradient sums of the tet's
+// edges gather over the steps and are reduced over runs of equal tet once.
+// Rows are formed from the staged parts as in k_push_multi.  A particle that
+// leaves its tet in one of the steps is left to k_adjoint_leavers.
+__global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
+    constexpr int kParts = kRowParts<1>;
+    constexpr int kRuns = 16;
+    constexpr int kEnt = kRuns * kRowReals;
+    __shared__ double part[kParts * kEnt];
+    __shared__ __align__(16) double rows[kEnt];
+    __shared__ double s_state[kMaxAdj][6][64];
+    __shared__ int s_tet[64];
+    const unsigned ln = threadIdx.x;
+    const int64_t p = b.first + (int64_t)xcd_block(blockIdx.x, gridDim.x) * 64 + ln;
     int T = -1;
-    if (p < a.n) {
+    if (p < b.end) {
         T = b.tet[p];
         if ((unsigned)T >= (unsigned)a.nt) {
             atomicOr(a.status, (unsigned)ETPIC_DEV_BADTET);
             T = -1;
         }
     }
-    double ge[12];
+    const bool act = T >= 0;
+    double l[4] = {0.0, 0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0}, xb[3] = {0.0, 0.0, 0.0}, vb[3] = {0.0, 0.0, 0.0};
+    if (act) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) ge[k] = 0.0;
-    if (T >= 0) {
-        double l[4];
-        l[1] = b.lam1[p];
-        l[2] = b.lam2[p];
-        l[3] = b.lam3[p];
-        l[0] = 1.0 - l[1] - l[2] - l[3];
-        const double v[3] = {b.v0[p], b.v1[p], b.v2[p]};
-        const double *cf = a.coef + (int64_t)T * 24;
-        double E[3], B[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            E[d] = l[0] * cf[d] + l[1] * cf[3 + d] + l[2] * cf[6 + d] + l[3] * cf[9 + d];
-            B[d] = l[0] * cf[12 + d] + l[1] * cf[15 + d] + l[2] * cf[18 + d] + l[3] * cf[21 + d];
+        for (int k = 0; k < 3; ++k) {
+            l[k + 1] = b.lam[k][p];
+            v[k] = b.v[k][p];
+            xb[k] = b.xb[k][p];
+            vb[k] = b.vb[k][p];
         }
-        const double h = a.h;
-        double vm[3], tau[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            vm[d] = v[d] + h * E[d];
-            tau[d] = h * B[d];
-        }
-        const double t2 = tau[0] * tau[0] + tau[1] * tau[1] + tau[2] * tau[2];
-        const double den = 1.0 + t2;
-        const double sg = 2.0 / den;
-        const double vr[3] = {vm[0] + (vm[1] * tau[2] - vm[2] * tau[1]), vm[1] + (vm[2] * tau[0] - vm[0] * tau[2]),
-                              vm[2] + (vm[0] * tau[1] - vm[1] * tau[0])};
-        double out[3];
-        out[0] = vm[0] + sg * (vr[1] * tau[2] - vr[2] * tau[1]) + h * E[0];
-        out[1] = vm[1] + sg * (vr[2] * tau[0] - vr[0] * tau[2]) + h * E[1];
-        out[2] = vm[2] + sg * (vr[0] * tau[1] - vr[1] * tau[0]) + h * E[2];
-        // reflections of this step (identity unless the particle left its tet)
-        double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
-        const double dx[3] = {a.dt_r * out[0], a.dt_r * out[1], a.dt_r * out[2]};
-        const double *gp = a.grad + (int64_t)T * 12;
-        double g[4][3];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) g[k][d] = gp[3 * k + d];
-        {
-            const double *gr = a.gpush + (int64_t)T * PushRow<double>::kStride;
-            double dl[4];
-#pragma unroll
-            for (int k = 1; k < 4; ++k) dl[k] = gr[3 * k - 3] * dx[0] + gr[3 * k - 2] * dx[1] + gr[3 * k - 1] * dx[2];
-            dl[0] = -(dl[1] + dl[2] + dl[3]);
-            const bool stays = (l[0] + dl[0] >= 0.0) && (l[1] + dl[1] >= 0.0) && (l[2] + dl[2] >= 0.0) &&
-                               (l[3] + dl[3] >= 0.0);
-            if (!stays) {
-                double lw[4] = {l[0], l[1], l[2], l[3]};
-                double dw[3] = {dx[0], dx[1], dx[2]};
-                double vw[3] = {out[0], out[1], out[2]};
-                walk<double, true>(a, T, lw, dw, vw, R);
-            }
-        }
-        const double xb[3] = {b.xb0[p], b.xb1[p], b.xb2[p]};
-        const double vb[3] = {b.vb0[p], b.vb1[p], b.vb2[p]};
-        double ob[3], xk[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            ob[i] = 0.0;
-            xk[i] = 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                ob[i] += R[3 * j + i] * (vb[j] + a.dt_r * xb[j]);
-                xk[i] += R[3 * j + i] * xb[j];
-            }
-        }
-        // Boris vjp: out = vm + vr x sig + h E, vr = vm + vm x tau, sig = 2 tau / (1 + |tau|^2)
-        const double sig[3] = {sg * tau[0], sg * tau[1], sg * tau[2]};
-        double Eb[3], Bb[3], vmb[3], vrb[3], sigb[3], taub[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            vmb[d] = ob[d];
-            Eb[d] = h * ob[d];
-        }
-        vrb[0] = sig[1] * ob[2] - sig[2] * ob[1];
-        vrb[1] = sig[2] * ob[0] - sig[0] * ob[2];
-        vrb[2] = sig[0] * ob[1] - sig[1] * ob[0];
-        sigb[0] = ob[1] * vr[2] - ob[2] * vr[1];
-        sigb[1] = ob[2] * vr[0] - ob[0] * vr[2];
-        sigb[2] = ob[0] * vr[1] - ob[1] * vr[0];
-        vmb[0] += vrb[0] + (tau[1] * vrb[2] - tau[2] * vrb[1]);
-        vmb[1] += vrb[1] + (tau[2] * vrb[0] - tau[0] * vrb[2]);
-        vmb[2] += vrb[2] + (tau[0] * vrb[1] - tau[1] * vrb[0]);
-        taub[0] = vrb[1] * vm[2] - vrb[2] * vm[1];
-        taub[1] = vrb[2] * vm[0] - vrb[0] * vm[2];
-        taub[2] = vrb[0] * vm[1] - vrb[1] * vm[0];
-        const double st = sigb[0] * tau[0] + sigb[1] * tau[1] + sigb[2] * tau[2];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            taub[d] += 2.0 * sigb[d] / den - 4.0 * st * tau[d] / (den * den);
-            Bb[d] = h * taub[d];
-            Eb[d] += h * vmb[d];
-        }
-        // gather vjp: position and edge DoFs
-        double Eg[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double ae = cf[3 * k] * Eb[0] + cf[3 * k + 1] * Eb[1] + cf[3 * k + 2] * Eb[2];
-            const double cb = cf[12 + 3 * k] * Bb[0] + cf[12 + 3 * k + 1] * Bb[1] + cf[12 + 3 * k + 2] * Bb[2];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) xk[d] += g[k][d] * (ae + cb);
-            Eg[k] = Eb[0] * g[k][0] + Eb[1] * g[k][1] + Eb[2] * g[k][2];
-        }
-        constexpr int le[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
-#pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            const double we = l[le[e][0]] * Eg[le[e][1]] - l[le[e][1]] * Eg[le[e][0]];
-            ge[2 * e] = we * b.c;
-            ge[2 * e + 1] = -we * b.s;
-        }
-        b.vb0[p] = vmb[0];
-        b.vb1[p] = vmb[1];
-        b.vb2[p] = vmb[2];
-        b.xb0[p] = xk[0];
-        b.xb1[p] = xk[1];
-        b.xb2[p] = xk[2];
     }
-    const WaveRuns runs = wave_runs(T);
+    double gm[9], gr[9];
+    load_rows<double, false>(a, max(T, 0), gm, gr);
+    const WaveRuns runs = wave_runs(T, ln);
+    const unsigned long long upto = ln == 63 ? ~0ull : ((2ull << ln) - 1ull);
+    const unsigned long long heads = __ballot(runs.head);
+    const int nruns = __popcll(heads), run = __popcll(heads & upto) - 1;
+    if (runs.head) s_tet[run] = T;
+    bool left = false;
+    double gc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, gs[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int r0 = 0; r0 < nruns; r0 += kRuns) {
+        const int nr = min(kRuns, nruns - r0), entries = nr * kRowReals;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = ln; i < nr * kParts * kRowReals; i += 64) {
+            const int j = i / (kParts * kRowReals), rem = i - j * (kParts * kRowReals);
+            const int q = rem / kRowReals, c = rem - q * kRowReals;
+            const int Tj = s_tet[r0 + j];
+            part[q * kEnt + j * kRowReals + c] = Tj >= 0 ? b.parts[(int64_t)Tj * (kParts * kRowReals) + rem] : 0.0;
+        }
+        const bool mine = act && run >= r0 && run < r0 + nr;
+        const double *cf = rows + (mine ? (run - r0) * kRowReals : 0);
+        auto form_rows = [&](int j) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int e = ln; e < entries; e += 64) rows[e] = row_entry<1>(part + e, kEnt, &b.c[j], &b.s[j]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        bool live = mine;
+#pragma unroll 1
+        for (int j = 0; j < b.nsteps; ++j) {
+            form_rows(j);
+            if (live) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) ge[k] = run_total(ge[k], runs);
-    if (T >= 0 && runs.lane == runs.run_end) {
-        const TetTopo *tp = a.topo + T;
+                for (int k = 0; k < 3; ++k) {
+                    s_state[j][k][ln] = l[k + 1];
+                    s_state[j][3 + k][ln] = v[k];
+                }
+                const double x[3] = {l[1], l[2], l[3]};
+                double dl[4], t[4];
+                gather_boris(cf, gm, x, a.h, v);
+                if (increments(gr, v, a.dt_r, 1.0, l, dl, t)) {
+#pragma unroll
+                    for (int k = 1; k < 4; ++k) l[k] = t[k];
+                } else {
+                    left = true;
+                    live = false;
+                }
+            }
+        }
+#pragma unroll 1
+        for (int j = b.nsteps - 1; j >= 0; --j) {
+            if (j != b.nsteps - 1) form_rows(j);   // the last step's rows are still there
+            if (live) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    l[k + 1] = s_state[j][k][ln];
+                    v[k] = s_state[j][3 + k][ln];
+                }
+                double w[6];
+                adjoint_step(cf, gm, gr, l, v, a.h, a.dt_r, nullptr, xb, vb, w);
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+                    gc[e] = fma(w[e], b.c[j], gc[e]);
+                    gs[e] = fma(w[e], -b.s[j], gs[e]);
+                }
+            }
+        }
+    }
+    if (act && !left) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            b.vb[k][p] = vb[k];
+            b.xb[k][p] = xb[k];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 6; ++e) {
+        gc[e] = run_total(gc[e], runs);
+        gs[e] = run_total(gs[e], runs);
+    }
+    if (act && runs.lane == runs.run_end) {
+        double re[6], im[6];
+        edge_sums(gc, re);
+        edge_sums(gs, im);
+        const int32_t *ed = push_row_edges(a.gpush + (int64_t)T * PushRow<double>::kStride);
 #pragma unroll
         for (int e = 0; e < 6; ++e) {
-            unsafeAtomicAdd(&b.grad_e[2 * (int64_t)tp->e[e]], ge[2 * e]);
-            unsafeAtomicAdd(&b.grad_e[2 * (int64_t)tp->e[e] + 1], ge[2 * e + 1]);
+            unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e]], re[e]);
+            unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e] + 1], im[e]);
+        }
+    }
+    // a launch takes at most kWalkQueueCap particles: the queue holds them all
+    const unsigned long long wmask = __ballot(left);
+    if (wmask) {
+        unsigned base = 0;
+        if (ln == 0) base = atomicAdd(&a.walk_ctr[0], (unsigned)__popcll(wmask));
+        base = __shfl(base, 0);
+        if (left) a.walk_queue[base + (unsigned)__popcll(wmask & (upto >> 1))] = (unsigned)p;
+    }
+}
+
+// The same for the queued particles, one lane each: forward through their
+// walks with every step's start kept in the segment's state slots, then back,
+// each step's reflections recomputed and its gradient added edge by edge.
+__global__ void __launch_bounds__(kBlock) k_adjoint_leavers(StepArgs<double> a, AdjArgs b, unsigned *next_ctr) {
+    if (blockIdx.x == 0 && threadIdx.x < 3) next_ctr[threadIdx.x] = 0u;
+    const unsigned count = min(__atomic_load_n(&a.walk_ctr[0], __ATOMIC_RELAXED), kWalkQueueCap);
+    for (unsigned i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
+        const int64_t p = a.walk_queue[i];
+        if (p >= b.end) continue;
+        int T = b.tet[p];
+        double l[4], v[3], xb[3], vb[3];
+        l[0] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            l[k + 1] = b.lam[k][p];
+            v[k] = b.v[k][p];
+            xb[k] = b.xb[k][p];
+            vb[k] = b.vb[k][p];
+        }
+        auto row_at = [&](int j, double cf[kRowReals]) {
+            const double *pr = b.parts + (int64_t)T * (kRowParts<1> * kRowReals);
+#pragma unroll
+            for (int c = 0; c < kRowReals; ++c) cf[c] = row_entry<1>(pr + c, kRowReals, &b.c[j], &b.s[j]);
+        };
+#pragma unroll 1
+        for (int j = 0; j < b.nsteps; ++j) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                b.s_lam[j][k][p] = l[k + 1];
+                b.s_v[j][k][p] = v[k];
+            }
+            b.s_tet[j][p] = T;
+            if (j == b.nsteps - 1) break;   // the last step's end is not needed
+            double cf[kRowReals], gm[9], gr[9], dl[4], t[4];
+            row_at(j, cf);
+            load_rows<double, false>(a, T, gm, gr);
+            const double x[3] = {l[1], l[2], l[3]};
+            gather_boris(cf, gm, x, a.h, v);
+            if (increments(gr, v, a.dt_r, 1.0, l, dl, t)) {
+#pragma unroll
+                for (int k = 1; k < 4; ++k) l[k] = t[k];
+            } else {
+                double d[3] = {a.dt_r * v[0], a.dt_r * v[1], a.dt_r * v[2]};
+                double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};   // not needed yet
+                T = walk<double, true>(a, T, l, d, v, R);
+            }
+        }
+#pragma unroll 1
+        for (int j = b.nsteps - 1; j >= 0; --j) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                l[k + 1] = b.s_lam[j][k][p];
+                v[k] = b.s_v[j][k][p];
+            }
+            T = b.s_tet[j][p];
+            double cf[kRowReals], gm[9], gr[9], dl[4], t[4];
+            row_at(j, cf);
+            load_rows<double, false>(a, T, gm, gr);
+            // reflections of this step (identity unless the particle left its tet)
+            double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+            const double x[3] = {l[1], l[2], l[3]};
+            double out[3] = {v[0], v[1], v[2]};
+            gather_boris(cf, gm, x, a.h, out);
+            if (!increments(gr, out, a.dt_r, 1.0, l, dl, t)) {
+                double d[3] = {a.dt_r * out[0], a.dt_r * out[1], a.dt_r * out[2]};
+                double lw[4] = {0.0, l[1], l[2], l[3]};
+                walk<double, true>(a, T, lw, d, out, R);
+            }
+            double w[6], g6[6];
+            adjoint_step(cf, gm, gr, l, v, a.h, a.dt_r, R, xb, vb, w);
+            edge_sums(w, g6);
+            const int32_t *ed = push_row_edges(a.gpush + (int64_t)T * PushRow<double>::kStride);
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e]], g6[e] * b.c[j]);
+                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e] + 1], -(g6[e] * b.s[j]));
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            b.vb[k][p] = vb[k];
+            b.xb[k][p] = xb[k];
         }
     }
 }
@@ -3895,8 +4015,7 @@ struct etpic_ctx {
     double *d_geo64 = nullptr;        // nt rows of GeoRow<double>
     float *d_geo32 = nullptr;         // nt rows of GeoRow<float>
     int32_t *d_tetface = nullptr;     // nt*4 face ids (face k opposite vertex k)
-    void *d_coef = nullptr;          // nt*kCoefDoubles doubles: a step's CoefRow rows, a call's row parts, or
-                                     // A_0..3, C_0..3 for the adjoint
+    void *d_coef = nullptr;          // nt*kCoefDoubles doubles: a step's CoefRow rows or a call's row parts
     double *d_coef_env = nullptr;    // nt*kEnvRow complex-envelope rows (bound by etpic_ds_rows_bind)
     int32_t *d_v2e_ptr = nullptr;
     int32_t *d_v2e_code = nullptr;
@@ -3911,7 +4030,7 @@ struct etpic_ctx {
     unsigned *d_status = nullptr;    // device status word
     unsigned *d_walk_queue = nullptr;  // kWalkQueueCap particle indices
     unsigned *d_slice_queue = nullptr; // kWalkQueueCap slice indices
-    unsigned *d_walk_ctr = nullptr;    // 3 sets of 3 walk-queue counters: one step per launch; several, alternating
+    unsigned *d_walk_ctr = nullptr;    // kCtrSets sets of 3 walk-queue counters
     unsigned long long *d_red = nullptr;  // 2 words for the residual maxima
     double *d_scratch = nullptr;          // device address of `scratch` on this device
     // mean same-tet run length from the last sort (sum count^2 / N_p), read
@@ -4189,19 +4308,18 @@ struct etpic_ctx {
             if (int r = sort_count(src, st)) return r;
         constexpr uint32_t kForced =
             ETPIC_STEP_SLICES_1 | ETPIC_STEP_SLICES_2 | ETPIC_STEP_SLICES_4 | ETPIC_STEP_SLICES_16;
-        // a leaver's mark holds its tet and its step: both have to fit an int32
-        const int64_t most = std::min<int64_t>(kMaxFused, (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1));
+        const int most = most_fused();
         if (nsteps == 1 || most < 2 || (flags & kForced))
             return single_steps<Real>(p, sp, plans, nsteps, dt, omega, dG, rho, flags, st, src);
         if constexpr (std::is_same<Real, float>::value) {
             if (flags & kFlagFixed)
                 return plans[0].snap[1]
-                           ? fused_steps<float, 3, true>(p, sp, plans, nsteps, (int)most, dt, omega, dG, rho, flags, st, src)
-                           : fused_steps<float, 1, true>(p, sp, plans, nsteps, (int)most, dt, omega, dG, rho, flags, st, src);
+                           ? fused_steps<float, 3, true>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src)
+                           : fused_steps<float, 1, true>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src);
         }
         return plans[0].snap[1]
-                   ? fused_steps<Real, 3, false>(p, sp, plans, nsteps, (int)most, dt, omega, dG, rho, flags, st, src)
-                   : fused_steps<Real, 1, false>(p, sp, plans, nsteps, (int)most, dt, omega, dG, rho, flags, st, src);
+                   ? fused_steps<Real, 3, false>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src)
+                   : fused_steps<Real, 1, false>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src);
     }
 
     template <typename Real>
@@ -4246,10 +4364,33 @@ struct etpic_ctx {
         return used_slots ? launch_edges(dG, st, ta, nullptr) : ETPIC_OK;
     }
 
+    // Steps per multi-step launch: a leaver's mark holds its tet and its step,
+    // and both have to fit an int32.
+    int most_fused() const {
+        return (int)std::max<int64_t>(
+            1, std::min<int64_t>(kMaxFused, (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
+    }
+
+    // the parts of the 10-real rows, from which multi-step launches form the
+    // row of each of their steps
+    template <int kSnap>
+    int launch_parts(const etpic_fields *const snap[3], const double w[3], hipStream_t st, TimingSet *ta) {
+        FieldPtrs F = field_ptrs(snap, w, 1.0, 0.0);
+        F.xcd = coef_xcd();
+        launch_timed(k_tet_coef<double, kSnap, kCoefParts>, grid_for(2 * host.nt), st, ev_start(ta, 0), ev_stop(ta, 0),
+                     host.nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef));
+        HIP_TRY(hipGetLastError());
+        return ETPIC_OK;
+    }
+
+    // Multi-step launches of p.  With src, the first launch reads src and
+    // writes p: at the tet-sorted places (sorted), or place for place.
+    // parts_ready: the rows' parts are there from an earlier call with the
+    // same fields.
     template <typename Real, int kSnap, bool kFixed>
     int fused_steps(const etpic_particles *p, const etpic_species *sp, const StepPlan *plans, int nsteps, int most,
                     double dt, double omega, double *dG, double *rho, uint32_t flags, hipStream_t st,
-                    const etpic_particles *src) {
+                    const etpic_particles *src, bool sorted = true, bool parts_ready = false) {
         const int remap = (flags & ETPIC_STEP_XCD_REMAP) ? 1 : 0;
         const int64_t n = p->n, nt = host.nt;
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
@@ -4267,19 +4408,14 @@ struct etpic_ctx {
         for (int i = 0, j0 = 0; i < launches; ++i) {
             const int j1 = (int)((int64_t)nsteps * (i + 1) / launches);   // equal shares, at least two steps each
             TimingSet *ts = nullptr;
-            const bool sorts = i == 0 && src;
+            const bool moves = i == 0 && src;
             if (flags & (ETPIC_STEP_TIMING | ETPIC_STEP_TIMING_ALL)) {
-                if (int r = timing_events(&ts, sorts)) return r;
+                if (int r = timing_events(&ts, moves && sorted)) return r;
                 ts->steps = j1 - j0;
             }
             ta = time_all ? ts : nullptr;
-            if (i == 0) {
-                FieldPtrs F = field_ptrs(plans[0].snap, plans[0].w, 1.0, 0.0);
-                F.xcd = coef_xcd();
-                launch_timed(k_tet_coef<double, kSnap, kCoefParts>, grid_for(2 * nt), st, ev_start(ta, 0),
-                             ev_stop(ta, 0), nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef));
-                HIP_TRY(hipGetLastError());
-            }
+            if (i == 0 && !parts_ready)
+                if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, st, ta)) return r;
             MultiArgs<kSnap> ma{};
             ma.parts = static_cast<const double *>(d_coef);
             ma.nsteps = j1 - j0;
@@ -4299,9 +4435,13 @@ struct etpic_ctx {
             unsigned *next = d_walk_ctr + (1 + ((i + 1) & 1)) * kCtrStride;
             a.walk_ctr = ctr;
             hipEvent_t e0 = ev_start(ts, 1), e1 = ev_stop(ts, 1);
-            if (sorts) {
+            if (moves) {
                 StepArgs<Real> as = a;
                 scatter_from(as, p, src);
+                if (!sorted) {
+                    as.cursor = nullptr;
+                    as.id = nullptr;
+                }
                 if (as.rho)
                     launch_timed(k_push_multi<Real, kSnap, true, true, kFixed>, push_grid, st, e0, e1, as, ma, remap);
                 else
@@ -4387,14 +4527,10 @@ struct etpic_ctx {
         const int64_t n = p->n, nt = host.nt;
         if (!d_coef_env)
             return fail(ETPIC_ESTATE, "no downshifted rows bound (etpic_ds_rows_bytes, etpic_ds_rows_bind)");
-        // a leaver's mark holds its tet and its step: both have to fit an int32
-        const int most = (int)std::max<int64_t>(
-            1, std::min<int64_t>(kMaxDs, (INT32_MAX - 2) / std::max<int64_t>(nt, 1)));
+        const int most = std::min(kMaxDs, most_fused());
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
         const etpic_fields *snap[3] = {f, nullptr, nullptr};
         const double w1[3] = {1.0, 0.0, 0.0};
-        FieldPtrs F = field_ptrs(snap, w1, 1.0, 0.0);
-        F.xcd = coef_xcd();
         TimingSet *ta = nullptr;
         unsigned *ctr = nullptr;
         for (int j0 = 0, i = 0; j0 < nsteps; ++i) {
@@ -4408,13 +4544,13 @@ struct etpic_ctx {
             }
             ta = time_all ? ts : nullptr;
             if (i == 0) {
-                if constexpr (f64)
-                    launch_timed(k_tet_coef<double, 1, kCoefParts>, grid_for(2 * nt), st, ev_start(ta, 0),
-                                 ev_stop(ta, 0), nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef));
-                else
+                if constexpr (f64) {
+                    if (int r = launch_parts<1>(snap, w1, st, ta)) return r;
+                } else {
                     launch_timed(k_tet_coef_env, dim3(grid_for(nt), 6), st, ev_start(ta, 0), ev_stop(ta, 0), nt,
-                                 d_gpush64, d_tetface, F, d_coef_env);
-                HIP_TRY(hipGetLastError());
+                                 d_gpush64, d_tetface, field_ptrs(snap, w1, 1.0, 0.0), d_coef_env);
+                    HIP_TRY(hipGetLastError());
+                }
             }
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j0 + len == nsteps ? rho : nullptr);
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
@@ -4676,15 +4812,6 @@ etpic_particles state_view(void *ws, size_t off, const AdjLayout &L, int64_t n) 
     return q;
 }
 
-int copy_state(const etpic_particles &src, const etpic_particles &dst, int64_t n, hipStream_t st) {
-    for (int k = 0; k < 3; ++k) {
-        HIP_TRY(hipMemcpyAsync(dst.lam[k], src.lam[k], sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-        HIP_TRY(hipMemcpyAsync(dst.vel[k], src.vel[k], sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-    }
-    HIP_TRY(hipMemcpyAsync(dst.tet, src.tet, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
-    return ETPIC_OK;
-}
-
 int check_step_args(const etpic_ctx *ctx, const etpic_species *sp, const etpic_fields *f, double dt, double omega) {
     if (!ctx || !sp || !f) return fail(ETPIC_EINVAL, "null argument");
     if (!ctx->has_mesh) return fail(ETPIC_ESTATE, "no mesh uploaded");
@@ -4775,7 +4902,7 @@ struct WsPtrs {
 WsPtrs ws_layout(Carve &cv) {
     WsPtrs w;
     w.status = cv.take<unsigned>(1);
-    w.walk_ctr = cv.take<unsigned>(3 * kCtrStride);
+    w.walk_ctr = cv.take<unsigned>(kCtrSets * kCtrStride);
     w.red = cv.take<unsigned long long>(2);
     w.runstat = cv.take<unsigned long long>(1);
     w.walk_queue = cv.take<unsigned>(kWalkQueueCap);
@@ -4872,7 +4999,7 @@ int etpic_workspace_bind(etpic_ctx *ctx, void *dev_buf, size_t bytes) {
     ctx->d_walk_queue = w.walk_queue;
     ctx->d_slice_queue = w.slice_queue;
     HIP_TRY(hipMemset(ctx->d_status, 0, sizeof(unsigned)));
-    HIP_TRY(hipMemset(ctx->d_walk_ctr, 0, 3 * kCtrStride * sizeof(unsigned)));
+    HIP_TRY(hipMemset(ctx->d_walk_ctr, 0, kCtrSets * kCtrStride * sizeof(unsigned)));
     HIP_TRY(hipDeviceSynchronize());
     ctx->runstat_pending = false;
     ctx->has_ws = true;
@@ -5201,6 +5328,17 @@ int etpic_adjoint_workspace(const etpic_ctx *ctx, int64_t n, int nsteps, int che
     return ETPIC_OK;
 }
 
+// nsteps float64 steps from one state buffer into another (see fused_steps).
+static int adjoint_forward(etpic_ctx *ctx, const etpic_particles &from, const etpic_particles &to,
+                           const etpic_species *sp, const etpic_fields *f, int64_t step0, int nsteps, double dt,
+                           double omega, double *dG, hipStream_t st, bool parts_ready) {
+    std::vector<StepPlan> plans((size_t)nsteps);
+    for (int j = 0; j < nsteps; ++j)
+        plans[j] = StepPlan{{f, nullptr, nullptr}, {1.0, 0.0, 0.0}, (double)(step0 + j) * dt};
+    return ctx->fused_steps<double, 1, false>(&to, sp, plans.data(), nsteps, ctx->most_fused(), dt, omega, dG, nullptr,
+                                              ETPIC_STEP_XCD_REMAP, st, &from, false, parts_ready);
+}
+
 int etpic_forward_checkpointed(etpic_ctx *ctx, const etpic_particles *p, const etpic_species *sp,
                                const etpic_fields *f, int64_t step0, int nsteps, double dt, double omega,
                                int checkpoint_every, void *workspace, size_t workspace_bytes, double *dG,
@@ -5214,12 +5352,15 @@ int etpic_forward_checkpointed(etpic_ctx *ctx, const etpic_particles *p, const e
     if (int r = set_device(ctx)) return r;
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *acc = dG ? dG : reinterpret_cast<double *>(static_cast<char *>(workspace) + L.dG_off);
-    for (int k = 0; k < nsteps; ++k) {
-        if (k % checkpoint_every == 0)
-            if (int r = copy_state(*p, state_view(workspace, (size_t)(k / checkpoint_every) * L.state, L, p->n), p->n, st))
-                return r;
-        if (int r = ctx->step<double>(p, sp, f, step0 + k, dt, omega, acc, nullptr, ETPIC_STEP_XCD_REMAP, stream))
-            return r;
+    // the state goes from checkpoint to checkpoint, the last segment's into p
+    const int64_t n = p->n;
+    k_copy_state<<<grid_for(n), kBlock, 0, st>>>(*p, state_view(workspace, 0, L, n));
+    HIP_TRY(hipGetLastError());
+    for (int seg = 0; seg < L.ncp; ++seg) {
+        const int k0 = seg * checkpoint_every, k1 = std::min(nsteps, k0 + checkpoint_every);
+        const etpic_particles from = state_view(workspace, (size_t)seg * L.state, L, n);
+        const etpic_particles to = seg + 1 < L.ncp ? state_view(workspace, (size_t)(seg + 1) * L.state, L, n) : *p;
+        if (int r = adjoint_forward(ctx, from, to, sp, f, step0 + k0, k1 - k0, dt, omega, acc, st, seg > 0)) return r;
     }
     return ETPIC_OK;
 }
@@ -5240,54 +5381,69 @@ int etpic_backward(etpic_ctx *ctx, int64_t n, const etpic_species *sp, const etp
     if (int r = set_device(ctx)) return r;
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *scratch_dG = reinterpret_cast<double *>(static_cast<char *>(workspace) + L.dG_off);
-    const int64_t nt = ctx->host.nt;
+    {
+        const etpic_fields *snap[3] = {f, nullptr, nullptr};
+        const double w1[3] = {1.0, 0.0, 0.0};
+        if (int r = ctx->launch_parts<1>(snap, w1, st, nullptr)) return r;
+    }
+    unsigned *const ctr = ctx->d_walk_ctr + 3 * kCtrStride;
+    unsigned flip = 0;
     for (int seg = L.ncp - 1; seg >= 0; --seg) {
-        const int k0 = seg * checkpoint_every, k1 = std::min(nsteps, k0 + checkpoint_every);
-        // recompute the states before steps k0 .. k1-1 into the slots
-        const etpic_particles first = state_view(workspace, L.slots_off, L, n);
-        if (int r = copy_state(state_view(workspace, (size_t)seg * L.state, L, n), first, n, st)) return r;
-        for (int k = k0; k < k1 - 1; ++k) {
-            const etpic_particles cur = state_view(workspace, L.slots_off + (size_t)(k - k0) * L.state, L, n);
-            const etpic_particles nxt = state_view(workspace, L.slots_off + (size_t)(k - k0 + 1) * L.state, L, n);
-            if (int r = copy_state(cur, nxt, n, st)) return r;
-            if (int r = ctx->step<double>(&nxt, sp, f, step0 + k, dt, omega, scratch_dG, nullptr,
-                                          ETPIC_STEP_XCD_REMAP, stream))
+        // the segment in pieces of at most kMaxAdj steps: the states its later
+        // pieces start from are recomputed into the slots first, the slots
+        // after them take the per-step states of the particles that leave
+        const int k0 = seg * checkpoint_every, len = std::min(nsteps, k0 + checkpoint_every) - k0;
+        const int pieces = (len + kMaxAdj - 1) / kMaxAdj;
+        auto begin = [&](int i) { return k0 + (int)((int64_t)len * i / pieces); };
+        auto start = [&](int i) {
+            return i == 0 ? state_view(workspace, (size_t)seg * L.state, L, n)
+                          : state_view(workspace, L.slots_off + (size_t)(i - 1) * L.state, L, n);
+        };
+        for (int i = 1; i < pieces; ++i)
+            if (int r = adjoint_forward(ctx, start(i - 1), start(i), sp, f, step0 + begin(i - 1),
+                                        begin(i) - begin(i - 1), dt, omega, scratch_dG, st, true))
                 return r;
-        }
-        for (int k = k1 - 1; k >= k0; --k) {
-            const etpic_particles cur = state_view(workspace, L.slots_off + (size_t)(k - k0) * L.state, L, n);
-            const double t = (double)(step0 + k) * dt;
-            const double c = std::cos(omega * t), s = std::sin(omega * t);
-            const etpic_fields *snap[3] = {f, nullptr, nullptr};
-            const double w1[3] = {1.0, 0.0, 0.0};
-            FieldPtrs F = field_ptrs(snap, w1, c, s);
-            F.xcd = ctx->coef_xcd();
-            k_tet_coef<double, 1, kCoefFull><<<grid_for(2 * nt), kBlock, 0, st>>>(nt, ctx->d_gpush64, ctx->d_tetface, F,
-                                                                       static_cast<double *>(ctx->d_coef));
-            HIP_TRY(hipGetLastError());
-            StepArgs<double> a = ctx->step_args<double>(&cur, sp, dt, scratch_dG, nullptr);
+        for (int i = pieces - 1; i >= 0; --i) {
+            const etpic_particles cur = start(i);
+            const StepArgs<double> base = ctx->step_args<double>(&cur, sp, dt, scratch_dG, nullptr);
             AdjArgs b{};
-            b.lam1 = cur.lam[0];
-            b.lam2 = cur.lam[1];
-            b.lam3 = cur.lam[2];
-            b.v0 = static_cast<const double *>(cur.vel[0]);
-            b.v1 = static_cast<const double *>(cur.vel[1]);
-            b.v2 = static_cast<const double *>(cur.vel[2]);
+            b.parts = static_cast<const double *>(ctx->d_coef);
             b.tet = cur.tet;
-            b.vb0 = vbar[0];
-            b.vb1 = vbar[1];
-            b.vb2 = vbar[2];
-            b.xb0 = xbar[0];
-            b.xb1 = xbar[1];
-            b.xb2 = xbar[2];
             b.grad_e = grad_e;
-            b.c = c;
-            b.s = s;
-            b.dt = dt;
-            k_adjoint<<<grid_for(n), kBlock, 0, st>>>(a, b);
-            HIP_TRY(hipGetLastError());
+            b.nsteps = begin(i + 1) - begin(i);
+            for (int k = 0; k < 3; ++k) {
+                b.lam[k] = cur.lam[k];
+                b.v[k] = static_cast<const double *>(cur.vel[k]);
+                b.vb[k] = vbar[k];
+                b.xb[k] = xbar[k];
+            }
+            for (int j = 0; j < b.nsteps; ++j) {
+                const double t = (double)(step0 + begin(i) + j) * dt;
+                b.c[j] = std::cos(omega * t);
+                b.s[j] = std::sin(omega * t);
+                const etpic_particles q = state_view(workspace, L.slots_off + (size_t)(pieces - 1 + j) * L.state, L, n);
+                for (int k = 0; k < 3; ++k) {
+                    b.s_lam[j][k] = q.lam[k];
+                    b.s_v[j][k] = static_cast<double *>(q.vel[k]);
+                }
+                b.s_tet[j] = q.tet;
+            }
+            // at most kWalkQueueCap particles per launch: the queue holds all that leave
+            for (int64_t first = 0; first < n; first += kWalkQueueCap) {
+                b.first = first;
+                b.end = std::min<int64_t>(n, first + kWalkQueueCap);
+                StepArgs<double> a = base;
+                a.walk_ctr = ctr + flip * kCtrStride;
+                flip ^= 1;
+                k_adjoint<<<(unsigned)((b.end - b.first + 63) / 64), 64, 0, st>>>(a, b);
+                HIP_TRY(hipGetLastError());
+                k_adjoint_leavers<<<kLeaverBlocks, kBlock, 0, st>>>(a, b, ctr + flip * kCtrStride);
+                HIP_TRY(hipGetLastError());
+            }
         }
     }
+    k_fill_u32<<<1, kBlock, 0, st>>>(ctr, 2 * kCtrStride, 0u);
+    HIP_TRY(hipGetLastError());
     return ETPIC_OK;
 }
 
