@@ -100,9 +100,9 @@ constexpr unsigned kWalkBlocks = 64;
 // launch's steps
 constexpr unsigned kLeaverBlocks = 512;
 constexpr int64_t kFewParticles = 2 * 1024 * 16;   // two 16-particle wavefronts on each of 256 CUs x 4 SIMDs
-// walk-counter sets, on lines of their own: 0 one step per launch, 1 and 2
-// alternating several, 3 and 4 alternating the reverse sweep
-constexpr unsigned kCtrSets = 5, kCtrStride = 64;
+// walk-counter sets: 0 one step per launch, 1 and 2 alternating several, 3 and
+// 4 alternating the reverse sweep
+constexpr unsigned kCtrSets = 5, kCtrStride = 2048 + 64;
 constexpr int64_t kMinPushWaves = 16384;      // 256 CUs x 64 wavefronts
 constexpr int64_t kInfinityCacheBytes = (int64_t)256 << 20;
 constexpr int64_t kFloatRowBytes = 48 + 64 + 48;   // float coefficient, push and geometry rows per tet
@@ -681,18 +681,37 @@ __device__ __forceinline__ double lam_at(const double *arr, int64_t p, int fixed
 // With `fixed` the end point is rounded to the fixed-point barycentrics (as
 // fix_round3) and the last piece runs to that rounded point, so that the
 // deposit and the stored end point agree exactly.
+//
+// The next tet's records are requested before the crossed piece's atomics are
+// issued: loads complete in order with them, and one behind six atomics would
+// wait for all six.  With `last` (lstart, dl) the piece in the final tet is not
+// deposited but returned, from where it starts.
+struct LastPiece {
+    double l[4], dl[4];
+};
 template <typename Real, bool kTrack, int kExtra = 0>
 __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4], double d[3], Real v[3], double *R,
-                                   double (*ext)[3] = nullptr, bool fixed = false) {
+                                   double (*ext)[3] = nullptr, bool fixed = false, LastPiece *last = nullptr) {
     int hops = 0;
     l[0] = lam0_of(l[1], l[2], l[3]);
-    for (;;) {
-        const double *gp = a.grad + (int64_t)T * 12;
-        double g[4][3];
+    double g[4][3];
+    auto load_grad = [&](int t) {
+        const double *gp = a.grad + (int64_t)t * 12;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
             for (int c = 0; c < 3; ++c) g[k][c] = gp[3 * k + c];
+    };
+    load_grad(T);
+    TetTopo tp = a.topo[T];
+    if (last) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            last->l[k] = l[k];
+            last->dl[k] = 0.0;
+        }
+    }
+    for (;;) {
         double dl[4];
 #pragma unroll
         for (int k = 1; k < 4; ++k) dl[k] = g[k][0] * d[0] + g[k][1] * d[1] + g[k][2] * d[2];
@@ -709,7 +728,6 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
                 }
             }
         }
-        const TetTopo tp = a.topo[T];
         // values at the exit face, selected without dynamic register indexing
         double gx = 0.0, gy = 0.0, gz = 0.0;
         int nb = -1;
@@ -732,15 +750,28 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
 #pragma unroll
                 for (int k = 0; k < 4; ++k) dl[k] = lq[k] - l[k];
             }
-            if (!kTrack) deposit_piece(a.dG, tp, l, dl, a.qw);
+            if (last) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    last->l[k] = l[k];
+                    last->dl[k] = dl[k];
+                }
+            } else if (!kTrack) {
+                deposit_piece(a.dG, tp, l, dl, a.qw);
+            }
 #pragma unroll
             for (int k = 0; k < 4; ++k) l[k] += dl[k];
             break;
         }
+        const TetTopo from = tp;
+        if (nb >= 0) {
+            load_grad(nb);
+            tp = a.topo[nb];
+        }
         double dlp[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) dlp[k] = smin * dl[k];
-        if (!kTrack) deposit_piece(a.dG, tp, l, dlp, a.qw);
+        if (!kTrack) deposit_piece(a.dG, from, l, dlp, a.qw);
         double lc[4], sum = 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -778,25 +809,42 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
 #pragma unroll
             for (int k = 0; k < 4; ++k) l[k] = lc[k];
         } else {
-            const TetTopo tn = a.topo[nb];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 double x = 0.0;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (tp.v[i] == tn.v[j]) x = lc[i];
+                    if (from.v[i] == tp.v[j]) x = lc[i];
                 l[j] = x;
             }
             T = nb;
         }
         if (++hops > ETPIC_HOP_CAP) {
             atomicOr(a.status, (unsigned)ETPIC_DEV_HOPCAP);
+            if (last) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    last->l[k] = l[k];
+                    last->dl[k] = 0.0;
+                }
+            }
             break;
         }
     }
     return T;
 }
 
+// The sums of a piece (l, dl) added to s (edge_sums), in units of 1 / one.
+__device__ __forceinline__ void add_piece(const LastPiece &q, double one, double s[6]) {
+    const double l1 = q.l[1] * one, l2 = q.l[2] * one, l3 = q.l[3] * one;
+    const double d1 = q.dl[1] * one, d2 = q.dl[2] * one, d3 = q.dl[3] * one;
+    s[0] += d1;
+    s[1] += d2;
+    s[2] += d3;
+    s[3] = fma(l1, d2, fma(-l2, d1, s[3]));
+    s[4] = fma(l1, d3, fma(-l3, d1, s[4]));
+    s[5] = fma(l2, d3, fma(-l3, d2, s[5]));
+}
 
 // q w * (the run's path-integral sums) onto the six edges of tet T, and
 // q w * (its end-point barycentric sums) onto the four vertices if rho is kept.
@@ -882,12 +930,27 @@ __global__ void __launch_bounds__(kBlock) k_slots_to_edges(int64_t ne, const int
                                                            unsigned *__restrict__ ctr) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ne; e += stride) {
+        // eight slots at a time, their loads in flight together (an interior
+        // edge of a tet mesh has about five)
+        const int32_t i0 = ptr[e], i1 = ptr[e + 1];
+        const double old = dG[e];
         double s = 0.0;
-        for (int32_t i = ptr[e]; i < ptr[e + 1]; ++i) s += tetG[slot[i]];
-        if (s != 0.0) dG[e] += s;
+        for (int32_t i = i0; i < i1; i += 8) {
+            int32_t at[8];
+            double x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) at[k] = slot[min(i + k, i1 - 1)];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = tetG[at[k]];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (i + k < i1) s += x[k];
+        }
+        if (s != 0.0) dG[e] = old + s;
     }
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nclear; i += stride) clear[i] = 0.0;
-    if (ctr && blockIdx.x == 0 && threadIdx.x < 3) ctr[threadIdx.x] = 0u;
+    if (ctr && blockIdx.x == 0)
+        for (unsigned i = threadIdx.x; i < kCtrStride; i += blockDim.x) ctr[i] = 0u;
 }
 
 
@@ -1497,9 +1560,10 @@ __device__ __forceinline__ void walk_particle(const StepArgs<Real> &a, int64_t p
 }
 
 // Walks the queued particles, one lane each, then the particles of the
-// overflow slices, one wavefront per slice.
+// overflow slices, one wavefront per slice.  The last block to finish resets
+// the counters for the next step.
 template <typename Real, typename WalkOne>
-__device__ __forceinline__ void walk_queues(const StepArgs<Real> &a, unsigned blk, unsigned nblk, WalkOne walk_one) {
+__device__ __forceinline__ void walk_queued(const StepArgs<Real> &a, unsigned blk, unsigned nblk, WalkOne walk_one) {
     const unsigned total = __atomic_load_n(&a.walk_ctr[0], __ATOMIC_RELAXED);
     if (a.scatter && (a.walk_by_slice || total > kWalkQueueCap)) {
         // after a scatter step whose walkers did not all fit in the queue:
@@ -1519,12 +1583,6 @@ __device__ __forceinline__ void walk_queues(const StepArgs<Real> &a, unsigned bl
             if (p < a.n) walk_one(p);
         }
     }
-}
-
-// As walk_queues; the last block to finish resets the counters for the next step.
-template <typename Real, typename WalkOne>
-__device__ __forceinline__ void walk_queued(const StepArgs<Real> &a, unsigned blk, unsigned nblk, WalkOne walk_one) {
-    walk_queues(a, blk, nblk, walk_one);
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1635,6 +1693,87 @@ __device__ __forceinline__ void unscale_sums(double s[6]) {
         }
 }
 
+// The leaver queue of the multi-step kernels: kShards parts of walk_queue, each
+// with its own length on a line of its own; kShardRun consecutive blocks of
+// particles share a part (their leavers then share tets and lines in the walk).  (One length for all had the wavefronts of a dense bunch,
+// most of which hold a leaver, wait for one address: 1e8 particles 9.4 ms per
+// launch, 6.7 ms without that wait.)  Counters of one set: [1] a scatter
+// launch overflowed, [2] slice_queue length, [kShardAt + kShardStride i] the
+// length of part i.
+constexpr unsigned kShards = 64, kShardRun = 32, kShardCap = kWalkQueueCap / kShards, kShardAt = 32, kShardStride = 32;
+static_assert(kShardAt + kShards * kShardStride <= kCtrStride, "a counter set holds its shards");
+
+// Queues the lanes of wmask (entry: this lane's).  False if they did not all
+// fit (or `allowed` is not set): none is queued then.
+template <typename Real>
+__device__ __forceinline__ bool queue_leavers(const StepArgs<Real> &a, unsigned long long wmask, bool left,
+                                              unsigned entry, bool allowed, unsigned blk) {
+    const unsigned ln = threadIdx.x & 63, cnt = (unsigned)__popcll(wmask), shard = blk / kShardRun % kShards;
+    unsigned base = 0;
+    if (ln == 0) base = atomicAdd(&a.walk_ctr[kShardAt + shard * kShardStride], cnt);
+    base = __shfl(base, 0);
+    const bool fits = allowed && base < kShardCap && cnt <= kShardCap - base;
+    const unsigned at = base + (unsigned)__popcll(wmask & ((1ull << ln) - 1ull));
+    if (left && at < kShardCap) a.walk_queue[shard * kShardCap + at] = fits ? entry : kQueueSkip;
+    return fits;
+}
+
+// Takes the queued particles, one lane each (block b from part b % kShards),
+// then those of the overflow slices, one wavefront per slice; after a scatter
+// launch whose leavers did not all fit, every marked particle, by a scan.
+template <typename Real, typename TakeOne>
+__device__ __forceinline__ void take_leavers(const StepArgs<Real> &a, TakeOne take_one) {
+    const unsigned blk = blockIdx.x, nblk = gridDim.x;
+    if (a.scatter && (a.walk_by_slice || __atomic_load_n(&a.walk_ctr[1], __ATOMIC_RELAXED))) {
+        for (int64_t p = (int64_t)blk * kBlock + threadIdx.x; p < a.n; p += (int64_t)nblk * kBlock) take_one(p);
+        return;
+    }
+    const unsigned shard = blk % kShards, per = nblk / kShards;
+    const unsigned count = min(__atomic_load_n(&a.walk_ctr[kShardAt + shard * kShardStride], __ATOMIC_RELAXED), kShardCap);
+    for (unsigned i = blk / kShards * kBlock + threadIdx.x; i < count; i += per * kBlock) {
+        const unsigned q = a.walk_queue[shard * kShardCap + i];
+        if (q != kQueueSkip && (int64_t)q < a.n) take_one((int64_t)q);
+    }
+    const unsigned slices = __atomic_load_n(&a.walk_ctr[2], __ATOMIC_RELAXED);
+    const unsigned wpb = kBlock / 64;
+    for (unsigned i = blk * wpb + (threadIdx.x >> 6); i < slices; i += nblk * wpb) {
+        const int64_t p = (int64_t)a.slice_queue[i] * 64 + (threadIdx.x & 63);
+        if (p < a.n) take_one(p);
+    }
+}
+
+// Clears a counter set (by one block).
+__device__ __forceinline__ void clear_counters(unsigned *ctr) {
+    if (threadIdx.x < 3) ctr[threadIdx.x] = 0u;
+    for (unsigned i = threadIdx.x; i < kShards; i += blockDim.x) ctr[kShardAt + i * kShardStride] = 0u;
+}
+
+// The row parts of a wavefront's nr tets into LDS, part[q * kEnt + 10 j + c]:
+// half a wavefront loads the row of one tet (its 30 or 70 reals in one or
+// three lots), two lots of tets in flight; a lane's place in the row is fixed,
+// so that a tet costs a few instructions.
+template <int kParts, int kEnt>
+__device__ __forceinline__ void stage_parts(const double *__restrict__ parts, const int *tets, int nr, int ln,
+                                            double *part) {
+    constexpr int kLen = kParts * kRowReals, kLots = (kLen + 31) / 32;
+    const int half = ln >> 5;
+#pragma unroll
+    for (int lot = 0; lot < kLots; ++lot) {
+        const int e = 32 * lot + (ln & 31), q = e / kRowReals;
+        if (e < kLen) {
+            double *dst = part + q * kEnt + (e - q * kRowReals);
+#pragma unroll 1
+            for (int j = half; j < nr; j += 4) {
+                const int k = min(j + 2, nr - 1);
+                const double x = parts[(int64_t)max(tets[j], 0) * kLen + e];
+                const double y = parts[(int64_t)max(tets[k], 0) * kLen + e];
+                dst[j * kRowReals] = x;
+                dst[k * kRowReals] = y;
+            }
+        }
+    }
+}
+
 template <typename Real, int kSnap, bool kRho, bool kScatter, bool kFixed>
 __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiArgs<kSnap> ma, int remap) {
     constexpr int kParts = kRowParts<kSnap>;
@@ -1659,6 +1798,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     double l[4] = {0.0, 0.0, 0.0, 0.0};   // l[0] unused: lam0 is implicit
     uint32_t u[3] = {0, 0, 0};
     Real v[3] = {0, 0, 0};
+    int64_t id = 0;
     const bool here = p < a.n && (int)ln < ma.width;
     if (here) {
         T = stored = __builtin_nontemporal_load(lane_at(a.tet + b0, ln));
@@ -1674,6 +1814,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         v[0] = __builtin_nontemporal_load(lane_at(a.v0 + b0, ln));
         v[1] = __builtin_nontemporal_load(lane_at(a.v1 + b0, ln));
         v[2] = __builtin_nontemporal_load(lane_at(a.v2 + b0, ln));
+        if (kScatter && a.id) id = __builtin_nontemporal_load(&a.id[p]);
         if ((unsigned)T >= (unsigned)a.nt) {
             atomicOr(a.status, (unsigned)ETPIC_DEV_BADTET);
             T = -1;
@@ -1687,13 +1828,10 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     const WaveRuns runs = wave_runs(T, ln);
     // scatter form: the sorted position, one cursor atomic per run; without
     // cursors the particles keep their places in the other arrays
-    unsigned dq = (unsigned)p;
-    if (kScatter && a.cursor) {
-        unsigned base = 0;
-        if (runs.head && act) base = atomicAdd(&a.cursor[T], (unsigned)(runs.run_end - runs.lane + 1));
-        base = __shfl(base, runs.head_lane);
-        dq = base + (unsigned)(runs.lane - runs.head_lane);
-    }
+    // (requested here, with the particle's id, and taken up after the steps)
+    unsigned base = 0;
+    if (kScatter && a.cursor && runs.head && act)
+        base = atomicAdd(&a.cursor[T], (unsigned)(runs.run_end - runs.lane + 1));
     const unsigned long long heads = __ballot(runs.head);
     const int nruns = __popcll(heads);
     const int run = __popcll(heads & (ln == 63 ? ~0ull : ((2ull << ln) - 1ull))) - 1;
@@ -1707,13 +1845,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         const int nr = min(kRuns, nruns - r0);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int i = ln; i < nr * kParts * kRowReals; i += 64) {
-            const int j = i / (kParts * kRowReals), rem = i - j * (kParts * kRowReals);
-            const int q = rem / kRowReals, c = rem - q * kRowReals;
-            const int Tj = s_tet[r0 + j];
-            part[q * kEnt + j * kRowReals + c] =
-                Tj >= 0 ? ma.parts[(int64_t)Tj * (kParts * kRowReals) + rem] : 0.0;
-        }
+        stage_parts<kParts, kEnt>(ma.parts, s_tet + r0, nr, ln, part);
         bool live = act && run >= r0 && run < r0 + nr;
         const Real *cf = rows + (live ? (run - r0) * kRowReals : 0);
         // the rows of step j + 1 are formed while step j's arithmetic runs
@@ -1776,6 +1908,8 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         }
     }
     const bool left = leave >= 0;
+    unsigned dq = (unsigned)p;
+    if (kScatter && a.cursor) dq = __shfl(base, runs.head_lane) + (unsigned)(runs.lane - runs.head_lane);
     // (a particle without a valid tet has no sorted place; one that keeps its
     // place is copied as it is)
     if (act || (kScatter && !a.cursor && here)) {
@@ -1794,7 +1928,7 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
             __builtin_nontemporal_store(v[1], &a.o_v1[q]);
             __builtin_nontemporal_store(v[2], &a.o_v2[q]);
             a.o_tet[q] = left ? leaver_mark(T, leave, a.nt) : stored;
-            if (a.id) __builtin_nontemporal_store(__builtin_nontemporal_load(&a.id[p]), &a.o_id[q]);
+            if (a.id) __builtin_nontemporal_store(id, &a.o_id[q]);
         } else {
             if (kFixed) {
                 __builtin_nontemporal_store(u[0], lane_at(reinterpret_cast<uint32_t *>(a.lam1) + b0, ln));
@@ -1826,24 +1960,22 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
         const unsigned long long upto = ln == 63 ? ~0ull : ((2ull << ln) - 1ull);
         r4[0] = (double)__popcll(stayed & upto & ~((1ull << runs.head_lane) - 1ull)) - r4[1] - r4[2] - r4[3];
         if (flush) {
-            const TetTopo *tp = a.topo + T;
+            const int32_t *tv = a.topo[T].v;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                if (r4[k] != 0.0) unsafeAtomicAdd(&a.rho[tp->v[k]], a.qw * r4[k]);
+                if (r4[k] != 0.0) unsafeAtomicAdd(&a.rho[tv[k]], a.qw * r4[k]);
         }
     }
     // leavers to the particle queue, or (in place) their slice when it is full
     const unsigned long long wmask = __ballot(left);
     if (wmask) {
-        const unsigned cnt = (unsigned)__popcll(wmask);
-        unsigned base = 0;
-        if (ln == 0) base = atomicAdd(&a.walk_ctr[0], cnt);
-        base = __shfl(base, 0);
-        const bool fits = (kScatter || !a.walk_by_slice) && base < kWalkQueueCap && cnt <= kWalkQueueCap - base;
-        const unsigned rank = (unsigned)__popcll(wmask & ((1ull << ln) - 1ull));
-        if (left && base + rank < kWalkQueueCap)
-            a.walk_queue[base + rank] = fits ? (kScatter ? dq : (unsigned)p) : kQueueSkip;
-        if (!kScatter && !fits && ln == 0) a.slice_queue[atomicAdd(&a.walk_ctr[2], 1u)] = (unsigned)(b0 >> 6);
+        const bool fits = queue_leavers(a, wmask, left, kScatter ? dq : (unsigned)p, kScatter || !a.walk_by_slice, blk);
+        if (!fits && ln == 0) {
+            if (kScatter)
+                atomicOr(&a.walk_ctr[1], 1u);   // (the slice's particles are spread over the output)
+            else
+                a.slice_queue[atomicAdd(&a.walk_ctr[2], 1u)] = (unsigned)(b0 >> 6);
+        }
     }
 }
 
@@ -1852,20 +1984,20 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
 // pieces are summed per visit of a tet and added to the tet's current slots.
 template <typename Real, int kSnap, bool kFixed>
 __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const MultiArgs<kSnap> &ma, int64_t p) {
-    const int marked = a.tet[p];
-    if (marked > -2) return;
-    const int code = walker_tet(marked);
-    int j = code / (int)a.nt;
-    int T = code - j * (int)a.nt;
-    if (j >= ma.nsteps) return;
     double *lam[3] = {a.lam1, a.lam2, a.lam3};
     uint32_t *fl[3] = {reinterpret_cast<uint32_t *>(a.lam1), reinterpret_cast<uint32_t *>(a.lam2),
                        reinterpret_cast<uint32_t *>(a.lam3)};
+    const int marked = a.tet[p];
     double l[4];
     l[0] = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) l[k + 1] = kFixed ? (double)fl[k][p] : lam[k][p];
     Real v[3] = {a.v0[p], a.v1[p], a.v2[p]};
+    if (marked > -2) return;
+    const int code = walker_tet(marked);
+    int j = code / (int)a.nt;
+    int T = code - j * (int)a.nt;
+    if (j >= ma.nsteps) return;
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     bool some = false;
     auto flush = [&]() {
@@ -1891,7 +2023,10 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
             if (kFixed)
 #pragma unroll
                 for (int k = 1; k < 4; ++k) l[k] *= kFix;
-            T = walk<Real, false>(a, T, l, d, v, nullptr, nullptr, kFixed);
+            LastPiece end;
+            T = walk<Real, false>(a, T, l, d, v, nullptr, nullptr, kFixed, &end);
+            add_piece(end, kOne<kFixed>, s);
+            some = true;
             if (kFixed) {
                 uint32_t u[3];
                 fix_round3(l[1], l[2], l[3], u);
@@ -1944,8 +2079,8 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
 // one for the next pair, so no block waits for the last one to reset them.
 template <typename Real, int kSnap, bool kFixed>
 __global__ void __launch_bounds__(kBlock) k_walk_multi(StepArgs<Real> a, MultiArgs<kSnap> ma, unsigned *next_ctr) {
-    if (blockIdx.x == 0 && threadIdx.x < 3) next_ctr[threadIdx.x] = 0u;
-    walk_queues(a, blockIdx.x, gridDim.x, [&](int64_t p) { walk_leaver<Real, kSnap, kFixed>(a, ma, p); });
+    if (blockIdx.x == 0) clear_counters(next_ctr);
+    take_leavers(a, [&](int64_t p) { walk_leaver<Real, kSnap, kFixed>(a, ma, p); });
 }
 
 // ------------------------------------------------------------------ downshifted step
@@ -2386,14 +2521,8 @@ __global__ void __launch_bounds__(kBlock) k_push_ds(StepArgs<Real> a, DsArgs<Rea
     // leavers to the particle queue, or their slice when it is full
     const unsigned long long wmask = __ballot(left);
     if (wmask) {
-        const unsigned cnt = (unsigned)__popcll(wmask);
-        unsigned base = 0;
-        if (ln == 0) base = atomicAdd(&a.walk_ctr[0], cnt);
-        base = __shfl(base, 0);
-        const bool fits = !a.walk_by_slice && base < kWalkQueueCap && cnt <= kWalkQueueCap - base;
-        const unsigned rank = (unsigned)__popcll(wmask & ((1ull << ln) - 1ull));
-        if (left && base + rank < kWalkQueueCap) a.walk_queue[base + rank] = fits ? (unsigned)p : kQueueSkip;
-        if (!fits && ln == 0) a.slice_queue[atomicAdd(&a.walk_ctr[2], 1u)] = (unsigned)(b0 >> 6);
+        if (!queue_leavers(a, wmask, left, (unsigned)p, !a.walk_by_slice, blk) && ln == 0)
+            a.slice_queue[atomicAdd(&a.walk_ctr[2], 1u)] = (unsigned)(b0 >> 6);
     }
 }
 
@@ -2449,7 +2578,10 @@ __device__ __forceinline__ void walk_leaver_ds(const StepArgs<Real> &a, const Ds
 #pragma unroll
                 for (int c = 0; c < 3; ++c) ext[i][c] = (double)s.V[i + 1][c];
             Real v[3] = {s.V[0][0], s.V[0][1], s.V[0][2]};
-            T = walk<Real, false, 3>(a, T, l, dd, v, nullptr, ext);
+            LastPiece end;
+            T = walk<Real, false, 3>(a, T, l, dd, v, nullptr, ext, false, &end);
+            add_piece(end, 1.0, sum);
+            some = true;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 s.V[0][c] = v[c];
@@ -2490,8 +2622,8 @@ __device__ __forceinline__ void walk_leaver_ds(const StepArgs<Real> &a, const Ds
 
 template <typename Real, bool kEdc>
 __global__ void __launch_bounds__(kBlock) k_walk_ds(StepArgs<Real> a, DsArgs<Real> d, unsigned *next_ctr) {
-    if (blockIdx.x == 0 && threadIdx.x < 3) next_ctr[threadIdx.x] = 0u;
-    walk_queues(a, blockIdx.x, gridDim.x, [&](int64_t p) { walk_leaver_ds<Real, kEdc>(a, d, p); });
+    if (blockIdx.x == 0) clear_counters(next_ctr);
+    take_leavers(a, [&](int64_t p) { walk_leaver_ds<Real, kEdc>(a, d, p); });
 }
 
 // ------------------------------------------------------------------ adjoint step
@@ -2661,12 +2793,7 @@ __global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
         const int nr = min(kRuns, nruns - r0), entries = nr * kRowReals;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int i = ln; i < nr * kParts * kRowReals; i += 64) {
-            const int j = i / (kParts * kRowReals), rem = i - j * (kParts * kRowReals);
-            const int q = rem / kRowReals, c = rem - q * kRowReals;
-            const int Tj = s_tet[r0 + j];
-            part[q * kEnt + j * kRowReals + c] = Tj >= 0 ? b.parts[(int64_t)Tj * (kParts * kRowReals) + rem] : 0.0;
-        }
+        stage_parts<kParts, kEnt>(b.parts, s_tet + r0, nr, ln, part);
         const bool mine = act && run >= r0 && run < r0 + nr;
         const double *cf = rows + (mine ? (run - r0) * kRowReals : 0);
         auto form_rows = [&](int j) {
@@ -3197,19 +3324,24 @@ __global__ void __launch_bounds__(kBlock) k_fill_u32(unsigned *__restrict__ x, i
     if (i < n) x[i] = val;
 }
 
+// Four slices per wavefront, their loads in flight together: with one slice
+// each the launch was bound by the rate at which wavefronts start.
+constexpr int kHistSlices = 4;
 __global__ void __launch_bounds__(kBlock) k_hist(int64_t n, int64_t nt, const int32_t *__restrict__ tet,
                                                  unsigned *__restrict__ count, unsigned *status) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int T = -1;
-    if (p < n) {
-        T = tet[p];
-        if ((unsigned)T >= (unsigned)nt) {
+    const int64_t p0 = (int64_t)blockIdx.x * (kHistSlices * kBlock) + threadIdx.x;
+    int T[kHistSlices];
+#pragma unroll
+    for (int i = 0; i < kHistSlices; ++i) T[i] = p0 + i * kBlock < n ? tet[p0 + i * kBlock] : -1;
+#pragma unroll
+    for (int i = 0; i < kHistSlices; ++i) {
+        if (p0 + i * kBlock < n && (unsigned)T[i] >= (unsigned)nt) {
             atomicOr(status, (unsigned)ETPIC_DEV_BADTET);
-            T = -1;
+            T[i] = -1;
         }
+        const WaveRuns r = wave_runs(T[i]);
+        if (r.head && T[i] >= 0) atomicAdd(&count[T[i]], (unsigned)(r.run_end - r.lane + 1));
     }
-    const WaveRuns r = wave_runs(T);
-    if (r.head && T >= 0) atomicAdd(&count[T], (unsigned)(r.run_end - r.lane + 1));
 }
 
 constexpr int kScanTile = 1024;   // elements per block in the block-local scan (4 per thread)
@@ -3266,37 +3398,22 @@ __global__ void __launch_bounds__(kBlock) k_scan_tiles(unsigned *__restrict__ x,
     if (threadIdx.x == kBlock - 1) sums[blockIdx.x] = wpre + inc;
 }
 
-// Exclusive scan of the (few) tile totals by a single block, looping over chunks.
-__global__ void __launch_bounds__(kBlock) k_scan_sums(unsigned *__restrict__ sums, int64_t m) {
-    __shared__ unsigned s_wave[kBlock / 64];
-    __shared__ unsigned s_carry;
-    if (threadIdx.x == 0) s_carry = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int64_t base = 0; base < m; base += kBlock) {
-        const int64_t i = base + threadIdx.x;
-        const unsigned v = i < m ? sums[i] : 0u;
-        unsigned inc = v;
-        for (int off = 1; off < 64; off <<= 1) {
-            unsigned y = __shfl_up(inc, off);
-            if (lane >= off) inc += y;
-        }
-        if (lane == 63) s_wave[wid] = inc;
-        __syncthreads();
-        unsigned wpre = 0;
-        for (int w = 0; w < wid; ++w) wpre += s_wave[w];
-        const unsigned carry = s_carry;
-        if (i < m) sums[i] = carry + wpre + inc - v;
-        __syncthreads();
-        if (threadIdx.x == kBlock - 1) s_carry = carry + wpre + inc;
-        __syncthreads();
-    }
-}
-
+// Adds to each tile's elements the totals of the tiles before it (one block
+// per tile; it sums those totals itself, which spares a launch for their scan).
 __global__ void __launch_bounds__(kBlock) k_scan_add(unsigned *__restrict__ x, int64_t n,
                                                      const unsigned *__restrict__ sums) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] += sums[i / kScanTile];
+    __shared__ unsigned s_wave[kBlock / 64];
+    unsigned before = 0;
+    for (unsigned i = threadIdx.x; i < blockIdx.x; i += kBlock) before += sums[i];
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = before;
+    __syncthreads();
+    before = 0;
+    for (int w = 0; w < kBlock / 64; ++w) before += s_wave[w];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + threadIdx.x * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (base + i < n) x[base + i] += before;
 }
 
 // hsrc / hdst (optional): nh further arrays of length n at stride n, of the
@@ -4229,7 +4346,7 @@ struct etpic_ctx {
     int sort_count(const etpic_particles *src, hipStream_t st) {
         const int64_t nt = host.nt, n = src->n, m = nt + 1;
         k_fill_u32<<<grid_for(m), kBlock, 0, st>>>(d_count, m, 0u);
-        k_hist<<<grid_for(n), kBlock, 0, st>>>(n, nt, src->tet, d_count, d_status);
+        k_hist<<<grid_for((n + kHistSlices - 1) / kHistSlices), kBlock, 0, st>>>(n, nt, src->tet, d_count, d_status);
         if (!runstat_pending) {
             k_fill_u32<<<1, kBlock, 0, st>>>(reinterpret_cast<unsigned *>(d_runstat), 2, 0u);
             k_run_stat<<<(unsigned)std::min<int64_t>(grid_for(nt), 256), kBlock, 0, st>>>(nt, d_count, d_runstat);
@@ -4239,8 +4356,7 @@ struct etpic_ctx {
             runstat_n = n;
         }
         k_scan_tiles<<<(unsigned)tiles, kBlock, 0, st>>>(d_count, m, d_tilesum);
-        k_scan_sums<<<1, kBlock, 0, st>>>(d_tilesum, tiles);
-        k_scan_add<<<grid_for(m), kBlock, 0, st>>>(d_count, m, d_tilesum);
+        k_scan_add<<<(unsigned)tiles, kBlock, 0, st>>>(d_count, m, d_tilesum);
         HIP_TRY(hipGetLastError());
         return ETPIC_OK;
     }
