@@ -37,7 +37,7 @@
 //                 interpolated samples with Adams-Bashforth positions, and the
 //                 particles that leave their tet.
 //   k_charge      vertex charge of the particles.
-//   k_gauss       continuity residual D^T dG - (rho_new - rho_old).
+//   k_gauss_*     continuity residual D^T dG - (rho_new - rho_old).
 //   k_locate, k_positions   Cartesian points <-> (tet, barycentrics).
 //   k_adjoint     reverse of one float64 step (gradient w.r.t. the edge envelope).
 //   k_field_spmv, k_nm_*, k_cocg_*   implicit envelope field step.
@@ -3117,95 +3117,83 @@ __global__ void __launch_bounds__(kBlock) k_positions(int64_t n, int64_t nt, con
 }
 
 // ------------------------------------------------------------------ vertex charge
+// A block takes kChargePer * 256 consecutive particles: sums per run of equal
+// tets, and the runs' vertices added up in a table in LDS (open addressing, the
+// key is the vertex) before they go to memory, since neighbouring tets share
+// most of their vertices.  A vertex that finds no place within four steps is
+// added directly, so any order of the particles is right.
+//   Bound by the atomics on the vertices, which all XCDs share: four per run of
+// a wavefront before, one per vertex of a block now, and an XCD's blocks take
+// one contiguous range.  1.23e6 particles, 11 per tet: 29.0 -> 13.2 us (1 or 4
+// per thread: 13.7, 14.1); 5e7, 109 per tet: 315 -> 261 us and 1e8, 1600 per
+// tet: 750 -> 571 us, both against a kernel that carried a run over 4 or 16
+// slices of a wavefront (8 per thread: 311, 658).
+constexpr int kChargePer = 2;
+constexpr int kChargeSlots = 512;
+
 __global__ void __launch_bounds__(kBlock) k_charge(int64_t n, int64_t nt, const double *__restrict__ lam1,
                                                    const double *__restrict__ lam2, const double *__restrict__ lam3,
                                                    const int32_t *__restrict__ tet, const TetTopo *__restrict__ topo,
                                                    double qw, double *__restrict__ rho, unsigned *status, int fixed) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int T = -1;
-    double l[4] = {0.0, 0.0, 0.0, 0.0};
-    if (p < n) {
-        T = tet[p];
-        if ((unsigned)T >= (unsigned)nt) {
+    __shared__ double s_sum[kChargeSlots];
+    __shared__ int s_vert[kChargeSlots];
+    for (int i = threadIdx.x; i < kChargeSlots; i += kBlock) {
+        s_vert[i] = -1;
+        s_sum[i] = 0.0;
+    }
+    const int64_t first = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kChargePer * kBlock) + threadIdx.x;
+    int t[kChargePer];
+    double x[kChargePer][3];
+#pragma unroll
+    for (int s = 0; s < kChargePer; ++s) {
+        const int64_t p = first + s * kBlock;
+        t[s] = -1;
+        x[s][0] = x[s][1] = x[s][2] = 0.0;
+        if (p < n) {
+            t[s] = tet[p];
+            x[s][0] = lam_at(lam1, p, fixed);
+            x[s][1] = lam_at(lam2, p, fixed);
+            x[s][2] = lam_at(lam3, p, fixed);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < kChargePer; ++s) {
+        int T = t[s];
+        if (first + s * kBlock < n && (unsigned)T >= (unsigned)nt) {
             atomicOr(status, (unsigned)ETPIC_DEV_BADTET);
             T = -1;
-        } else {
-            l[1] = lam_at(lam1, p, fixed);
-            l[2] = lam_at(lam2, p, fixed);
-            l[3] = lam_at(lam3, p, fixed);
-            l[0] = 1.0 - l[1] - l[2] - l[3];
-        }
-    }
-    const WaveRuns r = wave_runs(T);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) l[k] = run_total(l[k], r);
-    if (r.lane == r.run_end && T >= 0) {
-        const TetTopo tp = topo[T];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&rho[tp.v[k]], qw * l[k]);
-    }
-}
-
-// The same over kSlices consecutive slices of 64 particles per wavefront: the
-// run of one tet that reaches lane 63 of a slice is carried (as a
-// wavefront-uniform partial sum) into the next slice instead of being flushed,
-// so a tet holding thousands of sorted particles costs kSlices times fewer
-// same-address atomics.
-template <int kSlices>
-__global__ void __launch_bounds__(kBlock) k_charge_slices(int64_t n, int64_t nt, const double *__restrict__ lam1,
-                                                          const double *__restrict__ lam2,
-                                                          const double *__restrict__ lam3,
-                                                          const int32_t *__restrict__ tet,
-                                                          const TetTopo *__restrict__ topo, double qw,
-                                                          double *__restrict__ rho, unsigned *status, int fixed) {
-    const int lane = threadIdx.x & 63;
-    const int64_t base = (((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6) * 64 * kSlices;
-    auto flush = [&](int T, const double v[4]) {
-        const TetTopo tp = topo[T];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&rho[tp.v[k]], qw * v[k]);
-    };
-    int carry_t = -1;   // tet of the carried run (uniform over the wavefront), -1: none
-    double carry[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int s = 0; s < kSlices; ++s) {
-        const int64_t p = base + (int64_t)s * 64 + lane;
-        int T = -1;
-        double l[4] = {0.0, 0.0, 0.0, 0.0};
-        if (p < n) {
-            T = tet[p];
-            if ((unsigned)T >= (unsigned)nt) {
-                atomicOr(status, (unsigned)ETPIC_DEV_BADTET);
-                T = -1;
-            } else {
-                l[1] = lam_at(lam1, p, fixed);
-                l[2] = lam_at(lam2, p, fixed);
-                l[3] = lam_at(lam3, p, fixed);
-                l[0] = 1.0 - l[1] - l[2] - l[3];
-            }
-        }
-        const int t0 = __shfl(T, 0);
-        if (carry_t >= 0 && carry_t != t0) {   // the carried run ended with the previous slice
-            if (lane == 0) flush(carry_t, carry);
-            carry_t = -1;
         }
         const WaveRuns r = wave_runs(T);
+        const bool end = r.lane == r.run_end && T >= 0;
+        TetTopo tp;
+        if (end) tp = topo[T];
+        double l[4];
+        l[0] = 0.0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) l[k] = run_total(l[k], r);
-        const int first_end = __shfl(r.run_end, 0);
-        if (carry_t >= 0 && lane == first_end)   // the slice's first run continues the carried one
+        for (int k = 1; k < 4; ++k) l[k] = run_total(T >= 0 ? x[s][k - 1] : 0.0, r);
+        if (end) {
+            // lam_0 sums to the run's length less the other three sums
+            l[0] = (double)(r.run_end - r.head_lane + 1) - l[1] - l[2] - l[3];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) l[k] += carry[k];
-        const int t63 = __shfl(T, 63);
-        double last[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) last[k] = __shfl(l[k], 63);
-        const bool keep = s + 1 < kSlices && t63 >= 0;   // the run through lane 63 may go on
-        if (lane == r.run_end && T >= 0 && !(keep && r.run_end == 63)) flush(T, l);
-        carry_t = keep ? t63 : -1;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) carry[k] = keep ? last[k] : 0.0;
+            for (int k = 0; k < 4; ++k) {
+                const int v = tp.v[k];
+                unsigned h = ((unsigned)v * 2654435761u) >> 23;   // the top 9 bits
+                int tries = 4;
+                for (; tries > 0; --tries, h = (h + 1) & (kChargeSlots - 1)) {
+                    const int was = atomicCAS(&s_vert[h], -1, v);
+                    if (was == -1 || was == v) break;
+                }
+                if (tries > 0)
+                    unsafeAtomicAdd(&s_sum[h], l[k]);
+                else
+                    unsafeAtomicAdd(&rho[v], qw * l[k]);
+            }
+        }
     }
-    if (carry_t >= 0 && lane == 0) flush(carry_t, carry);
+    __syncthreads();
+    for (int i = threadIdx.x; i < kChargeSlots; i += kBlock)
+        if (s_vert[i] >= 0) unsafeAtomicAdd(&rho[s_vert[i]], qw * s_sum[i]);
 }
 
 // ------------------------------------------------------------------ continuity residual
@@ -3221,42 +3209,31 @@ __device__ __forceinline__ double max_keep_nan(double a, double b) { return (a !
 __device__ __forceinline__ double gauss_r(int64_t k, const int32_t *__restrict__ ptr,
                                           const int32_t *__restrict__ code, const double *__restrict__ dG,
                                           const double *__restrict__ rho_new, const double *__restrict__ rho_old) {
+    // eight edges at a time, their loads in flight together (an inner vertex has about
+    // fourteen), summed in the order of the list: a chain of two loads per eight edges
+    // where there was one per edge (22,000 vertices: 14.2 -> 4.8 us)
+    const int32_t i0 = ptr[k], i1 = ptr[k + 1];
+    const double change = rho_new[k] - rho_old[k];
     double div = 0.0;
-    for (int32_t i = ptr[k]; i < ptr[k + 1]; ++i) {
-        const int32_t c = code[i];
-        const double g = dG[c >> 1];
-        div += (c & 1) ? g : -g;
+    for (int32_t i = i0; i < i1; i += 8) {
+        int32_t c[8];
+        double g[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c[j] = code[min(i + j, i1 - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) g[j] = dG[c[j] >> 1];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (i + j < i1) div += (c[j] & 1) ? g[j] : -g[j];
     }
-    return fabs(div - (rho_new[k] - rho_old[k]));
+    return fabs(div - change);
 }
 
-__global__ void __launch_bounds__(kBlock) k_gauss(int64_t nv, const int32_t *__restrict__ ptr,
-                                                  const int32_t *__restrict__ code, const double *__restrict__ dG,
-                                                  const double *__restrict__ rho_new,
-                                                  const double *__restrict__ rho_old,
-                                                  unsigned long long *__restrict__ out) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double r = 0.0, p = 0.0;
-    if (k < nv) {
-        r = gauss_r(k, ptr, code, dG, rho_new, rho_old);
-        p = fabs(rho_old[k]);
-    }
-    // wave-level max then one atomic per wave; a NaN operand wins
-    for (int off = 32; off > 0; off >>= 1) {
-        r = max_keep_nan(r, __shfl_xor(r, off));
-        p = max_keep_nan(p, __shfl_xor(p, off));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        atomicMax(&out[0], (unsigned long long)__double_as_longlong(r));
-        atomicMax(&out[1], (unsigned long long)__double_as_longlong(p));
-    }
-}
-
-// The same maxima in two passes without atomics, for the allocation-free
-// entry point: k_gauss_part leaves one (max|r|, max|rho_old|) pair per block
-// (grid-stride over the vertices, kResBlocks blocks at most) in part[2 * block],
-// k_gauss_final reduces the pairs into out[0..1].  Every partial is written
-// before it is read, so nothing needs clearing between calls.
+// max|r| and max|rho_old| in two passes without atomics: k_gauss_part leaves
+// one pair per block (grid-stride over the vertices, kResBlocks blocks at
+// most) in part[2 * block], k_gauss_final reduces the pairs into out[0..1].
+// Every partial is written before it is read, so nothing needs clearing
+// between calls.
 constexpr int kResBlocks = 1024;
 
 __global__ void __launch_bounds__(kBlock) k_gauss_part(int64_t nv, const int32_t *__restrict__ ptr,
@@ -4148,13 +4125,13 @@ struct etpic_ctx {
     unsigned *d_walk_queue = nullptr;  // kWalkQueueCap particle indices
     unsigned *d_slice_queue = nullptr; // kWalkQueueCap slice indices
     unsigned *d_walk_ctr = nullptr;    // kCtrSets sets of 3 walk-queue counters
-    unsigned long long *d_red = nullptr;  // 2 words for the residual maxima
+    unsigned long long *d_red = nullptr;  // 2 words per block of the residual maxima
     double *d_scratch = nullptr;          // device address of `scratch` on this device
     // mean same-tet run length from the last sort (sum count^2 / N_p), read
     // back without blocking: the device word, its pinned host copy, the event
     // that marks the copy, and the value in use (0 until a sort has been seen)
     unsigned long long *d_runstat = nullptr;
-    unsigned long long *h_runstat = nullptr;
+    unsigned long long *h_runstat = nullptr;   // (and two words the residual's maxima are written into)
     hipEvent_t runstat_ev = nullptr;
     bool runstat_pending = false;
     int64_t runstat_n = 0;
@@ -4956,7 +4933,7 @@ int etpic_create(etpic_ctx **out, int device) {
     // read into, its event, the step-timing events; device memory comes from
     // the caller (etpic_workspace_bind, etpic_mesh_upload, ...)
     hipError_t e = hipSetDevice(device);
-    if (e == hipSuccess) e = hipHostMalloc(&c->h_runstat, sizeof(unsigned long long), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&c->h_runstat, 3 * sizeof(unsigned long long), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->runstat_ev, hipEventDisableTiming);
     c->spare.reserve(kTimingSets);
     c->timing.reserve(kTimingSets);
@@ -5019,7 +4996,7 @@ WsPtrs ws_layout(Carve &cv) {
     WsPtrs w;
     w.status = cv.take<unsigned>(1);
     w.walk_ctr = cv.take<unsigned>(kCtrSets * kCtrStride);
-    w.red = cv.take<unsigned long long>(2);
+    w.red = cv.take<unsigned long long>(2 * kResBlocks);
     w.runstat = cv.take<unsigned long long>(1);
     w.walk_queue = cv.take<unsigned>(kWalkQueueCap);
     w.slice_queue = cv.take<unsigned>(kWalkQueueCap);
@@ -5708,23 +5685,9 @@ int etpic_vertex_charge(etpic_ctx *ctx, const etpic_particles *p, int precision,
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int fixed = precision == ETPIC_MIXED_FIXED ? 1 : 0;
     const int64_t n = p->n;
-    // the charge's atomics go straight to the vertices: slices from shorter runs on
-    switch (ctx->slices_from_runs(n, 96.0, 256.0)) {
-    case 16:
-        k_charge_slices<16><<<grid_for((n + 15) / 16), kBlock, 0, st>>>(n, ctx->host.nt, p->lam[0], p->lam[1],
-                                                                        p->lam[2], p->tet, ctx->d_topo, sp->q * sp->w,
-                                                                        rho, ctx->d_status, fixed);
-        break;
-    case 4:
-        k_charge_slices<4><<<grid_for((n + 3) / 4), kBlock, 0, st>>>(n, ctx->host.nt, p->lam[0], p->lam[1], p->lam[2],
-                                                                     p->tet, ctx->d_topo, sp->q * sp->w, rho,
-                                                                     ctx->d_status, fixed);
-        break;
-    default:
-        k_charge<<<grid_for(n), kBlock, 0, st>>>(n, ctx->host.nt, p->lam[0], p->lam[1], p->lam[2], p->tet, ctx->d_topo,
-                                                 sp->q * sp->w, rho, ctx->d_status, fixed);
-        break;
-    }
+    k_charge<<<grid_for((n + kChargePer - 1) / kChargePer), kBlock, 0, st>>>(
+        n, ctx->host.nt, p->lam[0], p->lam[1], p->lam[2], p->tet, ctx->d_topo, sp->q * sp->w, rho, ctx->d_status,
+        fixed);
     HIP_TRY(hipGetLastError());
     return ETPIC_OK;
 }
@@ -5735,14 +5698,17 @@ int etpic_gauss_residual(etpic_ctx *ctx, const double *dG, const double *rho_new
     if (!ctx->has_mesh) return fail(ETPIC_ESTATE, "no mesh uploaded");
     if (int r = set_device(ctx)) return r;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    k_fill_u32<<<1, kBlock, 0, st>>>(reinterpret_cast<unsigned *>(ctx->d_red), 4, 0u);
     const int64_t nv = ctx->host.nv;
-    k_gauss<<<grid_for(nv), kBlock, 0, st>>>(nv, ctx->d_v2e_ptr, ctx->d_v2e_code, dG, rho_new, rho_old, ctx->d_red);
+    const int nblk = (int)std::min<int64_t>(std::max<int64_t>(grid_for(nv), 1), kResBlocks);
+    double *part = reinterpret_cast<double *>(ctx->d_red);
+    // the pair goes straight to the context's pinned words: no copy to wait for
+    double *res = reinterpret_cast<double *>(ctx->h_runstat + 1);
+    k_gauss_part<<<nblk, kBlock, 0, st>>>(nv, ctx->d_v2e_ptr, ctx->d_v2e_code, dG, rho_new, rho_old, part);
+    k_gauss_final<<<1, kBlock, 0, st>>>(part, nblk, res);
     HIP_TRY(hipGetLastError());
-    unsigned long long bits[2];
-    HIP_TRY(hipMemcpyAsync(bits, ctx->d_red, sizeof bits, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    std::memcpy(out_host, bits, sizeof bits);
+    out_host[0] = res[0];
+    out_host[1] = res[1];
     if (!std::isfinite(out_host[0]) || !std::isfinite(out_host[1]))
         return fail(ETPIC_ENAN, "continuity residual: non-finite current or charge (max|r| %g, max|rho_old| %g)",
                     out_host[0], out_host[1]);
