@@ -201,41 +201,56 @@ def _dptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
+_torch = _dtypes = None
+
+
+def _load_torch():
+    """torch (imported on first use) and the dtypes the library takes, by name."""
+    global _torch, _dtypes
+    if _torch is None:
+        import torch
+        _dtypes = {k: getattr(torch, k) for k in ("float64", "float32", "int32", "int64")}
+        _torch = torch
+    return _torch
+
+
 def _vec(t, n, name, dtype="float64", optional=True):
     """Device pointer of t after checking that it is a contiguous CUDA tensor
     of `dtype` holding exactly n elements (the library reads and writes that
     many through the pointer); None -> NULL when optional (the library then
     decides whether NULL is allowed).  A mismatch raises EtpicError(EINVAL)
     before anything is launched."""
-    import torch
     if t is None:
         if optional:
             return None
         raise EtpicError(EINVAL, f"{name} is required")
-    want = getattr(torch, dtype)
+    torch = _torch or _load_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise EtpicError(EINVAL, f"{name} must be a CUDA tensor")
-    if t.dtype != want:
+    if t.dtype != _dtypes[dtype]:
         raise EtpicError(EINVAL, f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise EtpicError(EINVAL, f"{name} must be contiguous")
     if t.numel() != n:
         raise EtpicError(EINVAL, f"{name} must hold {n} elements, got {t.numel()} (shape {tuple(t.shape)})")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _rows3(t, n, name, dtype="float64"):
     """The three row pointers of a contiguous [3, n] CUDA tensor of `dtype`."""
-    _vec(t, 3 * n, name, dtype, optional=False)
+    base = _vec(t, 3 * n, name, dtype, optional=False)
     if t.dim() != 2 or t.shape[0] != 3:
         raise EtpicError(EINVAL, f"{name} must have shape [3, {n}], got {tuple(t.shape)}")
-    return (C.c_void_p * 3)(*[t[k].data_ptr() for k in range(3)])
+    row = n * t.element_size()
+    return (C.c_void_p * 3)(base, base + row, base + 2 * row)
 
 
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch or _load_torch()
+    # (the handle alone: building torch's Stream object around it costs 2.4 us)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def mesh_canonical(xyz, tet_vert):
@@ -321,7 +336,7 @@ class Particles:
 
     @property
     def precision(self):
-        import torch
+        torch = _torch or _load_torch()
         if self.lam.dtype == torch.int32:
             return MIXED_FIXED
         return FP64 if self.vel.dtype == torch.float64 else MIXED
@@ -358,29 +373,23 @@ class Particles:
     def desc(self):
         """The C descriptor, after checking every array (CUDA memory, dtype,
         contiguity, [3, N] / [N] shapes, one device; EtpicError EINVAL)."""
-        import torch
-        n = self.n
-        if self.lam.dtype == torch.int32:
+        torch = _torch or _load_torch()
+        lam, vel, tet, ids, n = self.lam, self.vel, self.tet, self.ids, self.n
+        if lam.dtype == torch.int32:
             lam_dt, vel_dts = "int32", ("float32",)
         else:
             lam_dt, vel_dts = "float64", ("float64", "float32")
-        _rows3(self.lam, n, "lam", lam_dt)
-        vdt = str(self.vel.dtype).replace("torch.", "")
+        lam_rows = _rows3(lam, n, "lam", lam_dt)
+        vdt = str(vel.dtype)[6:]   # (less "torch.")
         if vdt not in vel_dts:
             raise EtpicError(EINVAL, f"vel must be {' or '.join(vel_dts)} with {lam_dt} lam, got {vdt}")
-        _rows3(self.vel, n, "vel", vdt)
-        _vec(self.tet, n, "tet", "int32", optional=False)
-        _vec(self.ids, n, "ids", "int64")
-        devs = {t.device for t in (self.lam, self.vel, self.tet, self.ids) if t is not None}
-        if len(devs) != 1:
+        vel_rows = _rows3(vel, n, "vel", vdt)
+        d = _Particles(n, lam_rows, vel_rows, _vec(tet, n, "tet", "int32", optional=False),
+                       _vec(ids, n, "ids", "int64"))
+        dev = lam.get_device()   # (all are CUDA tensors here)
+        if vel.get_device() != dev or tet.get_device() != dev or (ids is not None and ids.get_device() != dev):
+            devs = {t.device for t in (lam, vel, tet, ids) if t is not None}
             raise EtpicError(EINVAL, f"particle arrays on several devices: {sorted(map(str, devs))}")
-        d = _Particles()
-        d.n = self.n
-        for k in range(3):
-            d.lam[k] = self.lam[k].data_ptr()
-            d.vel[k] = self.vel[k].data_ptr()
-        d.tet = self.tet.data_ptr()
-        d.id = None if self.ids is None else self.ids.data_ptr()
         return d
 
 
@@ -406,6 +415,9 @@ class Fields:
     def desc(self, n_edge=None, n_face=None):
         """The C descriptor; with the mesh's edge and face counts, after
         checking every array against them (EtpicError EINVAL)."""
+        if n_edge is not None and n_face is not None:
+            return _Fields(_vec(self.e_env, 2 * n_edge, "e_env", optional=False), _vec(self.e_dc, n_edge, "e_dc"),
+                           _vec(self.b_env, 2 * n_face, "b_env", optional=False), _vec(self.b_dc, n_face, "b_dc"))
         if n_edge is not None:
             _vec(self.e_env, 2 * n_edge, "e_env", optional=False)
             _vec(self.e_dc, n_edge, "e_dc")
@@ -624,11 +636,10 @@ class Context:
                                        _stream(stream)))
 
     def gauss_residual(self, dG, rho_new, rho_old, stream=None):
-        out = np.zeros(2)
+        out = (C.c_double * 2)()
         _chk(lib().etpic_gauss_residual(self._h, self._dg(dG), self._rho(rho_new, "rho_new"),
-                                        self._rho(rho_old, "rho_old"),
-                                        _np_ptr(out, C.c_double), _stream(stream)))
-        return float(out[0]), float(out[1])
+                                        self._rho(rho_old, "rho_old"), out, _stream(stream)))
+        return out[0], out[1]
 
     def last_push_slices(self):
         """slices per wavefront of the last particle-kernel launch (1 = k_push)"""
