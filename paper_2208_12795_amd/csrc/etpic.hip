@@ -3458,20 +3458,46 @@ struct FieldCsr {
 };
 
 // Row-wise (M x1)_i and (K x2)_i with kRowLanes lanes per row, summed across
-// those lanes; every lane of the group returns the totals.
+// those lanes; every lane of the group returns the totals.  A lane's entries
+// are taken kRowBatch at a time with their loads in flight together (a row of
+// the edge matrices has about 18 entries;
+// batches of 3 need more registers than two blocks of 1024 have), and added in
+// the row's order.
+constexpr int kRowBatch = 2;
+
 __device__ __forceinline__ void csr_row2(const FieldCsr &S, int64_t row, int sub, const double2 *__restrict__ x1,
                                          const double2 *__restrict__ x2, double2 &m1, double2 &k2) {
     m1 = make_double2(0.0, 0.0);
     k2 = make_double2(0.0, 0.0);
     if (row < S.ne) {
-        for (int32_t j = S.rowptr[row] + sub; j < S.rowptr[row + 1]; j += kRowLanes) {
-            const int32_t c = S.col[j];
-            const double mv = S.M[j], kv = S.K[j];
-            const double2 a = x1[c], b = x2[c];
-            m1.x += mv * a.x;
-            m1.y += mv * a.y;
-            k2.x += kv * b.x;
-            k2.y += kv * b.y;
+        const int32_t j0 = S.rowptr[row], j1 = S.rowptr[row + 1];
+        for (int32_t j = j0 + sub; j < j1; j += kRowBatch * kRowLanes) {
+            int32_t at[kRowBatch], c[kRowBatch];
+            double mv[kRowBatch], kv[kRowBatch];
+            double2 a[kRowBatch], b[kRowBatch];
+#pragma unroll
+            for (int i = 0; i < kRowBatch; ++i) {
+                at[i] = min(j + i * kRowLanes, j1 - 1);
+                c[i] = S.col[at[i]];
+            }
+#pragma unroll
+            for (int i = 0; i < kRowBatch; ++i) {
+                mv[i] = S.M[at[i]];
+                kv[i] = S.K[at[i]];
+            }
+#pragma unroll
+            for (int i = 0; i < kRowBatch; ++i) {
+                a[i] = x1[c[i]];
+                b[i] = x2[c[i]];
+            }
+#pragma unroll
+            for (int i = 0; i < kRowBatch; ++i)
+                if (j + i * kRowLanes < j1) {
+                    m1.x += mv[i] * a[i].x;
+                    m1.y += mv[i] * a[i].y;
+                    k2.x += kv[i] * b[i].x;
+                    k2.y += kv[i] * b[i].y;
+                }
         }
     }
 #pragma unroll
@@ -3619,6 +3645,25 @@ struct NsCsr {
     const double *S;
 };
 
+// (S x)_row with kRowLanes lanes per row, as csr_row2 (a nodal row has about
+// 15 entries, one batch of 8 x 2).
+__device__ __forceinline__ double ns_row(const NsCsr &S, int64_t row, int sub, const double *__restrict__ x) {
+    double sx = 0.0;
+    if (row < S.nv) {
+        const int32_t j0 = S.rowptr[row], j1 = S.rowptr[row + 1];
+        for (int32_t j = j0 + sub; j < j1; j += 2 * kRowLanes) {
+            const int32_t j2 = min(j + kRowLanes, j1 - 1);
+            const int32_t c = S.col[j], c2 = S.col[j2];
+            const double v = S.S[j], v2 = S.S[j2], xc = x[c], xc2 = x[c2];
+            sx += v * xc;
+            if (j + kRowLanes < j1) sx += v2 * xc2;
+        }
+    }
+#pragma unroll
+    for (int off = kRowLanes / 2; off > 0; off >>= 1) sx += __shfl_xor(sx, off);
+    return sx;
+}
+
 // The CG kernels run on at most kNsBlocks blocks (grid-stride loops), so that
 // every block can sum all block partials of the previous kernel itself, in
 // the same fixed order: the scalars of the iteration need no kernel of their
@@ -3630,8 +3675,8 @@ constexpr int kNsBlocks = 512;
 constexpr int kNsThreads = 1024;   // product kernels: 16 wavefronts per block, enough rows in flight for one pass
 constexpr int kNsVecThreads = 256; // vector kernels (one node per lane): more, smaller blocks
 
-// Block-level sum of 4 doubles into partial[blockIdx.x * 4 + k].
-__device__ __forceinline__ void ns_block_sum4(double v[4], double *partial) {
+// Block-level sum of 4 doubles into partial[blk * 4 + k].
+__device__ __forceinline__ void ns_block_sum4(double v[4], double *partial, unsigned blk = blockIdx.x) {
     __shared__ double sh[kNsThreads / 64][4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -3643,18 +3688,25 @@ __device__ __forceinline__ void ns_block_sum4(double v[4], double *partial) {
     if (threadIdx.x < 4) {
         double t = 0.0;
         for (int w = 0; w < (int)(blockDim.x / 64); ++w) t += sh[w][threadIdx.x];
-        partial[blockIdx.x * 4 + threadIdx.x] = t;
+        partial[blk * 4 + threadIdx.x] = t;
     }
 }
 
-// Every thread gets the sums of the nb partials (fixed order).
-__device__ __forceinline__ void all_sum4(int64_t nb, const double *__restrict__ partial, double tot[4]) {
-    __shared__ double sh[kNsThreads / 64][4];
-    __shared__ double res[4];
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t b = threadIdx.x; b < nb; b += blockDim.x)
+// This thread's share of the sums of the nb partials: their loads go out with
+// the other loads of the kernel, all_sum4 adds the shares up.
+__device__ __forceinline__ void fetch_sum4(int64_t nb, const double *__restrict__ partial, double v[4]) {
+    int64_t b = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = b < nb ? partial[4 * b + k] : 0.0;
+    for (b += blockDim.x; b < nb; b += blockDim.x)
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += partial[4 * b + k];
+}
+
+// Every thread gets the sums of the block's shares (fixed order).
+__device__ __forceinline__ void all_sum4(double v[4], double tot[4]) {
+    __shared__ double sh[kNsThreads / 64][4];
+    __shared__ double res[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off);
@@ -3672,6 +3724,27 @@ __device__ __forceinline__ void all_sum4(int64_t nb, const double *__restrict__ 
     for (int k = 0; k < 4; ++k) tot[k] = res[k];
 }
 
+// What the host follows a solve by: three words of pinned memory.  word holds
+// (k + 1) << 1 | done of the last product launch that ran; r2 and b2 are read
+// once the stream has drained.
+struct SolveWatch {
+    unsigned long long word;
+    double r2, b2;
+};
+
+// Every kSolveReport-th launch reports, and the last: a store to host memory
+// keeps its kernel from ending for 1-2 us.
+constexpr int kSolveReport = 4;
+
+__device__ __forceinline__ void report(SolveWatch *watch, int k, bool done, bool last, double r2, double b2) {
+    if (last) {
+        watch->r2 = r2;
+        watch->b2 = b2;
+    }
+    if (last || k % kSolveReport == 0)
+        __hip_atomic_store(&watch->word, 2ull * (k + 1) + (done ? 1 : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Right-hand side of a nodal solve: b = -(gs (D^T G + rho0) + D^T w_comp)
 // at the nodes off the wall, 0 on it; every pointer may be NULL.  w is a
 // complex edge vector of which component comp (0 re, 1 im) is taken.
@@ -3686,18 +3759,28 @@ struct NsRhs {
 __device__ __forceinline__ double ns_rhs(int64_t i, const int32_t *__restrict__ ptr, const int32_t *__restrict__ code,
                                          const NsRhs &R, const uint8_t *__restrict__ wall) {
     if (wall[i]) return 0.0;
+    const int32_t i0 = ptr[i], i1 = ptr[i + 1];
     double div = R.rho0 ? R.rho0[i] : 0.0;
     double dw = 0.0;
-    for (int32_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-        const int32_t c = code[k];
+    for (int32_t k = i0; k < i1; k += 8) {   // eight edges' loads in flight together
+        int32_t c[8];
+        double g[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c[j] = code[min(k + j, i1 - 1)];
         if (R.G) {
-            const double g = R.G[c >> 1];
-            div += (c & 1) ? g : -g;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) g[j] = R.G[c[j] >> 1];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (k + j < i1) div += (c[j] & 1) ? g[j] : -g[j];
         }
         if (R.w) {
-            const double2 wv = R.w[c >> 1];
-            const double g = R.comp ? wv.y : wv.x;
-            dw += (c & 1) ? g : -g;
+            const double *w = reinterpret_cast<const double *>(R.w) + R.comp;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) g[j] = w[2 * (int64_t)(c[j] >> 1)];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (k + j < i1) dw += (c[j] & 1) ? g[j] : -g[j];
         }
     }
     return -(R.gs * div + dw);
@@ -3746,10 +3829,7 @@ __global__ void __launch_bounds__(kNsThreads) k_ns_start_warm(NsCsr S, const int
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t / kRowLanes < S.nv; t += stride) {
         const int64_t row = t / kRowLanes;
         const int sub = (int)(t % kRowLanes);
-        double sx = 0.0;
-        for (int32_t j = S.rowptr[row] + sub; j < S.rowptr[row + 1]; j += kRowLanes) sx += S.S[j] * x[S.col[j]];
-#pragma unroll
-        for (int off = kRowLanes / 2; off > 0; off >>= 1) sx += __shfl_xor(sx, off);
+        const double sx = ns_row(S, row, sub, x);
         if (sub == 0) {
             const double b = ns_rhs(row, ptr, code, R, wall);
             const double ri = b - sx;
@@ -3777,45 +3857,64 @@ __global__ void __launch_bounds__(kNsThreads) k_ns_start_warm(NsCsr S, const int
 // folded into the product, so no separate pass over p is needed), with the
 // partials of p . q.  check_only: the convergence test alone (after the last
 // allowed iteration).  Returns at once if an earlier launch found convergence.
+// The first pass over the rows does not need the scalars: its product runs
+// before the sums of the partials, whose loads are in flight meanwhile.
 __global__ void __launch_bounds__(kNsThreads) k_ns_apply(NsCsr S, double *__restrict__ sc,
                                                      const double *__restrict__ z, double *__restrict__ p,
                                                      double *__restrict__ q, const double *__restrict__ pin,
                                                      int64_t nb_in, double *__restrict__ pout, int k, double tol2,
-                                                     int check_only) {
-    if (sc[10] != 0.0) return;
-    double tot[4];
-    all_sum4(nb_in, pin, tot);
-    const double b2 = k == 0 ? tot[3] : sc[9];
+                                                     int check_only, SolveWatch *watch) {
+    const bool stopped = sc[10] != 0.0;
+    const double ro = sc[(k + 1) & 1], bb = sc[9];
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    const unsigned blk = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t t = (int64_t)blk * blockDim.x + threadIdx.x;
+    const int sub = (int)(t % kRowLanes);
+    int64_t row = t / kRowLanes;
+    double zr = 0.0, pr = 0.0, qr = 0.0;
+    if (row < S.nv && sub == 0) {
+        zr = z[row];
+        pr = p[row];
+        qr = q[row];
+    }
+    double az = ns_row(S, row, sub, z);
+    all_sum4(v, tot);
+    if (stopped) return;
+    const double b2 = k == 0 ? tot[3] : bb;
     const double r2 = tot[2], rn = tot[0];
     const bool done = b2 == 0.0 || !(r2 > tol2 * b2);   // no source: x = 0, done
-    const double ro = sc[(k + 1) & 1];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc[8] = r2;
         if (k == 0) sc[9] = b2;
         sc[k & 1] = rn;
         sc[10] = done ? 1.0 : 0.0;
         sc[11] = (double)k;
+        report(watch, k, done, done || check_only, r2, b2);
     }
     if (done || check_only) return;
     const double be = (k == 0 || ro == 0.0) ? 0.0 : rn / ro;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t / kRowLanes < S.nv; t += stride) {
-        const int64_t row = t / kRowLanes;
-        const int sub = (int)(t % kRowLanes);
-        double az = 0.0;
-        for (int32_t j = S.rowptr[row] + sub; j < S.rowptr[row + 1]; j += kRowLanes) az += S.S[j] * z[S.col[j]];
-#pragma unroll
-        for (int off = kRowLanes / 2; off > 0; off >>= 1) az += __shfl_xor(az, off);
-        if (sub == 0) {
-            const double pn = z[row] + be * p[row];
-            const double qn = az + be * q[row];
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    for (;;) {
+        if (row < S.nv && sub == 0) {
+            const double pn = zr + be * pr;
+            const double qn = az + be * qr;
             p[row] = pn;
             q[row] = qn;
             v[0] += pn * qn;
         }
+        t += stride;
+        row = t / kRowLanes;
+        if (row >= S.nv) break;   // (the lanes of a row leave together)
+        if (sub == 0) {
+            zr = z[row];
+            pr = p[row];
+            qr = q[row];
+        }
+        az = ns_row(S, row, sub, z);
     }
-    ns_block_sum4(v, pout);
+    ns_block_sum4(v, pout, blk);
 }
 
 // Iteration k, second half: alpha = rho_new / (p . q) from the partials of the
@@ -3827,20 +3926,40 @@ __global__ void __launch_bounds__(kNsVecThreads) k_ns_update(int64_t nv, const d
                                                       double *__restrict__ r, double *__restrict__ z,
                                                       const double *__restrict__ pin, int64_t nb_in,
                                                       double *__restrict__ pout, int k) {
-    if (sc[10] != 0.0) return;
-    double tot[4];
-    all_sum4(nb_in, pin, tot);
+    const bool stopped = sc[10] != 0.0;
+    const double rho = sc[k & 1];
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    double pi = 0.0, qi = 0.0, xi = 0.0, ri = 0.0, di = 0.0;
+    if (i < nv) {
+        pi = p[i];
+        qi = q[i];
+        xi = x[i];
+        ri = r[i];
+        di = dinv[i];
+    }
+    all_sum4(v, tot);
+    if (stopped) return;
     const double pq = tot[0];
-    const double al = pq != 0.0 ? sc[k & 1] / pq : 0.0;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += (int64_t)gridDim.x * blockDim.x) {
-        x[i] += al * p[i];
-        const double ri = r[i] - al * q[i];
+    const double al = pq != 0.0 ? rho / pq : 0.0;
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    while (i < nv) {
+        x[i] = xi + al * pi;
+        ri = ri - al * qi;
         r[i] = ri;
-        const double zi = dinv[i] * ri;
+        const double zi = di * ri;
         z[i] = zi;
         v[0] += ri * zi;
         v[2] += ri * ri;
+        i += (int64_t)gridDim.x * blockDim.x;
+        if (i < nv) {
+            pi = p[i];
+            qi = q[i];
+            xi = x[i];
+            ri = r[i];
+            di = dinv[i];
+        }
     }
     ns_block_sum4(v, pout);
 }
@@ -3855,21 +3974,39 @@ __global__ void __launch_bounds__(kNsVecThreads) k_ns_update(int64_t nv, const d
 // finite); beta = rho_k / rho_{k-1}, p = z + beta p, q = A z + beta q (= A p,
 // the direction update folded into the product), partials p^T q.
 // A = alpha M + beta_k K.  check_only: the test alone.
-__global__ void __launch_bounds__(kNsThreads) k_cocg_apply(FieldCsr S, double2 alpha, double beta_k,
+// As k_ns_apply, the first pass's product runs before the sums.  An XCD's
+// blocks take contiguous rows, which share the entries of z they read.
+__global__ void __launch_bounds__(kNsThreads, 8) k_cocg_apply(FieldCsr S, double2 alpha, double beta_k,
                                                        double *__restrict__ sc, const double2 *__restrict__ z,
                                                        double2 *__restrict__ p, double2 *__restrict__ q,
                                                        const double *__restrict__ pin, int64_t nb_in,
                                                        double *__restrict__ pout, int k, double tol2,
-                                                       int check_only) {
-    if (sc[10] != 0.0) return;
-    double tot[4];
-    all_sum4(nb_in, pin, tot);
-    const double b2 = k == 0 ? tot[3] : sc[9];
+                                                       int check_only, SolveWatch *watch) {
+    const bool stopped = sc[10] != 0.0;
+    const int o = 2 * ((k + 1) & 1);
+    const double2 ro = make_double2(sc[o], sc[o + 1]);
+    const double bb = sc[9];
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    const unsigned blk = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t t = (int64_t)blk * blockDim.x + threadIdx.x;
+    const int sub = (int)(t % kRowLanes);
+    int64_t row = t / kRowLanes;
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 zr = zero, pr = zero, qr = zero, m, kk;
+    if (row < S.ne && sub == 0) {
+        zr = z[row];
+        pr = p[row];
+        qr = q[row];
+    }
+    csr_row2(S, row, sub, z, z, m, kk);
+    all_sum4(v, tot);
+    if (stopped) return;
+    const double b2 = k == 0 ? tot[3] : bb;
     const double r2 = tot[2];
     const double2 rn = make_double2(tot[0], tot[1]);
     const bool done = b2 == 0.0 || !(r2 > tol2 * b2);
-    const int o = 2 * ((k + 1) & 1);
-    const double2 ro = make_double2(sc[o], sc[o + 1]);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc[8] = r2;
         if (k == 0) sc[9] = b2;
@@ -3877,27 +4014,32 @@ __global__ void __launch_bounds__(kNsThreads) k_cocg_apply(FieldCsr S, double2 a
         sc[2 * (k & 1) + 1] = rn.y;
         sc[10] = done ? 1.0 : 0.0;
         sc[11] = (double)k;
+        report(watch, k, done, done || check_only, r2, b2);
     }
     if (done || check_only) return;
-    const double2 be = (k == 0 || (ro.x == 0.0 && ro.y == 0.0)) ? make_double2(0.0, 0.0) : cdiv(rn, ro);
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t / kRowLanes < S.ne; t += stride) {
-        const int64_t row = t / kRowLanes;
-        const int sub = (int)(t % kRowLanes);
-        double2 m, kk;
-        csr_row2(S, row, sub, z, z, m, kk);
-        if (sub == 0) {
-            const double2 pn = cadd(z[row], cmul(be, p[row]));
-            const double2 qn = cadd(cadd(cmul(alpha, m), cscale(kk, beta_k)), cmul(be, q[row]));
+    const double2 be = (k == 0 || (ro.x == 0.0 && ro.y == 0.0)) ? zero : cdiv(rn, ro);
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    for (;;) {
+        if (row < S.ne && sub == 0) {
+            const double2 pn = cadd(zr, cmul(be, pr));
+            const double2 qn = cadd(cadd(cmul(alpha, m), cscale(kk, beta_k)), cmul(be, qr));
             p[row] = pn;
             q[row] = qn;
             const double2 pq = cmul(pn, qn);
             v[0] += pq.x;
             v[1] += pq.y;
         }
+        t += stride;
+        row = t / kRowLanes;
+        if (row >= S.ne) break;   // (the lanes of a row leave together)
+        if (sub == 0) {
+            zr = z[row];
+            pr = p[row];
+            qr = q[row];
+        }
+        csr_row2(S, row, sub, z, z, m, kk);
     }
-    ns_block_sum4(v, pout);
+    ns_block_sum4(v, pout, blk);
 }
 
 // Iteration k, second half: alpha = rho_k / (p^T q); x += alpha p, r -= alpha q,
@@ -3908,23 +4050,43 @@ __global__ void __launch_bounds__(kNsVecThreads) k_cocg_update(int64_t ne, const
                                                         double2 *__restrict__ x, double2 *__restrict__ r,
                                                         double2 *__restrict__ z, const double *__restrict__ pin,
                                                         int64_t nb_in, double *__restrict__ pout, int k) {
-    if (sc[10] != 0.0) return;
-    double tot[4];
-    all_sum4(nb_in, pin, tot);
-    const double2 pq = make_double2(tot[0], tot[1]);
+    const bool stopped = sc[10] != 0.0;
     const double2 rho = make_double2(sc[2 * (k & 1)], sc[2 * (k & 1) + 1]);
-    const double2 al = (pq.x == 0.0 && pq.y == 0.0) ? make_double2(0.0, 0.0) : cdiv(rho, pq);
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ne; i += (int64_t)gridDim.x * blockDim.x) {
-        x[i] = cadd(x[i], cmul(al, p[i]));
-        const double2 ri = csub(r[i], cmul(al, q[i]));
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 pi = zero, qi = zero, xi = zero, ri = zero, di = zero;
+    if (i < ne) {
+        pi = p[i];
+        qi = q[i];
+        xi = x[i];
+        ri = r[i];
+        di = dinv[i];
+    }
+    all_sum4(v, tot);
+    if (stopped) return;
+    const double2 pq = make_double2(tot[0], tot[1]);
+    const double2 al = (pq.x == 0.0 && pq.y == 0.0) ? zero : cdiv(rho, pq);
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    while (i < ne) {
+        x[i] = cadd(xi, cmul(al, pi));
+        ri = csub(ri, cmul(al, qi));
         r[i] = ri;
-        const double2 zi = cmul(dinv[i], ri);
+        const double2 zi = cmul(di, ri);
         z[i] = zi;
         const double2 rz = cmul(ri, zi);
         v[0] += rz.x;
         v[1] += rz.y;
         v[2] += ri.x * ri.x + ri.y * ri.y;
+        i += (int64_t)gridDim.x * blockDim.x;
+        if (i < ne) {
+            pi = p[i];
+            qi = q[i];
+            xi = x[i];
+            ri = r[i];
+            di = dinv[i];
+        }
     }
     ns_block_sum4(v, pout);
 }
@@ -4132,6 +4294,7 @@ struct etpic_ctx {
     // that marks the copy, and the value in use (0 until a sort has been seen)
     unsigned long long *d_runstat = nullptr;
     unsigned long long *h_runstat = nullptr;   // (and two words the residual's maxima are written into)
+    SolveWatch *h_watch = nullptr;             // pinned, behind those
     hipEvent_t runstat_ev = nullptr;
     bool runstat_pending = false;
     int64_t runstat_n = 0;
@@ -4933,7 +5096,9 @@ int etpic_create(etpic_ctx **out, int device) {
     // read into, its event, the step-timing events; device memory comes from
     // the caller (etpic_workspace_bind, etpic_mesh_upload, ...)
     hipError_t e = hipSetDevice(device);
-    if (e == hipSuccess) e = hipHostMalloc(&c->h_runstat, 3 * sizeof(unsigned long long), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&c->h_runstat, 4 * sizeof(unsigned long long) + sizeof(SolveWatch),
+                                               hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess) c->h_watch = reinterpret_cast<SolveWatch *>(c->h_runstat + 4);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->runstat_ev, hipEventDisableTiming);
     c->spare.reserve(kTimingSets);
     c->timing.reserve(kTimingSets);
@@ -5772,6 +5937,42 @@ int etpic_sort(etpic_ctx *ctx, const etpic_particles *src, const etpic_particles
 
 namespace {
 
+// Iterations of a solve: launch(k, false) enqueues iteration k, whose product
+// kernel first tests the residual of the ones before and reports in W;
+// launch(max_iter, true) the test alone.  The host enqueues up to kSolveLead
+// iterations beyond the last report, so the device never waits for it (a read
+// of the scalars every 5 or 10 iterations left it idle for 25 us each time:
+// two steps of the coupled loop on 59,900 edges 7.9 -> 6.6 ms with the loads
+// below, a field step on 460,000 edges 2.30 -> 2.17 ms); those enqueued past
+// convergence return at once.  Returns once the stream has drained, the last
+// report in W.
+constexpr int kSolveLead = kSolveReport + 2;
+
+template <typename Launch>
+int watch_solve(SolveWatch &W, hipStream_t st, int max_iter, Launch &&launch) {
+    __atomic_store_n(&W.word, 0ull, __ATOMIC_RELAXED);
+    W.r2 = W.b2 = 0.0;
+    for (int k = 0; k <= max_iter; ++k) {
+        unsigned long long w = 0;
+        for (unsigned spins = 1;; ++spins) {
+            w = __atomic_load_n(&W.word, __ATOMIC_RELAXED);
+            if ((w & 1) || (int64_t)(w >> 1) > (int64_t)k - kSolveLead) break;
+            // an error, or a stream that ran dry without a report, ends the wait
+            if ((spins & 1023) == 0 && hipStreamQuery(st) != hipErrorNotReady) {
+                w = __atomic_load_n(&W.word, __ATOMIC_RELAXED);
+                if ((w & 1) || (int64_t)(w >> 1) > (int64_t)k - kSolveLead) break;
+                HIP_TRY(hipStreamSynchronize(st));
+                return fail(ETPIC_EHIP, "solver: no report from iteration %d", k - kSolveLead);
+            }
+        }
+        if (w & 1) break;
+        launch(k, k == max_iter);
+        HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipStreamSynchronize(st));
+    return ETPIC_OK;
+}
+
 // Field solver arrays: CSR row pointers, columns, M and K values, Dirichlet
 // mask, face -> edge table, Jacobi inverse diagonal, 9 complex work vectors,
 // block partials and the 12 iteration scalars.
@@ -5937,31 +6138,20 @@ int etpic_field_step(etpic_ctx *ctx, double t_next, double *u, double *v, double
     HIP_TRY(hipGetLastError());
     const unsigned ga = (unsigned)std::min<int64_t>((ne * kRowLanes + kNsThreads - 1) / kNsThreads, kNsBlocks);
     const unsigned gu = (unsigned)std::min<int64_t>((ne + kNsVecThreads - 1) / kNsVecThreads, kNsBlocks);
-    // iterations in batches of `check`; the host reads the scalars once per batch
-    const int check = 5;
     const double tol2 = tol * tol;
-    double hs[12];
-    int k = 0;
-    for (;;) {
-        const int n = std::min(check, max_iter - k);
-        for (int j = 0; j < n; ++j, ++k) {
+    SolveWatch &W = *ctx->h_watch;
+    if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
             k_cocg_apply<<<ga, kNsThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, z, p, q, pa, k == 0 ? (int64_t)ge : gu,
-                                                    pb, k, tol2, 0);
-            k_cocg_update<<<gu, kNsVecThreads, 0, st>>>(ne, F.sc, F.dinv, p, q, x, r, z, pb, ga, pa, k);
-        }
-        if (k >= max_iter)
-            k_cocg_apply<<<ga, kNsThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, z, p, q, pa, k == 0 ? (int64_t)ge : gu,
-                                                    pb, k, tol2, 1);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(hs, F.sc, sizeof hs, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (hs[10] != 0.0 || k >= max_iter) break;
-    }
-    const double rel = hs[9] > 0.0 ? std::sqrt(hs[8] / hs[9]) : 0.0;
-    const int it = (int)hs[11];
+                                                    pb, k, tol2, check_only ? 1 : 0, &W);
+            if (!check_only)
+                k_cocg_update<<<gu, kNsVecThreads, 0, st>>>(ne, F.sc, F.dinv, p, q, x, r, z, pb, ga, pa, k);
+        }))
+        return rc;
+    const double rel = W.b2 > 0.0 ? std::sqrt(W.r2 / W.b2) : 0.0;
+    const int it = (int)(W.word >> 1) - 1;
     if (iters_out) *iters_out = it;
     if (resid_out) *resid_out = rel;
-    if (hs[10] == 0.0 || !std::isfinite(rel)) return fail(ETPIC_ENOCONV, "COCG: relative residual %.3e after %d iterations", rel, it);
+    if (!(W.word & 1) || !std::isfinite(rel)) return fail(ETPIC_ENOCONV, "COCG: relative residual %.3e after %d iterations", rel, it);
     k_nm_faraday<<<grid_for(F.nf), kBlock, 0, st>>>(F.nf, F.face_edge, U, us, x, reinterpret_cast<double2 *>(b), dt, w);
     k_nm_correct<<<ge, kBlock, 0, st>>>(ne, us, vs, x, U, V, A, dt);
     HIP_TRY(hipGetLastError());
@@ -6107,7 +6297,7 @@ int ns_solve_impl(etpic_ctx *ctx, const NsRhs &R, double *x, double c, double s,
     double *r = N.v(1), *z = N.v(2), *p = N.v(3), *q = N.v(4);
     // partials: pa from the product (gr blocks), pb from the start and the update
     double *pa = N.partial, *pb = N.partial + 4 * kNsBlocks;
-    int64_t nb = warm ? gr : gv;
+    const int64_t nb = warm ? gr : gv;
     if (warm)
         k_ns_start_warm<<<gr, kNsThreads, 0, st>>>(N.csr(), ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r,
                                                    z, p, q, pb, N.sc);
@@ -6115,33 +6305,22 @@ int ns_solve_impl(etpic_ctx *ctx, const NsRhs &R, double *x, double c, double s,
         k_ns_start<<<gv, kNsVecThreads, 0, st>>>(nv, ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r, z, p, q,
                                                  pb, N.sc);
     HIP_TRY(hipGetLastError());
-    // Iterations are launched in batches; the device raises the done flag when
-    // the residual is small enough and the rest of the batch returns at once.
-    // The host reads the scalars once per batch.
-    const int batch = 10;
     const double tol2 = tol * tol;
-    double hs[12];
-    int k = 0;
-    for (;;) {
-        const int n = std::min(batch, max_iter - k);
-        for (int j = 0; j < n; ++j, ++k) {
-            k_ns_apply<<<gr, kNsThreads, 0, st>>>(N.csr(), N.sc, z, p, q, pb, nb, pa, k, tol2, 0);
-            k_ns_update<<<gv, kNsVecThreads, 0, st>>>(nv, N.sc, N.dinv, p, q, x, r, z, pa, gr, pb, k);
-            nb = gv;
-        }
-        if (k >= max_iter) k_ns_apply<<<gr, kNsThreads, 0, st>>>(N.csr(), N.sc, z, p, q, pb, nb, pa, k, tol2, 1);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(hs, N.sc, sizeof hs, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (hs[10] != 0.0 || k >= max_iter) break;
-    }
-    const double bnorm2 = hs[9];
+    SolveWatch &W = *ctx->h_watch;
+    if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
+            k_ns_apply<<<gr, kNsThreads, 0, st>>>(N.csr(), N.sc, z, p, q, pb, k == 0 ? nb : (int64_t)gv, pa, k, tol2,
+                                                  check_only ? 1 : 0, &W);
+            if (!check_only)
+                k_ns_update<<<gv, kNsVecThreads, 0, st>>>(nv, N.sc, N.dinv, p, q, x, r, z, pa, gr, pb, k);
+        }))
+        return rc;
+    const double bnorm2 = W.b2;
     if (!(bnorm2 > 0.0) && warm) HIP_TRY(hipMemsetAsync(x, 0, sizeof(double) * nv, st));   // no source: x = 0
-    const double rel = bnorm2 > 0.0 ? std::sqrt(hs[8] / bnorm2) : 0.0;
-    const int it = (int)hs[11];
+    const double rel = bnorm2 > 0.0 ? std::sqrt(W.r2 / bnorm2) : 0.0;
+    const int it = (int)(W.word >> 1) - 1;
     if (iters_out) *iters_out = it;
     if (resid_out) *resid_out = rel;
-    if (hs[10] == 0.0 || !std::isfinite(rel))
+    if (!(W.word & 1) || !std::isfinite(rel))
         return fail(ETPIC_ENOCONV, "ns CG: relative residual %.3e after %d iterations", rel, it);
     if (x_out || e_out || edc_out)
         k_ns_out<<<grid_for(std::max(N.ne, nv)), kBlock, 0, st>>>(N.ne, nv, N.ev, x, c, s, x_out, e_out, edc_out,
