@@ -3597,6 +3597,7 @@ __global__ void __launch_bounds__(kBlock) k_cocg_init(int64_t ne, const double2 
         v[3] = v[2];
     }
     if (i == 0) {
+        sc[6] = 0.0;   // (the meeting of the resident solve)
         sc[10] = 0.0;
         sc[11] = 0.0;
     }
@@ -3808,6 +3809,7 @@ __global__ void __launch_bounds__(kNsVecThreads) k_ns_start(int64_t nv, const in
         v[3] += b * b;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[6] = 0.0;   // (the meeting of the resident solve)
         sc[10] = 0.0;
         sc[11] = 0.0;
     }
@@ -3844,6 +3846,7 @@ __global__ void __launch_bounds__(kNsThreads) k_ns_start_warm(NsCsr S, const int
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc[6] = 0.0;   // (the meeting of the resident solve)
         sc[10] = 0.0;
         sc[11] = 0.0;
     }
@@ -4089,6 +4092,365 @@ __global__ void __launch_bounds__(kNsVecThreads) k_cocg_update(int64_t ne, const
         }
     }
     ns_block_sum4(v, pout);
+}
+
+// ---- The same two iterations in one launch, for systems whose rows fit the
+// chip at once (kResRows rows per block, one block per CU): matrix rows and the
+// vectors but z stay in registers, and an iteration costs its gather of z and
+// two exchanges of block sums instead of two launches that load everything
+// again.
+//
+// Block sums are exchanged through `slots`, three sets of kResMaxBlocks x
+// kResStride words taken in turn.  A word that no block has written yet holds
+// kSlotEmpty (a NaN that the sums never are, see slot_bits); a block writes its
+// words of set s % 3 in exchange s, reads all blocks' words of it, and then
+// empties its own words of the set before, which every block has read by then
+// and which is next written two exchanges later.  Words and z are written and
+// read at agent scope; a block's z entries have left its CU before its word does.
+//
+// All blocks have to run at once.  They meet at a counter first: a block that
+// has waited kMeetTicks for the others (another stream's kernels may hold the
+// CUs) closes the meeting, unless it has become complete, and every block leaves,
+// those that start later too; nothing has been written by then and the host takes
+// the iterations by launches.  Past the meeting every block is resident, so each wait
+// ends; it is bounded all the same (kSlotSpins polls, seconds).
+//
+// Bound by latency: two exchanges of 2.5 us and a gather of z past the L2s.
+// Gauss-law solve on 9,261 nodes 12.6 -> 7.2 us per iteration (37 blocks),
+// field solve on 59,900 edges 23.6 -> 10.9 us (234 blocks); two steps of the
+// coupled loop on that mesh 6.63 -> 2.88 ms.  z read plainly after a fence that
+// invalidates the caches: 3.4 ms; block sums packed 8 to a line: 3.1 ms, one to
+// 32 or 128 bytes: 2.94 ms; more than one row per four lanes would need more
+// registers than 16 wavefronts have.
+constexpr int kResThreads = 1024, kResLanes = 4, kResRows = kResThreads / kResLanes;
+constexpr int kResMaxBlocks = 256;             // one per CU
+constexpr int kResEntries = 5;                 // entries per lane held in registers
+constexpr int kResVals = 4;
+constexpr int kResStride = 8;                   // words from block to block
+constexpr size_t kResSlots = (size_t)3 * kResMaxBlocks * kResStride;
+constexpr unsigned kMeetClosed = 0x80000000u;
+constexpr long long kMeetTicks = 50000;        // 0.5 ms of the 100 MHz counter
+constexpr unsigned kSlotSpins = 1u << 22;
+constexpr unsigned long long kSlotEmpty = 0xfff8c0de00000001ull;
+
+__device__ __forceinline__ unsigned long long slot_bits(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    return b == kSlotEmpty ? 0x7ff8000000000000ull : b;
+}
+
+__device__ __forceinline__ void agent_store(unsigned long long *at, unsigned long long x) {
+    __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ unsigned long long agent_load(const unsigned long long *at) {
+    return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// this wavefront's stores are where other XCDs see them
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Sum over the wavefront, in every lane: DPP row shifts and broadcasts, lane 63's total read back.
+__device__ __forceinline__ double wave_sum(double x) {
+    x += dpp_get<0x111, 0xf>(x);   // row_shr:1, 2, 4, 8
+    x += dpp_get<0x112, 0xf>(x);
+    x += dpp_get<0x114, 0xf>(x);
+    x += dpp_get<0x118, 0xf>(x);
+    x += dpp_get<0x142, 0xa>(x);   // row_bcast:15 into rows 1 and 3
+    x += dpp_get<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+    const long long b = __double_as_longlong(x);
+    return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(b >> 32), 63) << 32) |
+                                (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffffll), 63));
+}
+
+struct ResShared {
+    double wave[kResThreads / 64][kResVals];
+    double tot[kResVals];
+    int ok;
+};
+
+// The meeting; false: it was closed before all blocks came.  Also empties
+// this block's words of all three sets.
+__device__ __forceinline__ bool res_meet(ResShared &sh, unsigned *meet, unsigned long long *slots) {
+    const unsigned nb = gridDim.x;
+    if (threadIdx.x < 3 * kResVals)
+        agent_store(&slots[((size_t)(threadIdx.x / kResVals) * kResMaxBlocks + blockIdx.x) * kResStride +
+                           threadIdx.x % kResVals], kSlotEmpty);
+    if (threadIdx.x == 0) {   // (the same wavefront as the stores above)
+        stores_done();
+        unsigned seen = __hip_atomic_fetch_add(meet, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+        const long long t0 = wall_clock64();
+        while (seen < nb) {   // (a closed meeting reads as >= kMeetClosed)
+            __builtin_amdgcn_s_sleep(1);
+            seen = __hip_atomic_load(meet, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (seen < nb && wall_clock64() - t0 > kMeetTicks) {
+                unsigned was = seen;
+                if (__hip_atomic_compare_exchange_strong(meet, &was, was | kMeetClosed, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    was |= kMeetClosed;
+                seen = was;
+            }
+        }
+        sh.ok = seen == nb;
+    }
+    __syncthreads();
+    return sh.ok != 0;
+}
+
+// Sums of v over all blocks, to every thread; false (in every thread): a wait ran out.
+template <int kN>
+__device__ __forceinline__ bool res_exchange(ResShared &sh, unsigned long long *slots, unsigned s, double v[kN]) {
+    const unsigned nb = gridDim.x;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < kN; ++k) v[k] = wave_sum(v[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < kN; ++k) sh.wave[wid][k] = v[k];
+    stores_done();   // z
+    __syncthreads();
+    if (wid == 0) {
+        unsigned long long *set = slots + (size_t)(s % 3) * kResMaxBlocks * kResStride;
+        unsigned long long *before = slots + (size_t)((s + 2) % 3) * kResMaxBlocks * kResStride;
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            const double t = wave_sum(lane < kResThreads / 64 ? sh.wave[lane][k] : 0.0);
+            if (lane == 0) agent_store(&set[blockIdx.x * kResStride + k], slot_bits(t));
+        }
+        double sum[kN];
+#pragma unroll
+        for (int k = 0; k < kN; ++k) sum[k] = 0.0;
+        // a lane's words of up to four blocks are requested together
+        constexpr int kPer = kResMaxBlocks / 64;
+        unsigned long long got[kPer][kN];
+        unsigned spins = 0;
+        for (;;) {
+            bool have = true;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (i * 64 < (int)nb)
+#pragma unroll
+                    for (int k = 0; k < kN; ++k)
+                        got[i][k] = agent_load(&set[min(i * 64u + lane, nb - 1) * kResStride + k]);
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (i * 64 < (int)nb)
+#pragma unroll
+                    for (int k = 0; k < kN; ++k) have = have && got[i][k] != kSlotEmpty;
+            if (__all(have) || ++spins > kSlotSpins) break;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+#pragma unroll
+            for (int k = 0; k < kN; ++k)
+                if (i * 64u + lane < nb) sum[k] += __longlong_as_double((long long)got[i][k]);
+#pragma unroll
+        for (int k = 0; k < kN; ++k) {
+            sum[k] = wave_sum(sum[k]);
+            if (lane == 0) sh.tot[k] = sum[k];
+        }
+        if (lane < kResVals) agent_store(&before[blockIdx.x * kResStride + lane], kSlotEmpty);
+        if (lane == 0) sh.ok = spins <= kSlotSpins;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kN; ++k) v[k] = sh.tot[k];
+    return sh.ok != 0;
+}
+
+__device__ __forceinline__ double quad_sum(double x) {   // over the kResLanes lanes of a row
+    x += dpp_get<0xb1, 0xf>(x);   // quad_perm 1, 0, 3, 2
+    x += dpp_get<0x4e, 0xf>(x);   // quad_perm 2, 3, 0, 1
+    return x;
+}
+
+__device__ __forceinline__ double load_z(const double *z, int64_t i) {
+    return __longlong_as_double((long long)agent_load(reinterpret_cast<const unsigned long long *>(z) + i));
+}
+
+__device__ __forceinline__ void store_z(double *z, int64_t i, double x) {
+    agent_store(reinterpret_cast<unsigned long long *>(z) + i, (unsigned long long)__double_as_longlong(x));
+}
+
+// CG of the Gauss-law solve from what k_ns_start or k_ns_start_warm left.
+__global__ void __launch_bounds__(kResThreads) k_ns_resident(NsCsr S, double *sc, const double *dinv, double *x,
+                                                             const double *r, double *z, const double *pin,
+                                                             int64_t nb_in, unsigned long long *slots, double tol2,
+                                                             int max_iter, SolveWatch *watch) {
+    __shared__ ResShared sh;
+    const int64_t row = (int64_t)blockIdx.x * kResRows + threadIdx.x / kResLanes;
+    const int sub = threadIdx.x % kResLanes;
+    const bool mine = row < S.nv, owner = mine && sub == 0;
+    int32_t j0 = 0, j1 = 0;
+    if (mine) {
+        j0 = S.rowptr[row];
+        j1 = S.rowptr[row + 1];
+    }
+    int32_t c[kResEntries];
+    double a[kResEntries];
+#pragma unroll
+    for (int i = 0; i < kResEntries; ++i) {
+        const int32_t j = j0 + sub + i * kResLanes;
+        c[i] = mine ? (int32_t)row : 0;   // (an absent entry: 0 times the row's own z)
+        a[i] = 0.0;
+        if (j < j1) {
+            c[i] = S.col[j];
+            a[i] = S.S[j];
+        }
+    }
+    double xi = 0.0, ri = 0.0, zi = 0.0, di = 0.0, pi = 0.0, qi = 0.0;
+    if (owner) {
+        xi = x[row];
+        ri = r[row];
+        zi = z[row];
+        di = dinv[row];
+    }
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    all_sum4(v, tot);
+    if (!res_meet(sh, reinterpret_cast<unsigned *>(sc + 6), slots)) return;
+    const double b2 = tot[3];
+    double r2 = tot[2], rn = tot[0], ro = 0.0;
+    bool done;
+    int k = 0;
+    for (unsigned s = 0;; ++k, s += 2) {
+        done = b2 == 0.0 || !(r2 > tol2 * b2);   // no source: x = 0, done
+        if (done || k >= max_iter) break;
+        const double be = (k == 0 || ro == 0.0) ? 0.0 : rn / ro;
+        double az = 0.0;
+        double g[kResEntries];
+#pragma unroll
+        for (int i = 0; i < kResEntries; ++i) g[i] = load_z(z, c[i]);
+#pragma unroll
+        for (int i = 0; i < kResEntries; ++i) az += a[i] * g[i];
+        for (int32_t j = j0 + sub + kResEntries * kResLanes; j < j1; j += kResLanes) az += S.S[j] * load_z(z, S.col[j]);
+        az = quad_sum(az);
+        double w[2] = {0.0, 0.0};
+        if (owner) {
+            pi = zi + be * pi;
+            qi = az + be * qi;
+            w[0] = pi * qi;
+        }
+        if (!res_exchange<1>(sh, slots, s, w)) return;
+        const double al = w[0] != 0.0 ? rn / w[0] : 0.0;
+        w[0] = w[1] = 0.0;
+        if (owner) {
+            xi += al * pi;
+            ri -= al * qi;
+            zi = di * ri;
+            store_z(z, row, zi);
+            w[0] = ri * zi;
+            w[1] = ri * ri;
+        }
+        if (!res_exchange<2>(sh, slots, s + 1, w)) return;
+        ro = rn;
+        rn = w[0];
+        r2 = w[1];
+    }
+    if (owner) x[row] = xi;
+    if (blockIdx.x == 0 && threadIdx.x == 0) report(watch, k, done, true, r2, b2);
+}
+
+// COCG of the field step from what k_cocg_init left.
+__global__ void __launch_bounds__(kResThreads) k_cocg_resident(FieldCsr S, double2 alpha, double beta_k, double *sc,
+                                                               const double2 *dinv, double2 *x, const double2 *r,
+                                                               double2 *z, const double *pin, int64_t nb_in,
+                                                               unsigned long long *slots, double tol2, int max_iter,
+                                                               SolveWatch *watch) {
+    __shared__ ResShared sh;
+    const int64_t row = (int64_t)blockIdx.x * kResRows + threadIdx.x / kResLanes;
+    const int sub = threadIdx.x % kResLanes;
+    const bool mine = row < S.ne, owner = mine && sub == 0;
+    double *zs = reinterpret_cast<double *>(z);
+    int32_t j0 = 0, j1 = 0;
+    if (mine) {
+        j0 = S.rowptr[row];
+        j1 = S.rowptr[row + 1];
+    }
+    int32_t c[kResEntries];
+    double am[kResEntries], ak[kResEntries];
+#pragma unroll
+    for (int i = 0; i < kResEntries; ++i) {
+        const int32_t j = j0 + sub + i * kResLanes;
+        c[i] = mine ? (int32_t)row : 0;
+        am[i] = ak[i] = 0.0;
+        if (j < j1) {
+            c[i] = S.col[j];
+            am[i] = S.M[j];
+            ak[i] = S.K[j];
+        }
+    }
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 xi = zero, ri = zero, zi = zero, di = zero, pi = zero, qi = zero;
+    if (owner) {   // (x starts from zero)
+        ri = r[row];
+        zi = z[row];
+        di = dinv[row];
+    }
+    double v[4], tot[4];
+    fetch_sum4(nb_in, pin, v);
+    all_sum4(v, tot);
+    if (!res_meet(sh, reinterpret_cast<unsigned *>(sc + 6), slots)) return;
+    const double b2 = tot[3];
+    double r2 = tot[2];
+    double2 rn = make_double2(tot[0], tot[1]), ro = zero;
+    bool done;
+    int k = 0;
+    for (unsigned s = 0;; ++k, s += 2) {
+        done = b2 == 0.0 || !(r2 > tol2 * b2);
+        if (done || k >= max_iter) break;
+        const double2 be = (k == 0 || (ro.x == 0.0 && ro.y == 0.0)) ? zero : cdiv(rn, ro);
+        double2 m = zero, kk = zero;
+        double2 g[kResEntries];
+#pragma unroll
+        for (int i = 0; i < kResEntries; ++i)
+            g[i] = make_double2(load_z(zs, 2 * (int64_t)c[i]), load_z(zs, 2 * (int64_t)c[i] + 1));
+#pragma unroll
+        for (int i = 0; i < kResEntries; ++i) {
+            m.x += am[i] * g[i].x;
+            m.y += am[i] * g[i].y;
+            kk.x += ak[i] * g[i].x;
+            kk.y += ak[i] * g[i].y;
+        }
+        for (int32_t j = j0 + sub + kResEntries * kResLanes; j < j1; j += kResLanes) {
+            const int64_t cj = S.col[j];
+            const double mv = S.M[j], kv = S.K[j], zx = load_z(zs, 2 * cj), zy = load_z(zs, 2 * cj + 1);
+            m.x += mv * zx;
+            m.y += mv * zy;
+            kk.x += kv * zx;
+            kk.y += kv * zy;
+        }
+        m = make_double2(quad_sum(m.x), quad_sum(m.y));
+        kk = make_double2(quad_sum(kk.x), quad_sum(kk.y));
+        double w[3] = {0.0, 0.0, 0.0};
+        if (owner) {
+            pi = cadd(zi, cmul(be, pi));
+            qi = cadd(cadd(cmul(alpha, m), cscale(kk, beta_k)), cmul(be, qi));
+            const double2 pq = cmul(pi, qi);
+            w[0] = pq.x;
+            w[1] = pq.y;
+        }
+        if (!res_exchange<2>(sh, slots, s, w)) return;
+        const double2 pq = make_double2(w[0], w[1]);
+        const double2 al = (pq.x == 0.0 && pq.y == 0.0) ? zero : cdiv(rn, pq);
+        w[0] = w[1] = w[2] = 0.0;
+        if (owner) {
+            xi = cadd(xi, cmul(al, pi));
+            ri = csub(ri, cmul(al, qi));
+            zi = cmul(di, ri);
+            store_z(zs, 2 * row, zi.x);
+            store_z(zs, 2 * row + 1, zi.y);
+            const double2 rz = cmul(ri, zi);
+            w[0] = rz.x;
+            w[1] = rz.y;
+            w[2] = ri.x * ri.x + ri.y * ri.y;
+        }
+        if (!res_exchange<3>(sh, slots, s + 1, w)) return;
+        ro = rn;
+        rn = make_double2(w[0], w[1]);
+        r2 = w[2];
+    }
+    if (owner) x[row] = xi;
+    if (blockIdx.x == 0 && threadIdx.x == 0) report(watch, k, done, true, r2, b2);
 }
 
 // x_out = e^{-j w t} x on the nodes, e_out = e^{-j w t} D x on the edges
@@ -5973,6 +6335,23 @@ int watch_solve(SolveWatch &W, hipStream_t st, int max_iter, Launch &&launch) {
     return ETPIC_OK;
 }
 
+// A solve in one launch: launch(blocks) enqueues it for `rows` rows.  False in
+// `took` if there are more rows than one block per CU takes (kResMaxBlocks x
+// kResRows = 65,536: their vectors and matrix entries fill the registers) or if
+// the blocks did not meet; the start has to be enqueued again then.
+template <typename Launch>
+int resident_solve(SolveWatch &W, hipStream_t st, int64_t rows, bool &took, Launch &&launch) {
+    took = false;
+    const int64_t blocks = (rows + kResRows - 1) / kResRows;
+    if (blocks > kResMaxBlocks) return ETPIC_OK;
+    __atomic_store_n(&W.word, 0ull, __ATOMIC_RELAXED);
+    launch((unsigned)blocks);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
+    took = __atomic_load_n(&W.word, __ATOMIC_RELAXED) != 0;
+    return ETPIC_OK;
+}
+
 // Field solver arrays: CSR row pointers, columns, M and K values, Dirichlet
 // mask, face -> edge table, Jacobi inverse diagonal, 9 complex work vectors,
 // block partials and the 12 iteration scalars.
@@ -5993,7 +6372,7 @@ FieldPtrs2 field_layout(Carve &cv, int64_t ne, int64_t nf, int64_t nnz) {
     f.face_edge = cv.take<int32_t>(3 * nf);
     f.dinv = cv.take<double2>(ne);
     f.vec = cv.take<double2>(9 * ne);
-    f.partial = cv.take<double>(4 * (nb + kNsBlocks));
+    f.partial = cv.take<double>(4 * (nb + kNsBlocks) + kResSlots);
     f.sc = cv.take<double>(12);
     return f;
 }
@@ -6134,13 +6513,25 @@ int etpic_field_step(etpic_ctx *ctx, double t_next, double *u, double *v, double
     k_nm_rhs<<<gr, kBlock, 0, st>>>(F.csr(), wv, us, gdd, c, s, rhs);
     // partial sets: the start and the update write the first, the product the second
     double *pa = F.partial, *pb = F.partial + 4 * F.nb;
-    k_cocg_init<<<ge, kBlock, 0, st>>>(ne, rhs, F.dinv, x, r, z, p, q, pa, F.sc);
-    HIP_TRY(hipGetLastError());
     const unsigned ga = (unsigned)std::min<int64_t>((ne * kRowLanes + kNsThreads - 1) / kNsThreads, kNsBlocks);
     const unsigned gu = (unsigned)std::min<int64_t>((ne + kNsVecThreads - 1) / kNsVecThreads, kNsBlocks);
     const double tol2 = tol * tol;
     SolveWatch &W = *ctx->h_watch;
-    if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
+    auto start = [&] {
+        k_cocg_init<<<ge, kBlock, 0, st>>>(ne, rhs, F.dinv, x, r, z, p, q, pa, F.sc);
+    };
+    start();
+    HIP_TRY(hipGetLastError());
+    unsigned long long *slots = reinterpret_cast<unsigned long long *>(F.partial + 4 * (F.nb + kNsBlocks));
+    bool took = false;
+    if (int rc = resident_solve(W, st, ne, took, [&](unsigned blocks) {
+            k_cocg_resident<<<blocks, kResThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, F.dinv, x, r, z, pa, ge, slots,
+                                                            tol2, max_iter, &W);
+        }))
+        return rc;
+    if (!took && ne <= (int64_t)kResMaxBlocks * kResRows) start();
+    // (else: too many rows, or other work held the CUs)
+    if (!took) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
             k_cocg_apply<<<ga, kNsThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, z, p, q, pa, k == 0 ? (int64_t)ge : gu,
                                                     pb, k, tol2, check_only ? 1 : 0, &W);
             if (!check_only)
@@ -6179,7 +6570,7 @@ NsPtrs ns_layout(Carve &cv, int64_t nv, int64_t ne, int64_t nf, int64_t nnz) {
     n.dinv = cv.take<double>(nv);
     n.wall = cv.take<uint8_t>(nv);
     n.vec = cv.take<double>(8 * nv);
-    n.partial = cv.take<double>(8 * kNsBlocks);
+    n.partial = cv.take<double>(8 * kNsBlocks + kResSlots);
     n.sc = cv.take<double>(12);
     n.bzero = cv.take<double>(2 * nf);
     n.ezero = cv.take<double>(2 * ne);
@@ -6298,16 +6689,27 @@ int ns_solve_impl(etpic_ctx *ctx, const NsRhs &R, double *x, double c, double s,
     // partials: pa from the product (gr blocks), pb from the start and the update
     double *pa = N.partial, *pb = N.partial + 4 * kNsBlocks;
     const int64_t nb = warm ? gr : gv;
-    if (warm)
-        k_ns_start_warm<<<gr, kNsThreads, 0, st>>>(N.csr(), ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r,
-                                                   z, p, q, pb, N.sc);
-    else
-        k_ns_start<<<gv, kNsVecThreads, 0, st>>>(nv, ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r, z, p, q,
-                                                 pb, N.sc);
+    auto start = [&] {
+        if (warm)
+            k_ns_start_warm<<<gr, kNsThreads, 0, st>>>(N.csr(), ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r,
+                                                       z, p, q, pb, N.sc);
+        else
+            k_ns_start<<<gv, kNsVecThreads, 0, st>>>(nv, ctx->d_v2e_ptr, ctx->d_v2e_code, R, N.wall, N.dinv, x, r, z, p, q,
+                                                     pb, N.sc);
+    };
+    start();
     HIP_TRY(hipGetLastError());
     const double tol2 = tol * tol;
     SolveWatch &W = *ctx->h_watch;
-    if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
+    unsigned long long *slots = reinterpret_cast<unsigned long long *>(N.partial + 8 * kNsBlocks);
+    bool took = false;
+    if (int rc = resident_solve(W, st, nv, took, [&](unsigned blocks) {
+            k_ns_resident<<<blocks, kResThreads, 0, st>>>(N.csr(), N.sc, N.dinv, x, r, z, pb, nb, slots, tol2, max_iter,
+                                                          &W);
+        }))
+        return rc;
+    if (!took && nv <= (int64_t)kResMaxBlocks * kResRows) start();
+    if (!took) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
             k_ns_apply<<<gr, kNsThreads, 0, st>>>(N.csr(), N.sc, z, p, q, pb, k == 0 ? nb : (int64_t)gv, pa, k, tol2,
                                                   check_only ? 1 : 0, &W);
             if (!check_only)

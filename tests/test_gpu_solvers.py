@@ -74,3 +74,62 @@ def test_no_source(ctx):
     e = torch.ones((c.n_edge, 2), dtype=torch.float64, device="cuda")
     assert c.ns_solve(rho0=zero, e_out=e, tol=TOL) == (E.OK, 0, 0.0)
     assert torch.count_nonzero(e).item() == 0
+
+
+def test_solves_beside_other_work():
+    """Two contexts solving from two threads on streams of their own, beside a
+    third stream's products that fill the chip: whichever way a solve takes its
+    iterations then, it converges to the result of the quiet one."""
+    import threading
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2208_12795_amd import etpic as E
+    xyz, tv = synth.kuhn_mesh((20, 20, 20), (1.0, 1.0, 1.0), 0.1, np.random.default_rng(6))
+    ctxs = []
+    for _ in range(2):
+        c = E.Context(0)
+        c.upload_mesh(xyz, tv)
+        c.field_setup(2e-11, 3e9, EPS0, MU0)
+        c.ns_setup(EPS0)
+        ctxs.append(c)
+    ne, nf, nv = ctxs[0].n_edge, ctxs[0].n_face, ctxs[0].n_vert
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *n: torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    rho0, state = rnd(nv), [rnd(ne, 2), rnd(ne, 2) * 1e9, rnd(ne, 2) * 1e18, rnd(nf, 2) * 1e-9]
+
+    def both(c, stream=None):
+        s = [t.clone() for t in state]
+        e = torch.zeros((ne, 2), dtype=torch.float64, device="cuda")
+        a = c.field_step(2e-11, *s, tol=TOL, stream=stream)
+        b = c.ns_solve(rho0=rho0, e_out=e, tol=TOL, stream=stream)
+        return a, b, s[2], e
+    quiet = both(ctxs[0])
+    scale = [float(quiet[k].abs().max()) for k in (2, 3)]
+    m = rnd(4096, 4096)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        for _ in range(8):
+            m2 = m @ m
+    bad = []
+
+    def work(c):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(4):
+                a, b, x, e = both(c, st)
+                st.synchronize()
+                # both solves stop at a residual of 1e-12: the results differ by that times the condition
+                far = max(float((v - q).abs().max()) / s for v, q, s in zip((x, e), quiet[2:], scale))
+                if a[0] != E.OK or b[0] != E.OK or abs(a[1] - quiet[0][1]) > 1 or abs(b[1] - quiet[1][1]) > 1 or far > 1e-8:
+                    bad.append((a, b, far))
+    threads = [threading.Thread(target=work, args=(c,)) for c in ctxs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not bad and bool(torch.isfinite(m2).all())
+    for c in ctxs:
+        c.close()
