@@ -2636,7 +2636,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_ds(StepArgs<Real> a, DsArgs<Rea
 // and accumulates the gradient with respect to the complex edge envelope,
 // dL/dRe e_e + j dL/dIm e_e = (Ebar . W1_e(x_k)) e^{-j w t_k}, reduced over runs
 // of equal tet before the float64 atomics.
-constexpr int kMaxAdj = 5;   // steps reversed per launch: their states fill the LDS left beside the rows
+constexpr int kMaxAdj = 5;   // steps reversed per launch: the states between them fill the LDS left beside the rows
 
 __global__ void __launch_bounds__(kBlock) k_copy_state(etpic_particles src, etpic_particles dst) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2750,16 +2750,22 @@ __device__ __forceinline__ void adjoint_step(const double *cf, const double *gm,
 // edges gather over the steps and are reduced over runs of equal tet once.
 // Rows are formed from the staged parts as in k_push_multi.  A particle that
 // leaves its tet in one of the steps is left to k_adjoint_leavers.
+//   Bound by latency at the wavefronts that the LDS lets in: the last step's
+// start stays in registers and the first one's is read again, so 14.6 KB per
+// wavefront instead of 20.7, and the leavers' queue comes in parts, for which
+// fewer wavefronts wait.  2e6 particles, 5 steps: 218 -> 175 us (8 rows staged
+// at a time instead of 16: 166, but a second pass from 9 tets per wavefront on).
 __global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
     constexpr int kParts = kRowParts<1>;
     constexpr int kRuns = 16;
     constexpr int kEnt = kRuns * kRowReals;
     __shared__ double part[kParts * kEnt];
     __shared__ __align__(16) double rows[kEnt];
-    __shared__ double s_state[kMaxAdj][6][64];
+    __shared__ double s_state[kMaxAdj - 2][6][64];   // starts of all but the first and the last step
     __shared__ int s_tet[64];
     const unsigned ln = threadIdx.x;
-    const int64_t p = b.first + (int64_t)xcd_block(blockIdx.x, gridDim.x) * 64 + ln;
+    const unsigned blk = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t p = b.first + (int64_t)blk * 64 + ln;
     int T = -1;
     if (p < b.end) {
         T = b.tet[p];
@@ -2808,31 +2814,45 @@ __global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
         for (int j = 0; j < b.nsteps; ++j) {
             form_rows(j);
             if (live) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    s_state[j][k][ln] = l[k + 1];
-                    s_state[j][3 + k][ln] = v[k];
-                }
+                const bool on = j < b.nsteps - 1;
                 const double x[3] = {l[1], l[2], l[3]};
-                double dl[4], t[4];
-                gather_boris(cf, gm, x, a.h, v);
-                if (increments(gr, v, a.dt_r, 1.0, l, dl, t)) {
+                double dl[4], t[4], out[3] = {v[0], v[1], v[2]};
+                if (on && j > 0)
 #pragma unroll
-                    for (int k = 1; k < 4; ++k) l[k] = t[k];
-                } else {
+                    for (int k = 0; k < 3; ++k) {
+                        s_state[j - 1][k][ln] = l[k + 1];
+                        s_state[j - 1][3 + k][ln] = v[k];
+                    }
+                gather_boris(cf, gm, x, a.h, out);
+                if (!increments(gr, out, a.dt_r, 1.0, l, dl, t)) {
                     left = true;
                     live = false;
+                } else if (on) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        l[k + 1] = t[k + 1];
+                        v[k] = out[k];
+                    }
                 }
             }
         }
 #pragma unroll 1
         for (int j = b.nsteps - 1; j >= 0; --j) {
-            if (j != b.nsteps - 1) form_rows(j);   // the last step's rows are still there
+            const bool kept = j == b.nsteps - 1;   // the last step's rows and states are still there
+            if (!kept) form_rows(j);
             if (live) {
+                if (!kept && j > 0) {
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    l[k + 1] = s_state[j][k][ln];
-                    v[k] = s_state[j][3 + k][ln];
+                    for (int k = 0; k < 3; ++k) {
+                        l[k + 1] = s_state[j - 1][k][ln];
+                        v[k] = s_state[j - 1][3 + k][ln];
+                    }
+                } else if (!kept) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        l[k + 1] = b.lam[k][p];
+                        v[k] = b.v[k][p];
+                    }
                 }
                 double w[6];
                 adjoint_step(cf, gm, gr, l, v, a.h, a.dt_r, nullptr, xb, vb, w);
@@ -2867,25 +2887,21 @@ __global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
             unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e] + 1], im[e]);
         }
     }
-    // a launch takes at most kWalkQueueCap particles: the queue holds them all
+    // a launch takes at most kWalkQueueCap particles, and a part of the queue
+    // belongs to at most kShardCap of them: the queue holds them all
     const unsigned long long wmask = __ballot(left);
-    if (wmask) {
-        unsigned base = 0;
-        if (ln == 0) base = atomicAdd(&a.walk_ctr[0], (unsigned)__popcll(wmask));
-        base = __shfl(base, 0);
-        if (left) a.walk_queue[base + (unsigned)__popcll(wmask & (upto >> 1))] = (unsigned)p;
-    }
+    if (wmask) queue_leavers(a, wmask, left, (unsigned)p, true, blk);
 }
 
 // The same for the queued particles, one lane each: forward through their
 // walks with every step's start kept in the segment's state slots, then back,
-// each step's reflections recomputed and its gradient added edge by edge.
+// each step's reflections recomputed.  Bound by the float64 atomics on the
+// edges, 12 per tet a particle visits (12 per step before: 125 -> 53 us at 2e6
+// particles and 5 steps).
 __global__ void __launch_bounds__(kBlock) k_adjoint_leavers(StepArgs<double> a, AdjArgs b, unsigned *next_ctr) {
-    if (blockIdx.x == 0 && threadIdx.x < 3) next_ctr[threadIdx.x] = 0u;
-    const unsigned count = min(__atomic_load_n(&a.walk_ctr[0], __ATOMIC_RELAXED), kWalkQueueCap);
-    for (unsigned i = blockIdx.x * kBlock + threadIdx.x; i < count; i += gridDim.x * kBlock) {
-        const int64_t p = a.walk_queue[i];
-        if (p >= b.end) continue;
+    if (blockIdx.x == 0) clear_counters(next_ctr);
+    take_leavers(a, [&](int64_t p) {
+        if (p >= b.end) return;
         int T = b.tet[p];
         double l[4], v[3], xb[3], vb[3];
         l[0] = 0.0;
@@ -2924,6 +2940,20 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_leavers(StepArgs<double> a, 
                 T = walk<double, true>(a, T, l, d, v, R);
             }
         }
+        // the gradient sums of consecutive steps in one tet go to its edges together
+        double gc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, gs[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        auto flush = [&]() {
+            double re[6], im[6];
+            edge_sums(gc, re);
+            edge_sums(gs, im);
+            const int32_t *ed = push_row_edges(a.gpush + (int64_t)T * PushRow<double>::kStride);
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e]], re[e]);
+                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e] + 1], im[e]);
+                gc[e] = gs[e] = 0.0;
+            }
+        };
 #pragma unroll 1
         for (int j = b.nsteps - 1; j >= 0; --j) {
 #pragma unroll
@@ -2931,7 +2961,11 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_leavers(StepArgs<double> a, 
                 l[k + 1] = b.s_lam[j][k][p];
                 v[k] = b.s_v[j][k][p];
             }
-            T = b.s_tet[j][p];
+            const int at = b.s_tet[j][p];
+            if (at != T || j == b.nsteps - 1) {
+                if (j < b.nsteps - 1) flush();
+                T = at;
+            }
             double cf[kRowReals], gm[9], gr[9], dl[4], t[4];
             row_at(j, cf);
             load_rows<double, false>(a, T, gm, gr);
@@ -2945,22 +2979,21 @@ __global__ void __launch_bounds__(kBlock) k_adjoint_leavers(StepArgs<double> a, 
                 double lw[4] = {0.0, l[1], l[2], l[3]};
                 walk<double, true>(a, T, lw, d, out, R);
             }
-            double w[6], g6[6];
+            double w[6];
             adjoint_step(cf, gm, gr, l, v, a.h, a.dt_r, R, xb, vb, w);
-            edge_sums(w, g6);
-            const int32_t *ed = push_row_edges(a.gpush + (int64_t)T * PushRow<double>::kStride);
 #pragma unroll
             for (int e = 0; e < 6; ++e) {
-                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e]], g6[e] * b.c[j]);
-                unsafeAtomicAdd(&b.grad_e[2 * (int64_t)ed[e] + 1], -(g6[e] * b.s[j]));
+                gc[e] = fma(w[e], b.c[j], gc[e]);
+                gs[e] = fma(w[e], -b.s[j], gs[e]);
             }
         }
+        flush();
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             b.vb[k][p] = vb[k];
             b.xb[k][p] = xb[k];
         }
-    }
+    });
 }
 
 // ------------------------------------------------------------------ point location
