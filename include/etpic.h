@@ -310,11 +310,11 @@ int etpic_gather_push_deposit(etpic_ctx *ctx, const etpic_particles *p, int prec
 /* nsteps consecutive steps (times (step0 + j) dt, j = 0..nsteps-1) with the same
  * field DoFs: the same result as nsteps calls of etpic_gather_push_deposit,
  * with rho (if not NULL) deposited after the last step only.  Up to 16 steps
- * share one particle-kernel launch, in which the particle state stays in
- * registers (one step per launch where a flag forces the slices per
- * wavefront); the field coefficients are prepared once per call.  With
- * ETPIC_STEP_TIMING, etpic_kernel_time books a launch's time evenly over its
- * steps.
+ * (32 of at most 32,768 particles) share one particle-kernel launch, in which
+ * the particle state stays in registers (one step per launch where a flag
+ * forces the slices per wavefront); the field coefficients are prepared once
+ * per call.  With ETPIC_STEP_TIMING, etpic_kernel_time books a launch's time
+ * evenly over its steps.
  * Asynchronous on `stream`.  Errors as etpic_gather_push_deposit. */
 int etpic_run_steps(etpic_ctx *ctx, const etpic_particles *p, int precision, const etpic_species *sp,
                     const etpic_fields *f, int64_t step0, int nsteps, double dt, double omega, double *dG,

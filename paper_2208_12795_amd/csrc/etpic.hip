@@ -1609,7 +1609,7 @@ __global__ void __launch_bounds__(kBlock) k_walk(StepArgs<Real> a) {
 // itself.  Measured, ten steps and their re-sort in one call, 40^3 x 6 tets,
 // against one step per launch: 1e7 float64 2.90 -> 0.78 ms, 5e7 mixed 9.64 ->
 // 2.50 ms, 1e7 compact 1.99 -> 0.71 ms; the 100 steps of 1,000 electrons on
-// 750 tets 1.15 -> 0.16 ms.
+// 750 tets 1.14 -> 0.12 ms.
 //
 // The rows of each step come from the parts of the tet's row (real, imaginary,
 // dc, built once per call by the coefficient pass).  A wavefront stages the
@@ -1623,7 +1623,12 @@ __global__ void __launch_bounds__(kBlock) k_walk(StepArgs<Real> a) {
 // A particle that leaves its tet at step j stops there (its start point of
 // that step, its new velocity and j are kept: tet = -(T + j nt + 2)) and is
 // queued; k_walk_multi walks it and takes it through the remaining steps.
-constexpr int kMaxFused = 16;
+//
+// A launch takes up to 16 steps, of few particles up to 32: there the launch
+// itself and the walk after it are the larger part (100 steps of 1,000
+// electrons: 7 launches 147, 4 launches 122 us), while of many particles more steps in
+// one launch mean more of them that finish it in the walk.
+constexpr int kMaxFused = 32, kMaxFusedMany = 16;
 constexpr int kCoefDoubles = kRowParts<3> * kRowReals;   // per tet: the largest of the coefficient forms
 
 template <int kSnap>
@@ -4945,7 +4950,7 @@ struct etpic_ctx {
     // src, the particles of src are first counting-sorted by tet into p, the
     // scatter folded into the first launch's particle kernel.
     //
-    // Several steps go up to kMaxFused at a time through k_push_multi and
+    // Several steps go up to most_fused at a time through k_push_multi and
     // k_walk_multi; one step, or steps whose slices per wavefront a flag
     // forces, through the one-step kernels (coefficients, particle kernel,
     // walk), which read 10 reals per tet instead of the 30 or 70 of the row
@@ -4959,7 +4964,7 @@ struct etpic_ctx {
             if (int r = sort_count(src, st)) return r;
         constexpr uint32_t kForced =
             ETPIC_STEP_SLICES_1 | ETPIC_STEP_SLICES_2 | ETPIC_STEP_SLICES_4 | ETPIC_STEP_SLICES_16;
-        const int most = most_fused();
+        const int most = most_fused(p->n);
         if (nsteps == 1 || most < 2 || (flags & kForced))
             return single_steps<Real>(p, sp, plans, nsteps, dt, omega, dG, rho, flags, st, src);
         if constexpr (std::is_same<Real, float>::value) {
@@ -5017,9 +5022,9 @@ struct etpic_ctx {
 
     // Steps per multi-step launch: a leaver's mark holds its tet and its step,
     // and both have to fit an int32.
-    int most_fused() const {
-        return (int)std::max<int64_t>(
-            1, std::min<int64_t>(kMaxFused, (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
+    int most_fused(int64_t n) const {
+        return (int)std::max<int64_t>(1, std::min<int64_t>(n <= kFewParticles ? kMaxFused : kMaxFusedMany,
+                                                           (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
     }
 
     // the parts of the 10-real rows, from which multi-step launches form the
@@ -5178,7 +5183,7 @@ struct etpic_ctx {
         const int64_t n = p->n, nt = host.nt;
         if (!d_coef_env)
             return fail(ETPIC_ESTATE, "no downshifted rows bound (etpic_ds_rows_bytes, etpic_ds_rows_bind)");
-        const int most = std::min(kMaxDs, most_fused());
+        const int most = std::min(kMaxDs, most_fused(p->n));
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
         const etpic_fields *snap[3] = {f, nullptr, nullptr};
         const double w1[3] = {1.0, 0.0, 0.0};
@@ -5988,7 +5993,7 @@ static int adjoint_forward(etpic_ctx *ctx, const etpic_particles &from, const et
     std::vector<StepPlan> plans((size_t)nsteps);
     for (int j = 0; j < nsteps; ++j)
         plans[j] = StepPlan{{f, nullptr, nullptr}, {1.0, 0.0, 0.0}, (double)(step0 + j) * dt};
-    return ctx->fused_steps<double, 1, false>(&to, sp, plans.data(), nsteps, ctx->most_fused(), dt, omega, dG, nullptr,
+    return ctx->fused_steps<double, 1, false>(&to, sp, plans.data(), nsteps, ctx->most_fused(to.n), dt, omega, dG, nullptr,
                                               ETPIC_STEP_XCD_REMAP, st, &from, false, parts_ready);
 }
 

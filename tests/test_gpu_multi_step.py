@@ -190,3 +190,9 @@ def test_reverse_in_pieces_matches_every_step_checkpoints(E, torch_cuda, n, nste
     for a, b in zip(out[0][1], out[1][1]):
         assert torch.allclose(a, b, rtol=0, atol=1e-12 * b.abs().max().item())
     ctx.close()
+
+
+# one launch's most steps and one more, of few particles and of more than few
+@pytest.mark.parametrize("n,nsteps", [(65, 32), (65, 65), (32768, 17), (32769, 17)])
+def test_steps_per_launch(E, torch_cuda, n, nsteps):
+    test_multi_equals_single_steps(E, torch_cuda, n, False, nsteps, 300.0, False, 0)
