@@ -2,13 +2,16 @@
 """Throughput of the envelope-tracking particle-mesh step on one MI355X.
 
 A step is one pass of the particle path over all particles: the per-tet
-carrier-rotated field coefficients (k_tet_coef), the particle kernel (gather,
-Boris push, in-tet path-integral deposit with same-tet sums before the edge
-atomics; k_push), the walk of the particles that left their tet (k_walk), and
-the counting sort by tet every `--sort-every` steps (amortised, inside the
-timed region).  The steps between two sorts go through one multi-step call,
-in which the walk of a step and the coefficient pass of the next share one
-kernel launch.  Default workload: the 40^3 x 6 jittered Kuhn mesh (384,000
+carrier-rotated field coefficients, gather, Boris push, in-tet path-integral
+deposit, the walk of the particles that left their tet, and the counting sort
+by tet every `--sort-every` steps (amortised, inside the timed region).  The
+steps between two sorts go through one multi-step call, in which up to 16
+steps share a launch of the particle kernel (k_push_multi, the particle state
+in registers, each step's field rows formed from per-tet parts in LDS; the
+first launch also scatters the particles to their sorted places) and one of
+the walk (k_walk_multi, which takes the leavers through their remaining
+steps); single steps, as in the warmup and the logged phase, go through
+k_tet_coef, k_push and k_walk.  Default workload: the 40^3 x 6 jittered Kuhn mesh (384,000
 tets) with 10,000,000 electrons (Maxwellian, 1e6 m/s), an 8-mode envelope on a
 10 GHz carrier, B = 0.5 T, dt = 1e-12 s; `--workload large-box` runs the 2:1:1
 160x80x80 x 6 mesh with 2e8 electrons (bunch + background, B = 1 T along x).
@@ -57,8 +60,9 @@ VALU_PEAK_PER_S = 256 * 4 * 2.4e9 / 4
 #                     fixed point (compact mixed form): 4 + 2 x (12 + 12) = 52 B.
 #                     (The tet id is rewritten only for the particles that
 #                     leave their tet, by the walk kernel.)
-#  per tet and step : its coefficient row (24 reals), gradient row (9 reals) and
-#                     edge ids (6 x 4 B), read once: 288 B (float64), 156 B (mixed)
+#  per tet and step : its coefficient row (10 reals), gradient row (9 reals), edge
+#                     ids (6 x 4 B) and geometry row (9 reals), read once: 248 B
+#                     (float64), 136 B (both mixed forms)
 #  per edge and step: the current accumulator read + written once (16 B)
 BYTES_PER_PARTICLE = {"fp64": 100, "mixed": 76, "mixed_fixed": 52}
 # per tet and launch: the step's coefficient row (A_0, beta, C_0, b: 10 reals),
@@ -68,6 +72,16 @@ BYTES_PER_PARTICLE = {"fp64": 100, "mixed": 76, "mixed_fixed": 52}
 BYTES_PER_TET = {"fp64": 248, "mixed": 136, "mixed_fixed": 136}
 BYTES_PER_EDGE = 16
 KERNEL_NAME = {"fp64": "k_push<double>", "mixed": "k_push<float>", "mixed_fixed": "k_push_fixed"}
+# The same for a launch of several steps, k_push_multi: the state once per
+# launch, with the tet id and, where the launch sorts, the 8 B id written too;
+# per tet the row's parts (real, imaginary and dc of its 10 reals, float64:
+# 240 B), the gradient row, edge ids and geometry row, and the current slots
+# read and written (96 B).
+MULTI_BYTES_PER_PARTICLE = {"fp64": 104, "mixed": 80, "mixed_fixed": 56}
+MULTI_BYTES_PER_TET = {"fp64": 240 + 72 + 24 + 72 + 96, "mixed": 240 + 36 + 24 + 36 + 96,
+                       "mixed_fixed": 240 + 36 + 24 + 36 + 96}
+ID_BYTES = 16
+MAX_STEPS_PER_LAUNCH = 16   # 32 of at most 32,768 particles
 # Algorithmic bytes of a whole step (what the method must move per particle-step
 # and per tet, independent of how the kernels split the work): the particle
 # state read and written, tet included (2 x (lam 24 + v 24 + tet 4) = 104 B in
@@ -77,6 +91,8 @@ KERNEL_NAME = {"fp64": "k_push<double>", "mixed": "k_push<float>", "mixed_fixed"
 # (2 x (52 + 8) + 8 = 128 B in float64, 2 x (40 + 8) + 8 = 104 B mixed).
 # The compact mixed form stores the barycentrics as 32-bit fixed point:
 # 2 x (12 + 12 + 4) = 56 B per particle-step, 2 x (28 + 8) + 8 = 80 B per sort.
+# Where a launch takes several steps it moves the state and the tets' data once
+# for all of them, and a sort it takes along adds the ids, keys and offsets (24 B).
 STEP_BYTES_PER_PARTICLE = {"fp64": 104, "mixed": 80, "mixed_fixed": 56}
 STEP_BYTES_PER_TET = 320
 SORT_BYTES_PER_PARTICLE = {"fp64": 128, "mixed": 104, "mixed_fixed": 80}
@@ -115,7 +131,16 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_name(form, slices):
+def steps_per_launch(block, n):
+    """Steps of one launch of the particle kernel in a call of `block` steps of n particles."""
+    most = 2 * MAX_STEPS_PER_LAUNCH if n <= 32768 else MAX_STEPS_PER_LAUNCH
+    return block / -(-block // most)
+
+
+def kernel_name(form, slices, per=1, sorts=False):
+    if per > 1:
+        flags = [str(x).lower() for x in (False, sorts, form == "mixed_fixed")]
+        return f"k_push_multi<{REAL[form]}, 1, {', '.join(flags)}>"
     if slices <= 1:
         return KERNEL_NAME[form]
     if slices == 2:   # two pipelined slices per wavefront (float forms)
@@ -266,8 +291,12 @@ def run_form(E, torch, ctx, w, precision, steps, warmup, sort_every, fields, nlo
     gauss_ms = g0.elapsed_time(g1)
     n = parts.n
     logged = logged_steps(E, torch, ctx, parts, sp, fields, w, step + 1, nlog) if nlog else None
+    per = steps_per_launch(min(block, steps), n)
     return {
         "slices": slices,
+        "steps_per_launch": per,
+        "sorts_in_launch": bool(sort_every) and per == min(block, steps),
+        "launch_ms": (kt["push"] + kt["push_sort"]) / max(kt["steps_push"] + kt["steps_sort"], 1) * per,
         "spin_up_ms": round(spin_ms, 1),
         "stream_ms": stream_ms,
         "logged": logged,
@@ -277,13 +306,14 @@ def run_form(E, torch, ctx, w, precision, steps, warmup, sort_every, fields, nlo
         "sort_step_kernel_ms": kt["push_sort"] / max(kt["steps_sort"], 1),
         "coef_ms": kb["coef"] / max(nbl, 1),
         "walk_ms": kb["walk"] / max(nbl, 1),
-        "timing_note": "kernel_ms: particle kernel of the in-place steps; sort_step_kernel_ms: the one of the "
-                       "first step after each re-sort, which also scatters the particles to their sorted places "
-                       "(both from HIP events bound to the kernel's dispatches over the timed region); walk_ms "
-                       "and coef_ms per step from a block of %d steps after the timed region with every kernel "
-                       "timed: walk_ms covers the walk and, except before a sort, the next step's coefficient "
-                       "pass (one launch), and the edge gather of the per-tet sums at the end of the block; "
-                       "coef_ms averages the stand-alone passes over the steps" % nbd,
+        "timing_note": "launch_ms: one launch of the particle kernel, which takes steps_per_launch steps and, "
+                       "the first after each re-sort, scatters the particles to their sorted places; its time is "
+                       "booked evenly over its steps, kernel_ms the share of a step in place and "
+                       "sort_step_kernel_ms of a sorting launch's first step (from HIP events bound to the "
+                       "kernel's dispatches over the timed region); walk_ms and coef_ms per step from a block of "
+                       "%d steps after the timed region with every kernel timed: walk_ms covers the walk of a "
+                       "launch's leavers through their remaining steps and the edge gather of the per-tet sums "
+                       "at the end of the block, coef_ms the pass that builds the rows' parts once per call" % nbd,
         "launches": launches,
         "sort_ms": sort_ms,
         "gauss_rel": r / p,
@@ -429,8 +459,7 @@ def ns_solve_timing(E, torch, ctx, w, reps=3):
             "split_loop_ms_per_step": split_ms, "split_loop_iterations_per_step": split_it / 5,
             "loop_ms_per_step": loop[1][0], "loop_cg_iterations_per_solve": loop[1][1],
             "loop10_ms_per_step": loop[10][0], "loop10_cg_iterations_per_solve": loop[10][1],
-            "note": "side path, not in value; wall time of the whole solve (one host read of the iteration "
-                    "scalars per 10 iterations included), best of %d; loop: 20 particle steps of all %d "
+            "note": "side path, not in value; wall time of the whole solve (the host's wait for its result included), best of %d; loop: 20 particle steps of all %d "
                     "electrons (sorted by tet once) with a warm-started solve before every step (loop) or "
                     "every 10th (loop10), mean per step; em_loop: particle step, implicit field step and "
                     "Gauss correction per step, mean of 5; split_loop: the same with the field step on the "
@@ -499,25 +528,24 @@ def coarse_step_timing(E, torch, synth, ctx, w, fine=10, reps=5):
     ctx.check()
     ms = e0.elapsed_time(e1) / (reps * fine)
     return {"fine_steps_per_coarse": fine, "ms_per_fine_step": ms, "value": parts.n / (ms * 1e-3),
-            "coef_ms": kb["coef"] / max(nbl, 1), "walk_coef_ms": kb["walk"] / max(nbl, 1),
+            "coef_ms": kb["coef"] / max(nbl, 1), "walk_ms": kb["walk"] / max(nbl, 1),
             "push_ms": kt["push"] / max(kt["steps_push"], 1),
             "note": "float64, three envelope snapshots interpolated at every fine step; no sort inside"}
 
 
-# downshifted step without dc edge DoFs, see ds_step_timing
-DS_BYTES_PER_PARTICLE = {"fp64": 556, "mixed": 304}
-DS_BYTES_PER_TET = {"fp64": 576 + 96, "mixed": 576 + 64}   # complex-envelope rows and the push row
+# launch of downshifted steps without dc edge DoFs, see ds_step_timing
+DS_BYTES_PER_PARTICLE = {"fp64": 868, "mixed": 460}
+DS_BYTES_PER_TET = {"fp64": 240 + 72 + 24 + 72 + 96, "mixed": 240 + 36 + 24 + 36 + 96}   # as k_push_multi's
 
 
 def ds_step_timing(E, torch, ctx, w, form="fp64", nsteps=10, reps=3):
     """Downshifted form (carrier-exact velocity quadrature of envelope samples
     interpolated over three steps, Adams-Bashforth positions), same workload and
     step as the metric, particles sorted once, calls of `nsteps` steps after a
-    3-step ramp.  Algorithmic bytes per particle-step of its particle kernel,
-    float64: read tet 4, lam 24, v 24, three earlier velocities 72, two E
-    samples (Re, Im) 96, two B samples (Re, Im, dc) 144; write lam 24, v 24,
-    one velocity 24, one E sample 48, one B sample 72: 556 B.  Mixed (float32
-    velocities and samples): 196 read + 108 written = 304 B."""
+    3-step ramp, one launch each.  Algorithmic bytes per particle and launch:
+    read tet 4, lam 24, v 24 and the history 384 (the earlier velocities and the
+    field samples of the ring), all but the tet written back: 868 B in float64.
+    Mixed (float32 velocities and history): 232 read + 228 written = 460 B."""
     sp = E.Species(w.q, w.m, w.w)
     f = E.Fields.from_numpy(w.e_env, w.b_env, None, w.b_dc)
     parts = E.Particles.from_numpy(w.tet, w.lam, w.vel, w.ids, precision=E.FP64 if form == "fp64" else E.MIXED)
@@ -544,16 +572,16 @@ def ds_step_timing(E, torch, ctx, w, form="fp64", nsteps=10, reps=3):
     ms = e0.elapsed_time(e1) / (reps * nsteps)
     push_ms = kt["push"] / max(kt["steps_push"], 1)
     nbytes = DS_BYTES_PER_PARTICLE[form] * parts.n + DS_BYTES_PER_TET[form] * w.tet_vert.shape[0] + 16 * ctx.n_edge
-    ach = nbytes / (push_ms * 1e-3) / 1e9
+    ach = nbytes / (push_ms * nsteps * 1e-3) / 1e9
     del hist
     return {"ms_per_step": ms, "value": parts.n / (ms * 1e-3), "push_ms": push_ms,
             "walk_ms": kb["walk"] / max(nbl, 1), "coef_env_ms": kb["coef"],
             "roofline": {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(ach / HBM_PEAK_GBS, 4),
                          "kernel": "k_push_ds<double, false>" if form == "fp64" else "k_push_ds<float, false>",
-                         "bytes_per_launch": nbytes},
-            "note": f"{form} downshifted step (side path, not in value); the complex-envelope rows are built "
-                    "once per call"}
+                         "bytes_per_launch": nbytes, "steps_per_launch": nsteps},
+            "note": f"{form} downshifted step (side path, not in value), {nsteps} steps per launch; the parts of "
+                    "the rows are built once per call"}
 
 
 def adjoint_timing(E, torch, synth):
@@ -660,31 +688,41 @@ def roofline(res, form, n_p, n_t, n_e, sort_every, copy_gbs, traffic_path=None, 
     events on its launch stream), the attainable rate of its access pattern
     alone (stream probe) and of a device copy, and the whole step's
     algorithmic bytes over the measured time per step; with a VALU summary, the
-    same kernel against the vector-ALU issue ceiling (the binding one for the
-    compact mixed form)."""
+    same kernel against the vector-ALU issue ceiling (the binding one of a
+    launch of several steps, which reads and writes the state only once)."""
     r = res[form]
-    name = kernel_name(form, r["slices"])
-    bytes_launch = BYTES_PER_PARTICLE[form] * n_p + BYTES_PER_TET[form] * n_t + BYTES_PER_EDGE * n_e
-    ach = bytes_launch / (r["kernel_ms"] * 1e-3) / 1e9
+    per, sorts = r["steps_per_launch"], r["sorts_in_launch"]
+    name = kernel_name(form, r["slices"], per, sorts)
+    if per > 1:
+        bytes_launch = MULTI_BYTES_PER_PARTICLE[form] * n_p + MULTI_BYTES_PER_TET[form] * n_t
+        bytes_launch += ID_BYTES * n_p if sorts else 0
+        launch_ms = r["launch_ms"]
+    else:
+        bytes_launch = BYTES_PER_PARTICLE[form] * n_p + BYTES_PER_TET[form] * n_t + BYTES_PER_EDGE * n_e
+        launch_ms = r["kernel_ms"]
+    ach = bytes_launch / (launch_ms * 1e-3) / 1e9
     stream_gbs = BYTES_PER_PARTICLE[form] * n_p / (r["stream_ms"] * 1e-3) / 1e9
     traffic = None
     if traffic_path is not None:
         from paper_2208_12795_amd import rocprof_summary
         traffic = rocprof_summary.read_traffic(traffic_path, name)
-    step_bytes = STEP_BYTES_PER_PARTICLE[form] * n_p + STEP_BYTES_PER_TET * n_t
-    if sort_every:
+    step_bytes = (STEP_BYTES_PER_PARTICLE[form] * n_p + STEP_BYTES_PER_TET * n_t) / per
+    if sort_every and sorts and per > 1:
+        step_bytes += (ID_BYTES + 8) * n_p / sort_every
+    elif sort_every:
         step_bytes += SORT_BYTES_PER_PARTICLE[form] * n_p / sort_every
     step_gbs = step_bytes / (r["ms_per_step"] * 1e-3) / 1e9
     return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": name,
-            "bytes_per_launch": bytes_launch, "kernel_ms": round(r["kernel_ms"], 5),
+            "bytes_per_launch": bytes_launch, "kernel_ms": round(launch_ms, 5), "steps_per_launch": per,
             "stream_GBs": round(stream_gbs, 1), "frac_of_stream": round(ach / stream_gbs, 4),
             "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(ach / copy_gbs, 4),
-            "alu": alu_roofline(valu_path, name, r["kernel_ms"]),
+            "alu": alu_roofline(valu_path, name, launch_ms),
             "whole_step": {"bytes_per_step": int(step_bytes), "ms_per_step": round(r["ms_per_step"], 5),
                            "achieved": round(step_gbs, 1), "frac": round(step_gbs / HBM_PEAK_GBS, 4),
                            "note": "algorithmic bytes of the whole step (state %d B per particle, %d B per "
-                                   "tet, sort amortised) over the measured time per step"
+                                   "tet, both once per launch of steps_per_launch steps, sort amortised) over "
+                                   "the measured time per step"
                                    % (STEP_BYTES_PER_PARTICLE[form], STEP_BYTES_PER_TET)}}
 
 

@@ -92,9 +92,8 @@ constexpr int kTimingSets = 512;             // event sets of the step-timing po
 constexpr uint32_t kFlagFixed = 1u << 31;
 constexpr unsigned kWalkQueueCap = 1u << 23;  // entries of each walk queue; N_p <= 64 * kWalkQueueCap
 constexpr unsigned kQueueSkip = 0xffffffffu;  // particle-queue entry to skip
-// grid of the walk kernel (and the walk half of k_walk_coef): the walk is
-// bound by its dependent loads and atomics, not by lanes, and fewer blocks
-// leave the coefficient pass more of the chip and pay fewer end-of-walk fences
+// grid of the walk kernel: the walk is bound by its dependent loads and
+// atomics, not by lanes, and fewer blocks pay fewer end-of-walk fences
 constexpr unsigned kWalkBlocks = 64;
 // grid of k_walk_multi, whose lanes take their particle through the rest of a
 // launch's steps
@@ -4709,7 +4708,7 @@ struct etpic_ctx {
     // stop events of its kernels, interval k = 0 coefficient pass, 1 particle
     // kernel, 2 walk, 3 edge gather of the per-tet sums, each bound to its
     // kernel's dispatch (launch_timed); `has` marks the intervals launched
-    // (a coefficient pass that ran inside the previous walk launch has none),
+    // (a call of several steps has one coefficient pass),
     // `sorting` whether the particle kernel also sorted (k_push_sort).  The
     // sets are created with the context (a fixed pool of kTimingSets, the
     // vectors reserved so that pointers to sets stay valid);
