@@ -602,17 +602,21 @@ __device__ __forceinline__ int walker_tet(int marked) { return -marked - 2; }
 // q w * path integral of the six edge functions along one straight piece inside
 // a tet: with lam linear along the piece, int W1_ij . dr = m_i dl_j - m_j dl_i,
 // m = lam at the midpoint, dl the barycentric increment of the piece.
-__device__ __forceinline__ void deposit_piece(double *__restrict__ dG, const TetTopo &tp, const double l[4],
-                                              const double dl[4], double qw) {
+__device__ __forceinline__ void piece_sums(const double l[4], const double dl[4], double g6[6]) {
     double m[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) m[k] = l[k] + 0.5 * dl[k];
     const int le[6][2] = {{0, 1}, {0, 2}, {0, 3}, {1, 2}, {1, 3}, {2, 3}};
 #pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const int i = le[e][0], j = le[e][1];
-        unsafeAtomicAdd(&dG[tp.e[e]], qw * (m[i] * dl[j] - m[j] * dl[i]));
-    }
+    for (int e = 0; e < 6; ++e) g6[e] = m[le[e][0]] * dl[le[e][1]] - m[le[e][1]] * dl[le[e][0]];
+}
+
+__device__ __forceinline__ void deposit_piece(double *__restrict__ dG, const TetTopo &tp, const double l[4],
+                                              const double dl[4], double qw) {
+    double g6[6];
+    piece_sums(l, dl, g6);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) unsafeAtomicAdd(&dG[tp.e[e]], qw * g6[e]);
 }
 
 // lambda_0 = 1 - (l1 + l2 + l3) with the rounding error of the sum carried
@@ -685,12 +689,23 @@ __device__ __forceinline__ double lam_at(const double *arr, int64_t p, int fixed
 // issued: loads complete in order with them, and one behind six atomics would
 // wait for all six.  With `last` (lstart, dl) the piece in the final tet is not
 // deposited but returned, from where it starts.
+// `crossed` takes the pieces up to a face, onto the edges of their tet unless
+// the caller has a place for them.  Products and sums are fused where it says
+// fma and nowhere else that the path depends on: the end point must be the
+// same bits whatever is done with the pieces.
 struct LastPiece {
     double l[4], dl[4];
 };
-template <typename Real, bool kTrack, int kExtra = 0>
-__device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4], double d[3], Real v[3], double *R,
-                                   double (*ext)[3] = nullptr, bool fixed = false, LastPiece *last = nullptr) {
+struct ToEdges {
+    double *dG, qw;
+    __device__ __forceinline__ void operator()(int, const TetTopo &tp, const double l[4], const double dl[4]) const {
+        deposit_piece(dG, tp, l, dl, qw);
+    }
+};
+template <typename Real, bool kTrack, int kExtra = 0, typename Crossed>
+__device__ __forceinline__ int walk_pieces(const StepArgs<Real> &a, int T, double l[4], double d[3], Real v[3],
+                                           double *R, double (*ext)[3], bool fixed, LastPiece *last,
+                                           const Crossed &crossed) {
     int hops = 0;
     l[0] = lam0_of(l[1], l[2], l[3]);
     double g[4][3];
@@ -713,7 +728,7 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
     for (;;) {
         double dl[4];
 #pragma unroll
-        for (int k = 1; k < 4; ++k) dl[k] = g[k][0] * d[0] + g[k][1] * d[1] + g[k][2] * d[2];
+        for (int k = 1; k < 4; ++k) dl[k] = fma(g[k][2], d[2], fma(g[k][0], d[0], g[k][1] * d[1]));
         dl[0] = -(dl[1] + dl[2] + dl[3]);
         double smin = 1.0;
         int kmin = -1;
@@ -768,9 +783,13 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
             tp = a.topo[nb];
         }
         double dlp[4];
+        {
+            // (rounded: its sum with l below must not become an fma in one form of the walk only)
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) dlp[k] = smin * dl[k];
-        if (!kTrack) deposit_piece(a.dG, from, l, dlp, a.qw);
+            for (int k = 0; k < 4; ++k) dlp[k] = smin * dl[k];
+        }
+        if (!kTrack) crossed(T, from, l, dlp);
         double lc[4], sum = 0.0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -780,16 +799,16 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
 #pragma unroll
         for (int k = 0; k < 4; ++k) lc[k] /= sum;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) d[c] -= smin * d[c];
+        for (int c = 0; c < 3; ++c) d[c] = fma(-smin, d[c], d[c]);
         if (nb < 0) {
-            const double nn = sqrt(gx * gx + gy * gy + gz * gz);
+            const double nn = sqrt(fma(gz, gz, fma(gx, gx, gy * gy)));
             const double nh[3] = {gx / nn, gy / nn, gz / nn};
-            double dd = d[0] * nh[0] + d[1] * nh[1] + d[2] * nh[2];
-            Real vv = v[0] * (Real)nh[0] + v[1] * (Real)nh[1] + v[2] * (Real)nh[2];
+            double dd = fma(d[2], nh[2], fma(d[0], nh[0], d[1] * nh[1]));
+            Real vv = fma(v[2], (Real)nh[2], fma(v[0], (Real)nh[0], v[1] * (Real)nh[1]));
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                d[c] -= 2.0 * dd * nh[c];
-                v[c] -= (Real)2 * vv * (Real)nh[c];
+                d[c] = fma(-(2.0 * dd), nh[c], d[c]);
+                v[c] = fma(-((Real)2 * vv), (Real)nh[c], v[c]);
             }
 #pragma unroll
             for (int i = 0; i < kExtra; ++i) {
@@ -831,6 +850,12 @@ __device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4],
         }
     }
     return T;
+}
+
+template <typename Real, bool kTrack, int kExtra = 0>
+__device__ __forceinline__ int walk(const StepArgs<Real> &a, int T, double l[4], double d[3], Real v[3], double *R,
+                                   double (*ext)[3] = nullptr, bool fixed = false, LastPiece *last = nullptr) {
+    return walk_pieces<Real, kTrack, kExtra>(a, T, l, d, v, R, ext, fixed, last, ToEdges{a.dG, a.qw});
 }
 
 // The sums of a piece (l, dl) added to s (edge_sums), in units of 1 / one.
@@ -1722,7 +1747,7 @@ __device__ __forceinline__ bool queue_leavers(const StepArgs<Real> &a, unsigned 
     return fits;
 }
 
-// Takes the queued particles, one lane each (block b from part b % kShards),
+// Takes the queued particles, one lane each (block b a share of part b % kShards),
 // then those of the overflow slices, one wavefront per slice; after a scatter
 // launch whose leavers did not all fit, every marked particle, by a scan.
 template <typename Real, typename TakeOne>
@@ -1732,9 +1757,10 @@ __device__ __forceinline__ void take_leavers(const StepArgs<Real> &a, TakeOne ta
         for (int64_t p = (int64_t)blk * kBlock + threadIdx.x; p < a.n; p += (int64_t)nblk * kBlock) take_one(p);
         return;
     }
-    const unsigned shard = blk % kShards, per = nblk / kShards;
+    const unsigned shard = blk % kShards, per = nblk / kShards, part = blk / kShards;
     const unsigned count = min(__atomic_load_n(&a.walk_ctr[kShardAt + shard * kShardStride], __ATOMIC_RELAXED), kShardCap);
-    for (unsigned i = blk / kShards * kBlock + threadIdx.x; i < count; i += per * kBlock) {
+    const unsigned to = (unsigned)((uint64_t)count * (part + 1) / per);
+    for (unsigned i = (unsigned)((uint64_t)count * part / per) + threadIdx.x; i < to; i += kBlock) {
         const unsigned q = a.walk_queue[shard * kShardCap + i];
         if (q != kQueueSkip && (int64_t)q < a.n) take_one((int64_t)q);
     }
@@ -1983,11 +2009,76 @@ __global__ void __launch_bounds__(kBlock) k_push_multi(StepArgs<Real> a, MultiAr
     }
 }
 
+// Where a block of k_walk_multi adds up what its leavers leave in each tet
+// (six edge sums, four vertex sums) before it goes to memory: leavers of one
+// place cross the same few tets.  Open addressing by tet; what finds no place
+// within kTries steps goes to memory directly.  The walk was bound by these
+// float64 atomics, 16 or more per leaver: 1e8 particles in a bunch 1430 -> 780 us,
+// 1e7 float64 50 -> 37, 5e7 mixed 127 -> 111.
+struct LeaverSums {
+    static constexpr int kSlots = 512, kTries = 8, kSums = 10;
+    double sum[kSlots][kSums];
+    int tet[kSlots];
+
+    __device__ __forceinline__ int place(int T) {
+        int h = T & (kSlots - 1);
+        for (int tries = 0; tries < kTries; ++tries, h = (h + 1) & (kSlots - 1)) {
+            const int was = atomicCAS(&tet[h], -1, T);
+            if (was == -1 || was == T) return h;
+        }
+        return -1;
+    }
+    template <typename Real>
+    __device__ __forceinline__ void add_edges(const StepArgs<Real> &a, int T, const double g6[6]) {
+        const int h = place(T);
+        if (h >= 0) {
+#pragma unroll
+            for (int e = 0; e < 6; ++e) unsafeAtomicAdd(&sum[h][e], g6[e]);
+        } else {
+            double *slot = a.tetG + (int64_t)T * 8;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) unsafeAtomicAdd(&slot[e], a.qw * g6[e]);
+        }
+    }
+    template <typename Real>
+    __device__ __forceinline__ void add_charge(const StepArgs<Real> &a, int T, const double l[4]) {
+        const int h = place(T);
+        if (h >= 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&sum[h][6 + k], l[k]);
+        } else {
+            const TetTopo tp = a.topo[T];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&a.rho[tp.v[k]], a.qw * l[k]);
+        }
+    }
+    // by all threads of the block
+    __device__ __forceinline__ void clear() {
+        for (int i = threadIdx.x; i < kSlots; i += blockDim.x) tet[i] = -1;
+        for (int i = threadIdx.x; i < kSlots * kSums; i += blockDim.x) (&sum[0][0])[i] = 0.0;
+        __syncthreads();
+    }
+    template <typename Real>
+    __device__ __forceinline__ void flush(const StepArgs<Real> &a) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < kSlots * kSums; i += blockDim.x) {
+            const int h = i / kSums, k = i % kSums, T = tet[h];
+            const double x = sum[h][k];
+            if (T < 0 || x == 0.0) continue;
+            if (k < 6)
+                unsafeAtomicAdd(&a.tetG[(int64_t)T * 8 + k], a.qw * x);
+            else
+                unsafeAtomicAdd(&a.rho[a.topo[T].v[k - 6]], a.qw * x);
+        }
+    }
+};
+
 // A leaver of k_push_multi: its walk at the step it left in, then its
 // remaining steps, each as the particle kernel and the walk take it.  In-tet
 // pieces are summed per visit of a tet and added to the tet's current slots.
 template <typename Real, int kSnap, bool kFixed>
-__device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const MultiArgs<kSnap> &ma, int64_t p) {
+__device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const MultiArgs<kSnap> &ma, LeaverSums &sums,
+                                            int64_t p) {
     double *lam[3] = {a.lam1, a.lam2, a.lam3};
     uint32_t *fl[3] = {reinterpret_cast<uint32_t *>(a.lam1), reinterpret_cast<uint32_t *>(a.lam2),
                        reinterpret_cast<uint32_t *>(a.lam3)};
@@ -2009,12 +2100,9 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
         double g6[6];
         unscale_sums<kFixed>(s);
         edge_sums(s, g6);
-        double *slot = a.tetG + (int64_t)T * 8;
+        sums.add_edges(a, T, g6);
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            if (g6[e] != 0.0) unsafeAtomicAdd(&slot[e], a.qw * g6[e]);
-            s[e] = 0.0;
-        }
+        for (int e = 0; e < 6; ++e) s[e] = 0.0;
         some = false;
     };
     bool walks = true;
@@ -2028,7 +2116,12 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
 #pragma unroll
                 for (int k = 1; k < 4; ++k) l[k] *= kFix;
             LastPiece end;
-            T = walk<Real, false>(a, T, l, d, v, nullptr, nullptr, kFixed, &end);
+            T = walk_pieces<Real, false>(a, T, l, d, v, nullptr, nullptr, kFixed, &end,
+                                         [&](int t, const TetTopo &, const double l0[4], const double dl[4]) {
+                                             double g6[6];
+                                             piece_sums(l0, dl, g6);
+                                             sums.add_edges(a, t, g6);
+                                         });
             add_piece(end, kOne<kFixed>, s);
             some = true;
             if (kFixed) {
@@ -2071,10 +2164,8 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
     a.v1[p] = v[1];
     a.v2[p] = v[2];
     if (a.rho) {
-        const TetTopo tp = a.topo[T];
         l[0] = 1.0 - l[1] - l[2] - l[3];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&a.rho[tp.v[k]], a.qw * l[k]);
+        sums.add_charge(a, T, l);
     }
 }
 
@@ -2083,8 +2174,11 @@ __device__ __forceinline__ void walk_leaver(const StepArgs<Real> &a, const Multi
 // one for the next pair, so no block waits for the last one to reset them.
 template <typename Real, int kSnap, bool kFixed>
 __global__ void __launch_bounds__(kBlock) k_walk_multi(StepArgs<Real> a, MultiArgs<kSnap> ma, unsigned *next_ctr) {
+    __shared__ LeaverSums sums;
     if (blockIdx.x == 0) clear_counters(next_ctr);
-    take_leavers(a, [&](int64_t p) { walk_leaver<Real, kSnap, kFixed>(a, ma, p); });
+    sums.clear();
+    take_leavers(a, [&](int64_t p) { walk_leaver<Real, kSnap, kFixed>(a, ma, sums, p); });
+    sums.flush(a);
 }
 
 // ------------------------------------------------------------------ downshifted step
@@ -5026,6 +5120,15 @@ struct etpic_ctx {
                                                            (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
     }
 
+    // Blocks of k_walk_multi.  Few particles: as many as the queue has parts (an
+    // empty block costs its table's clearing; 1,000 electrons 5.4 us with 512).
+    // More blocks take a long queue's leavers sooner and pay for it with more
+    // tables: 5e7 particles 111 us with 512, 130 with 1024; 1e8 in a bunch 1075 and
+    // 780.
+    static unsigned leaver_blocks(int64_t n) {
+        return n <= kFewParticles ? kShards : n < ((int64_t)1 << 26) ? kLeaverBlocks : 2 * kLeaverBlocks;
+    }
+
     // the parts of the 10-real rows, from which multi-step launches form the
     // row of each of their steps
     template <int kSnap>
@@ -5108,7 +5211,7 @@ struct etpic_ctx {
                 launch_timed(k_push_multi<Real, kSnap, false, false, kFixed>, push_grid, st, e0, e1, a, ma, remap);
             }
             HIP_TRY(hipGetLastError());
-            launch_timed(k_walk_multi<Real, kSnap, kFixed>, kLeaverBlocks, st, ev_start(ta, 2), ev_stop(ta, 2), a, ma,
+            launch_timed(k_walk_multi<Real, kSnap, kFixed>, leaver_blocks(n), st, ev_start(ta, 2), ev_stop(ta, 2), a, ma,
                          next);
             HIP_TRY(hipGetLastError());
             j0 = j1;
