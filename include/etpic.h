@@ -103,7 +103,8 @@ enum etpic_precision {
 
 /* bits of the device status word read by etpic_check */
 enum etpic_device_flags {
-    ETPIC_DEV_HOPCAP = 1u, /* walk hop cap reached (particle left where it stopped) */
+    ETPIC_DEV_HOPCAP = 1u, /* walk hop cap reached (particle left where it stopped), or a
+                              particle of the reverse sweep found no place in its queue */
     ETPIC_DEV_NAN = 2u,    /* non-finite field or velocity */
     ETPIC_DEV_BADTET = 4u  /* tet index outside [0, N_t) */
 };

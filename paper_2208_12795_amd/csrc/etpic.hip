@@ -2988,7 +2988,9 @@ __global__ void __launch_bounds__(64) k_adjoint(StepArgs<double> a, AdjArgs b) {
     // a launch takes at most kWalkQueueCap particles, and a part of the queue
     // belongs to at most kShardCap of them: the queue holds them all
     const unsigned long long wmask = __ballot(left);
-    if (wmask) queue_leavers(a, wmask, left, (unsigned)p, true, blk);
+    static_assert(kWalkQueueCap / 64 % (kShards * kShardRun) == 0, "the launch's blocks share the parts evenly");
+    if (wmask && !queue_leavers(a, wmask, left, (unsigned)p, true, blk) && ln == 0)
+        atomicOr(a.status, (unsigned)ETPIC_DEV_HOPCAP);
 }
 
 // The same for the queued particles, one lane each: forward through their
@@ -6146,7 +6148,11 @@ int etpic_backward(etpic_ctx *ctx, int64_t n, const etpic_species *sp, const etp
         const double w1[3] = {1.0, 0.0, 0.0};
         if (int r = ctx->launch_parts<1>(snap, w1, st, nullptr)) return r;
     }
+    // both counter sets of the sweep, all parts of each: a launch's leavers
+    // kernel clears the other set only
     unsigned *const ctr = ctx->d_walk_ctr + 3 * kCtrStride;
+    k_fill_u32<<<grid_for(2 * kCtrStride), kBlock, 0, st>>>(ctr, 2 * kCtrStride, 0u);
+    HIP_TRY(hipGetLastError());
     unsigned flip = 0;
     for (int seg = L.ncp - 1; seg >= 0; --seg) {
         // the segment in pieces of at most kMaxAdj steps: the states its later
@@ -6202,8 +6208,6 @@ int etpic_backward(etpic_ctx *ctx, int64_t n, const etpic_species *sp, const etp
             }
         }
     }
-    k_fill_u32<<<1, kBlock, 0, st>>>(ctr, 2 * kCtrStride, 0u);
-    HIP_TRY(hipGetLastError());
     return ETPIC_OK;
 }
 

@@ -196,3 +196,29 @@ def test_reverse_in_pieces_matches_every_step_checkpoints(E, torch_cuda, n, nste
 @pytest.mark.parametrize("n,nsteps", [(65, 32), (65, 65), (32768, 17), (32769, 17)])
 def test_steps_per_launch(E, torch_cuda, n, nsteps):
     test_multi_equals_single_steps(E, torch_cuda, n, False, nsteps, 300.0, False, 0)
+
+
+# 1 and 3 reverse launches per sweep; more particles than the first parts of the leavers' queue take
+@pytest.mark.parametrize("n,nsteps,every", [(40_001, 5, 5), (40_001, 11, 11), (40_001, 4, 5)])
+def test_reverse_sweeps_in_a_row_start_from_empty_queues(E, torch_cuda, n, nsteps, every):
+    """Sweeps with an odd number of launches on one context, one after the
+    other, against a context that has made none: the same derivatives to the
+    rounding of the sums (1e-13 of the largest, as above)."""
+    torch = torch_cuda
+
+    def sweeps(many):
+        w, ctx, f, sp, p = problem(E, torch, n, 0, True)
+        p.vel *= 30.0
+        start = p.tet.clone()
+        ws = torch.empty(ctx.adjoint_workspace_bytes(n, nsteps, every), dtype=torch.uint8, device="cuda")
+        ctx.forward_checkpointed(p, sp, f, 3, nsteps, 1e-9, w.omega, every, ws)
+        assert (p.tet != start).double().mean().item() > 0.01
+        for _ in range(many):
+            vbar, xbar = p.vel.clone(), torch.zeros_like(p.vel)
+            g = torch.zeros((ctx.n_edge, 2), dtype=torch.float64, device="cuda")
+            ctx.backward(n, sp, f, 3, nsteps, 1e-9, w.omega, every, ws, vbar, xbar, g)
+        ctx.check()
+        ctx.close()
+        return vbar, xbar, g
+    for got, want in zip(sweeps(3), sweeps(1)):
+        assert torch.allclose(got, want, rtol=0, atol=1e-13 * want.abs().max().item())
