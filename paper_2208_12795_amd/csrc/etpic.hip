@@ -4835,6 +4835,15 @@ struct etpic_ctx {
         *ts = &timing.back();
         return ETPIC_OK;
     }
+    // A timed call that needs more sets than are left is refused before its
+    // first launch: one that stopped between two launches would leave leavers
+    // queued and currents in the tets' slots for the next call to find.
+    int timing_room(uint32_t flags, int sets) const {
+        if ((flags & (ETPIC_STEP_TIMING | ETPIC_STEP_TIMING_ALL)) && (size_t)sets > spare.size())
+            return fail(ETPIC_EINVAL, "step timing: %d event sets needed, %zu of %d left (etpic_kernel_time returns them)",
+                        sets, spare.size(), kTimingSets);
+        return ETPIC_OK;
+    }
     // start / stop event of interval k of a timing set (none without a set)
     static hipEvent_t ev_start(TimingSet *ts, int k) {
         if (!ts) return nullptr;
@@ -5055,12 +5064,14 @@ struct etpic_ctx {
                   double omega, double *dG, double *rho, uint32_t flags, void *stream,
                   const etpic_particles *src = nullptr) {
         hipStream_t st = static_cast<hipStream_t>(stream);
-        if (src)
-            if (int r = sort_count(src, st)) return r;
         constexpr uint32_t kForced =
             ETPIC_STEP_SLICES_1 | ETPIC_STEP_SLICES_2 | ETPIC_STEP_SLICES_4 | ETPIC_STEP_SLICES_16;
         const int most = most_fused(p->n);
-        if (nsteps == 1 || most < 2 || (flags & kForced))
+        const bool single = nsteps == 1 || most < 2 || (flags & kForced);
+        if (int r = timing_room(flags, single ? nsteps : (nsteps + most - 1) / most)) return r;
+        if (src)
+            if (int r = sort_count(src, st)) return r;
+        if (single)
             return single_steps<Real>(p, sp, plans, nsteps, dt, omega, dG, rho, flags, st, src);
         if constexpr (std::is_same<Real, float>::value) {
             if (flags & kFlagFixed)
@@ -5293,6 +5304,8 @@ struct etpic_ctx {
         const double w1[3] = {1.0, 0.0, 0.0};
         TimingSet *ta = nullptr;
         unsigned *ctr = nullptr;
+        const int alone = std::min(nsteps, std::max(0, 3 - hist0));   // launches of the first three steps
+        if (int r = timing_room(flags, alone + (nsteps - alone + most - 1) / most)) return r;
         for (int j0 = 0, i = 0; j0 < nsteps; ++i) {
             const int H = hist0 + j0;
             const int left = nsteps - j0, launches = (left + most - 1) / most;

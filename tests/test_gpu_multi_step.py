@@ -222,3 +222,43 @@ def test_reverse_sweeps_in_a_row_start_from_empty_queues(E, torch_cuda, n, nstep
         return vbar, xbar, g
     for got, want in zip(sweeps(3), sweeps(1)):
         assert torch.allclose(got, want, rtol=0, atol=1e-13 * want.abs().max().item())
+
+
+@pytest.mark.parametrize("downshifted", [False, True])
+def test_timed_call_without_room_for_its_events_changes_nothing(E, torch_cuda, downshifted):
+    """All but one of the 512 event sets taken: a timed call of two launches is
+    refused before the first of them, and the call after it finds nothing
+    queued or half deposited."""
+    torch = torch_cuda
+    n, nsteps, dt_scale = 1000, 33, 100.0
+    w, ctx, f, sp, p = problem(E, torch, n, 0, False)
+    dt, timed = w.dt * dt_scale, E.STEP_XCD_REMAP | E.STEP_TIMING
+    g = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    q = p.clone()
+    for j in range(511):
+        ctx.gather_push_deposit(q, sp, f, j, w.dt, w.omega, g, flags=timed)
+    hist = ctx.ds_history(p) if downshifted else None
+
+    def call(ctx, p, hist, g, flags):
+        if downshifted:
+            ctx.ds_steps(p, hist, sp, f, 5, nsteps, 0, 1e-2 * dt, w.omega, g, flags=flags)
+        else:
+            ctx.run_steps(p, sp, f, 5, nsteps, dt, w.omega, g, flags=flags)
+    g.zero_()
+    before = p.clone()
+    with pytest.raises(E.EtpicError) as ei:
+        call(ctx, p, hist, g, timed)
+    assert ei.value.code == E.EINVAL
+    same_state(p.to_numpy(), before.to_numpy())
+    assert torch.count_nonzero(g).item() == 0
+    assert ctx.kernel_time()[1] == 511
+    call(ctx, p, hist, g, timed)
+    ctx.check()
+    _, fresh, _, _, q = problem(E, torch, n, 0, False)
+    g2 = torch.zeros_like(g)
+    call(fresh, q, fresh.ds_history(q) if downshifted else None, g2, E.STEP_XCD_REMAP)
+    fresh.check()
+    same_state(p.to_numpy(), q.to_numpy())
+    assert torch.allclose(g, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    ctx.close()
+    fresh.close()
