@@ -379,6 +379,18 @@ __device__ __forceinline__ void half_row(int face, const double z[6], const doub
     }
 }
 
+// Clears the current slots of tets [T0, T0 + nloc) (by one block; null: none).
+// A call clears the slots it is about to use in its first kernel, the
+// coefficient pass, whose stores these join: so a call recorded into a graph
+// may be replayed, and one that stopped short leaves nothing for the next.
+// (Each slot cleared by the edge that read it: 8-byte stores out of order,
+// 35 instead of 19 us on 384,000 tets; a fill of its own: one launch more.)
+__device__ __forceinline__ void clear_slots(double *slots, int64_t T0, int nloc) {
+    if (!slots) return;
+    double2 *dst = reinterpret_cast<double2 *>(slots + T0 * 8);
+    for (int i = threadIdx.x; i < nloc * 4; i += blockDim.x) dst[i] = make_double2(0.0, 0.0);
+}
+
 // What a coefficient pass writes per tet: the particle step's 10 reals of one
 // step (CoefRow), or the parts of the 10-real row (kRowParts * 10 float64)
 // from which a multi-step launch forms the row of each of its steps.
@@ -387,7 +399,7 @@ enum CoefMode { kCoefStep, kCoefParts };
 template <typename Real, int kSnap, int kMode>
 __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ prow,
                                          const int32_t *__restrict__ tetface, const FieldPtrs &F,
-                                         Real *__restrict__ coef, unsigned blk) {
+                                         Real *__restrict__ coef, double *__restrict__ slots, unsigned blk) {
     // A block covers kTets tets.  Their push rows and face ids are staged in
     // LDS with coalesced 16-byte loads; then the block's first kTets lanes
     // take the edges and the other kTets lanes the faces, so each wavefront
@@ -541,13 +553,15 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
             put(kParts - 1, o);
         }
     }
+    clear_slots(slots, T0, nloc);
 }
 
 template <typename Real, int kSnap, int kMode>
 __global__ void __launch_bounds__(kBlock) k_tet_coef(int64_t nt, const double *__restrict__ prow,
                                                      const int32_t *__restrict__ tetface, FieldPtrs F,
-                                                     Real *__restrict__ coef) {
-    tet_coef<Real, kSnap, kMode>(nt, prow, tetface, F, coef, F.xcd ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x);
+                                                     Real *__restrict__ coef, double *__restrict__ slots) {
+    tet_coef<Real, kSnap, kMode>(nt, prow, tetface, F, coef, slots,
+                                 F.xcd ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x);
 }
 
 // ------------------------------------------------------------------ particle step
@@ -944,13 +958,12 @@ __device__ __forceinline__ void flush_runs_together(const StepArgs<Real> &a, int
 
 // The per-tet current slots of a multi-step call added to the edges: dG[e] +=
 // the slots that name edge e, in the fixed order of the edge's CSR (no atomics:
-// every particle and walk kernel of the call has finished).  The same launch
-// clears the other slot buffer, which the next call accumulates into, and the
-// walk counters `ctr` of the call's last multi-step launch (null: none).
+// every particle and walk kernel of the call has finished).  The slots stay as
+// they are: the next call's first kernel clears them (clear_slots).  Also
+// clears the walk counters `ctr` of the call's last multi-step launch (null: none).
 __global__ void __launch_bounds__(kBlock) k_slots_to_edges(int64_t ne, const int32_t *__restrict__ ptr,
                                                            const int32_t *__restrict__ slot,
                                                            const double *__restrict__ tetG, double *__restrict__ dG,
-                                                           double *__restrict__ clear, int64_t nclear,
                                                            unsigned *__restrict__ ctr) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < ne; e += stride) {
@@ -972,7 +985,6 @@ __global__ void __launch_bounds__(kBlock) k_slots_to_edges(int64_t ne, const int
         }
         if (s != 0.0) dG[e] = old + s;
     }
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nclear; i += stride) clear[i] = 0.0;
     if (ctr && blockIdx.x == 0)
         for (unsigned i = threadIdx.x; i < kCtrStride; i += blockDim.x) ctr[i] = 0u;
 }
@@ -2200,9 +2212,13 @@ constexpr int kEnvRow = 72;
 
 __global__ void __launch_bounds__(kBlock) k_tet_coef_env(int64_t nt, const double *__restrict__ prow,
                                                          const int32_t *__restrict__ tetface, FieldPtrs F,
-                                                         double *__restrict__ out) {
+                                                         double *__restrict__ out, double *__restrict__ slots) {
     // blockIdx.y: 0..2 the edge rows (Re, Im, dc), 3..5 the face rows
     const int part = blockIdx.y;
+    if (part == 0) {
+        const int64_t T0 = (int64_t)blockIdx.x * kBlock;
+        clear_slots(slots, T0, (int)min((int64_t)kBlock, nt - T0));
+    }
     const int64_t T = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (T >= nt) return;
     const double *row = prow + T * PushRow<double>::kStride;
@@ -4772,8 +4788,7 @@ struct etpic_ctx {
     int32_t *d_v2e_code = nullptr;
     int32_t *d_e2s_ptr = nullptr;    // edge -> tet-slot CSR (ne+1)
     int32_t *d_e2s_slot = nullptr;   // its slots, 8 * tet + local edge (6 nt)
-    double *d_tetG[2] = {nullptr, nullptr};  // per-tet current slots (nt*8 each), alternate per call
-    int tetG_cur = 0;
+    double *d_tetG = nullptr;        // per-tet current slots (nt*8), cleared by a call's first kernel
     double *d_xyz = nullptr;         // 3*nv vertex coordinates
     int32_t *d_grid = nullptr;       // start tets of the point-location grid
     GridArgs grid{};
@@ -4896,16 +4911,18 @@ struct etpic_ctx {
     int coef_xcd() const { return (16 * host.ne + 24 * host.nf) / 8 <= (int64_t)4 << 20 ? 1 : 0; }
 
     template <typename Real>
-    int launch_coef(const StepPlan &plan, double omega, hipStream_t s, TimingSet *ts = nullptr) {
+    int launch_coef(const StepPlan &plan, double omega, double *slots, hipStream_t s, TimingSet *ts = nullptr) {
         const int64_t nt = host.nt;
         FieldPtrs F = field_ptrs(plan.snap, plan.w, std::cos(omega * plan.t), std::sin(omega * plan.t));
         F.xcd = coef_xcd();
         hipEvent_t e0 = ev_start(ts, 0), e1 = ev_stop(ts, 0);
         Real *coef = static_cast<Real *>(d_coef);
         if (plan.snap[1])
-            launch_timed(k_tet_coef<Real, 3, kCoefStep>, grid_for(2 * nt), s, e0, e1, nt, d_gpush64, d_tetface, F, coef);
+            launch_timed(k_tet_coef<Real, 3, kCoefStep>, grid_for(2 * nt), s, e0, e1, nt, d_gpush64, d_tetface, F, coef,
+                         slots);
         else
-            launch_timed(k_tet_coef<Real, 1, kCoefStep>, grid_for(2 * nt), s, e0, e1, nt, d_gpush64, d_tetface, F, coef);
+            launch_timed(k_tet_coef<Real, 1, kCoefStep>, grid_for(2 * nt), s, e0, e1, nt, d_gpush64, d_tetface, F, coef,
+                         slots);
         HIP_TRY(hipGetLastError());
         return ETPIC_OK;
     }
@@ -5037,15 +5054,12 @@ struct etpic_ctx {
         a.cursor = d_count;
     }
 
-    // The call's per-tet sums onto the edges; the other slot buffer is cleared
-    // for the next call.
+    // The call's per-tet sums onto the edges.
     int launch_edges(double *dG, hipStream_t st, TimingSet *ta, unsigned *ctr) {
-        const int64_t ne = host.ne, nt = host.nt;
-        const unsigned gb = (unsigned)std::min<int64_t>(grid_for(std::max<int64_t>(ne, 8 * nt)), 4096);
-        launch_timed(k_slots_to_edges, gb, st, ev_start(ta, 3), ev_stop(ta, 3), ne, d_e2s_ptr, d_e2s_slot,
-                     d_tetG[tetG_cur], dG, d_tetG[tetG_cur ^ 1], 8 * nt, ctr);
+        const int64_t ne = host.ne;
+        const unsigned gb = (unsigned)std::min<int64_t>(grid_for(ne), 4096);
+        launch_timed(k_slots_to_edges, gb, st, ev_start(ta, 3), ev_stop(ta, 3), ne, d_e2s_ptr, d_e2s_slot, d_tetG, dG, ctr);
         HIP_TRY(hipGetLastError());
-        tetG_cur ^= 1;
         return ETPIC_OK;
     }
 
@@ -5100,11 +5114,11 @@ struct etpic_ctx {
             if (flags & (ETPIC_STEP_TIMING | ETPIC_STEP_TIMING_ALL))
                 if (int r = timing_events(&ts, sorts)) return r;
             ta = time_all ? ts : nullptr;
-            if (int r = launch_coef<Real>(plans[j], omega, st, ta)) return r;
+            if (int r = launch_coef<Real>(plans[j], omega, j == 0 ? d_tetG : nullptr, st, ta)) return r;
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j == nsteps - 1 ? rho : nullptr);
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
             a.fixed = (flags & kFlagFixed) ? 1 : 0;
-            a.tetG = d_tetG[tetG_cur];
+            a.tetG = d_tetG;
             if (sorts) {
                 // read src, write p at the sorted positions; the walk then runs on p
                 StepArgs<Real> as = a;
@@ -5149,7 +5163,7 @@ struct etpic_ctx {
         FieldPtrs F = field_ptrs(snap, w, 1.0, 0.0);
         F.xcd = coef_xcd();
         launch_timed(k_tet_coef<double, kSnap, kCoefParts>, grid_for(2 * host.nt), st, ev_start(ta, 0), ev_stop(ta, 0),
-                     host.nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef));
+                     host.nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef), d_tetG);
         HIP_TRY(hipGetLastError());
         return ETPIC_OK;
     }
@@ -5185,8 +5199,12 @@ struct etpic_ctx {
                 ts->steps = j1 - j0;
             }
             ta = time_all ? ts : nullptr;
-            if (i == 0 && !parts_ready)
+            if (i == 0 && parts_ready) {
+                k_fill_u32<<<grid_for(16 * nt), kBlock, 0, st>>>(reinterpret_cast<unsigned *>(d_tetG), 16 * nt, 0u);
+                HIP_TRY(hipGetLastError());
+            } else if (i == 0) {
                 if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, st, ta)) return r;
+            }
             MultiArgs<kSnap> ma{};
             ma.parts = static_cast<const double *>(d_coef);
             ma.nsteps = j1 - j0;
@@ -5201,7 +5219,7 @@ struct etpic_ctx {
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j1 == nsteps ? rho : nullptr);
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
             a.fixed = kFixed ? 1 : 0;
-            a.tetG = d_tetG[tetG_cur];
+            a.tetG = d_tetG;
             ctr = d_walk_ctr + (1 + (i & 1)) * kCtrStride;
             unsigned *next = d_walk_ctr + (1 + ((i + 1) & 1)) * kCtrStride;
             a.walk_ctr = ctr;
@@ -5321,13 +5339,13 @@ struct etpic_ctx {
                     if (int r = launch_parts<1>(snap, w1, st, ta)) return r;
                 } else {
                     launch_timed(k_tet_coef_env, dim3(grid_for(nt), 6), st, ev_start(ta, 0), ev_stop(ta, 0), nt,
-                                 d_gpush64, d_tetface, field_ptrs(snap, w1, 1.0, 0.0), d_coef_env);
+                                 d_gpush64, d_tetface, field_ptrs(snap, w1, 1.0, 0.0), d_coef_env, d_tetG);
                     HIP_TRY(hipGetLastError());
                 }
             }
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j0 + len == nsteps ? rho : nullptr);
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
-            a.tetG = d_tetG[tetG_cur];
+            a.tetG = d_tetG;
             ctr = d_walk_ctr + (1 + (i & 1)) * kCtrStride;
             unsigned *next = d_walk_ctr + (1 + ((i + 1) & 1)) * kCtrStride;
             a.walk_ctr = ctr;
@@ -5452,8 +5470,7 @@ struct etpic_ctx {
         d_coef_env = nullptr;
         d_v2e_ptr = d_v2e_code = nullptr;
         d_e2s_ptr = d_e2s_slot = nullptr;
-        d_tetG[0] = d_tetG[1] = nullptr;
-        tetG_cur = 0;
+        d_tetG = nullptr;
         d_xyz = nullptr;
         d_grid = nullptr;
         grid = GridArgs{};
@@ -5707,7 +5724,7 @@ struct MeshPtrs {
     int32_t *grid, *v2e_ptr, *v2e_code;
     unsigned *count, *tilesum;
     int32_t *e2s_ptr, *e2s_slot;
-    double *tetG[2];
+    double *tetG;
 };
 MeshPtrs mesh_layout(Carve &cv, const etpic::HostMesh &M, size_t grid_cells) {
     const int64_t nt = M.nt;
@@ -5728,8 +5745,7 @@ MeshPtrs mesh_layout(Carve &cv, const etpic::HostMesh &M, size_t grid_cells) {
     m.tilesum = cv.take<unsigned>((nt + 1 + kScanTile - 1) / kScanTile);
     m.e2s_ptr = cv.take<int32_t>(M.ne + 1);
     m.e2s_slot = cv.take<int32_t>(6 * nt);
-    m.tetG[0] = cv.take<double>(8 * nt);
-    m.tetG[1] = cv.take<double>(8 * nt);
+    m.tetG = cv.take<double>(8 * nt);
     return m;
 }
 
@@ -5835,9 +5851,7 @@ int etpic_mesh_upload(etpic_ctx *ctx, int64_t n_vert, const double *xyz_host, in
     ctx->tiles = (nt + 1 + kScanTile - 1) / kScanTile;
     ctx->d_e2s_ptr = m.e2s_ptr;
     ctx->d_e2s_slot = m.e2s_slot;
-    ctx->d_tetG[0] = m.tetG[0];
-    ctx->d_tetG[1] = m.tetG[1];
-    ctx->tetG_cur = 0;
+    ctx->d_tetG = m.tetG;
     {
         constexpr int s64 = PushRow<double>::kStride, s32 = PushRow<float>::kStride;
         std::vector<double> gp64((size_t)nt * s64, 0.0);
@@ -5885,8 +5899,7 @@ int etpic_mesh_upload(etpic_ctx *ctx, int64_t n_vert, const double *xyz_host, in
     HIP_TRY(hipMemcpy(ctx->d_v2e_code, M.v2e_code.data(), sizeof(int32_t) * 2 * M.ne, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->d_e2s_ptr, M.e2s_ptr.data(), sizeof(int32_t) * (M.ne + 1), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->d_e2s_slot, M.e2s_slot.data(), sizeof(int32_t) * 6 * nt, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemset(ctx->d_tetG[0], 0, sizeof(double) * 8 * nt));
-    HIP_TRY(hipMemset(ctx->d_tetG[1], 0, sizeof(double) * 8 * nt));
+    HIP_TRY(hipMemset(ctx->d_tetG, 0, sizeof(double) * 8 * nt));
     HIP_TRY(hipDeviceSynchronize());
     ctx->host = std::move(M);
     ctx->has_mesh = true;
