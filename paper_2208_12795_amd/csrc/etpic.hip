@@ -195,6 +195,7 @@ struct FieldPtrs {
     const double *b_dc;
     double w[3];   // snapshot weights (kSnap = 3)
     double c, s;   // cos(w t), sin(w t) of the fine step's time
+    double w2[3], c2, s2;   // the same of the second step (kCoefPair)
     int xcd;       // coefficient pass: one contiguous tet range per XCD
 };
 
@@ -392,9 +393,12 @@ __device__ __forceinline__ void clear_slots(double *slots, int64_t T0, int nloc)
 }
 
 // What a coefficient pass writes per tet: the particle step's 10 reals of one
-// step (CoefRow), or the parts of the 10-real row (kRowParts * 10 float64)
-// from which a multi-step launch forms the row of each of its steps.
-enum CoefMode { kCoefStep, kCoefParts };
+// step (CoefRow), the parts of the 10-real row (kRowParts * 10 float64) from
+// which a multi-step launch forms the row of each of its steps, or the float64
+// rows of two steps and a third of zeros, which a launch reads as the parts of
+// one snapshot: re alone (weights 1, 0) is the first step's row, im alone
+// (weights 0, -1) the second's.
+enum CoefMode { kCoefStep, kCoefParts, kCoefPair };
 
 template <typename Real, int kSnap, int kMode>
 __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ prow,
@@ -522,6 +526,7 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
                 dst[i] = c < kRowReals ? sout[tt * kOut + c] : (Real)0;
             }
         } else {
+            constexpr int kOuts = kMode == kCoefPair ? 3 : kParts;   // tens of reals per tet
             double *sout = lds;
             auto put = [&](int q, const double o[6]) {
                 __syncthreads();   // the staged rows or the previous part read
@@ -535,22 +540,47 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
                     }
                 }
                 __syncthreads();
-                double *dst = coef + T0 * (kParts * kRowReals) + q * kRowReals;
+                double *dst = coef + T0 * (kOuts * kRowReals) + q * kRowReals;
                 for (int i = threadIdx.x; i < nloc * kRowReals; i += kBlock) {
                     const int tt = i / kRowReals, c = i - tt * kRowReals;
-                    dst[(int64_t)tt * (kParts * kRowReals) + c] = sout[tt * kOut + c];
+                    dst[(int64_t)tt * (kOuts * kRowReals) + c] = sout[tt * kOut + c];
                 }
             };
+            if constexpr (kMode == kCoefPair) {
+                double o[6], o2[6];
+                const double none[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                if (act) {
+                    dc_part(o);
 #pragma unroll
-            for (int k = 0; k < kSnap; ++k) {
-                double re[6], im[6];
-                if (act) env_parts(k, re, im);
-                put(2 * k, re);
-                put(2 * k + 1, im);
+                    for (int d = 0; d < 6; ++d) o2[d] = o[d];
+#pragma unroll
+                    for (int k = 0; k < kSnap; ++k) {   // as row_entry
+                        double re[6], im[6];
+                        env_parts(k, re, im);
+                        const double wc = F.w[k] * F.c, ws = F.w[k] * F.s;
+                        const double wc2 = F.w2[k] * F.c2, ws2 = F.w2[k] * F.s2;
+#pragma unroll
+                        for (int d = 0; d < 6; ++d) {
+                            o[d] = fma(re[d], wc, fma(-im[d], ws, o[d]));
+                            o2[d] = fma(re[d], wc2, fma(-im[d], ws2, o2[d]));
+                        }
+                    }
+                }
+                put(0, o);
+                put(1, o2);
+                put(2, none);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kSnap; ++k) {
+                    double re[6], im[6];
+                    if (act) env_parts(k, re, im);
+                    put(2 * k, re);
+                    put(2 * k + 1, im);
+                }
+                double o[6];
+                if (act) dc_part(o);
+                put(kParts - 1, o);
             }
-            double o[6];
-            if (act) dc_part(o);
-            put(kParts - 1, o);
         }
     }
     clear_slots(slots, T0, nloc);
@@ -5080,7 +5110,8 @@ struct etpic_ctx {
         hipStream_t st = static_cast<hipStream_t>(stream);
         constexpr uint32_t kForced =
             ETPIC_STEP_SLICES_1 | ETPIC_STEP_SLICES_2 | ETPIC_STEP_SLICES_4 | ETPIC_STEP_SLICES_16;
-        const int most = most_fused(p->n);
+        const bool pairs = in_pairs(plans[0], nsteps, p->n);
+        const int most = std::min(pairs ? 2 : kMaxFused, most_fused(p->n));
         const bool single = nsteps == 1 || most < 2 || (flags & kForced);
         if (int r = timing_room(flags, single ? nsteps : (nsteps + most - 1) / most)) return r;
         if (src)
@@ -5089,11 +5120,11 @@ struct etpic_ctx {
             return single_steps<Real>(p, sp, plans, nsteps, dt, omega, dG, rho, flags, st, src);
         if constexpr (std::is_same<Real, float>::value) {
             if (flags & kFlagFixed)
-                return plans[0].snap[1]
+                return plans[0].snap[1] && !pairs
                            ? fused_steps<float, 3, true>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src)
                            : fused_steps<float, 1, true>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src);
         }
-        return plans[0].snap[1]
+        return plans[0].snap[1] && !pairs
                    ? fused_steps<Real, 3, false>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src)
                    : fused_steps<Real, 1, false>(p, sp, plans, nsteps, most, dt, omega, dG, rho, flags, st, src);
     }
@@ -5147,6 +5178,17 @@ struct etpic_ctx {
                                                            (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
     }
 
+    // Steps over three snapshots that go two to a launch, from the two steps'
+    // own rows (kCoefPair, 240 B per tet) instead of the parts of three
+    // snapshots (560 B per tet, which the particle kernel stages too).
+    // On 384,000 tets, mixed, one step per launch / parts / pairs: two steps of
+    // 2e5 particles 217 / 228 / 159 us, of 1e7 603 / 576 / 440; three steps of
+    // 1,000 156 / 174 / 146, but of 2e5 294 / 229 us by one launch already, as
+    // are all on few tets (750: 72 / 43), where the launches count.
+    bool in_pairs(const StepPlan &first, int nsteps, int64_t n) const {
+        return first.snap[1] && (nsteps == 2 || (nsteps == 3 && n <= kFewParticles && host.nt >= 65536));
+    }
+
     // Blocks of k_walk_multi.  Few particles: as many as the queue has parts (an
     // empty block costs its table's clearing; 1,000 electrons 5.4 us with 512).
     // More blocks take a long queue's leavers sooner and pay for it with more
@@ -5168,10 +5210,26 @@ struct etpic_ctx {
         return ETPIC_OK;
     }
 
+    // the rows of two steps (b null: of one), for a launch of them
+    int launch_pair(const StepPlan &a, const StepPlan *b, double omega, double *slots, hipStream_t st, TimingSet *ta) {
+        FieldPtrs F = field_ptrs(a.snap, a.w, std::cos(omega * a.t), std::sin(omega * a.t));
+        F.xcd = coef_xcd();
+        if (b) {
+            for (int k = 0; k < 3; ++k) F.w2[k] = b->w[k];
+            F.c2 = std::cos(omega * b->t);
+            F.s2 = std::sin(omega * b->t);
+        }
+        launch_timed(k_tet_coef<double, 3, kCoefPair>, grid_for(2 * host.nt), st, ev_start(ta, 0), ev_stop(ta, 0),
+                     host.nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef), slots);
+        HIP_TRY(hipGetLastError());
+        return ETPIC_OK;
+    }
+
     // Multi-step launches of p.  With src, the first launch reads src and
     // writes p: at the tet-sorted places (sorted), or place for place.
     // parts_ready: the rows' parts are there from an earlier call with the
-    // same fields.
+    // same fields.  Plans over three snapshots with kSnap = 1: two steps to a
+    // launch, from their own rows.
     template <typename Real, int kSnap, bool kFixed>
     int fused_steps(const etpic_particles *p, const etpic_species *sp, const StepPlan *plans, int nsteps, int most,
                     double dt, double omega, double *dG, double *rho, uint32_t flags, hipStream_t st,
@@ -5180,6 +5238,7 @@ struct etpic_ctx {
         const int64_t n = p->n, nt = host.nt;
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
         const int launches = (nsteps + most - 1) / most;
+        const bool pairs = kSnap == 1 && plans[0].snap[1];
         // few particles: 16 to a wavefront.  A wavefront is then bound by the
         // latency of its steps, and one whose 64 particles sit in 64 tets
         // takes its steps in four passes one after the other; up to two
@@ -5202,6 +5261,10 @@ struct etpic_ctx {
             if (i == 0 && parts_ready) {
                 k_fill_u32<<<grid_for(16 * nt), kBlock, 0, st>>>(reinterpret_cast<unsigned *>(d_tetG), 16 * nt, 0u);
                 HIP_TRY(hipGetLastError());
+            } else if (pairs) {
+                if (int r = launch_pair(plans[j0], j1 - j0 > 1 ? &plans[j0 + 1] : nullptr, omega,
+                                        i == 0 ? d_tetG : nullptr, st, ta))
+                    return r;
             } else if (i == 0) {
                 if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, st, ta)) return r;
             }
@@ -5212,8 +5275,8 @@ struct etpic_ctx {
             for (int j = j0; j < j1; ++j) {
                 const double c = std::cos(omega * plans[j].t), sn = std::sin(omega * plans[j].t);
                 for (int k = 0; k < kSnap; ++k) {
-                    ma.wc[j - j0][k] = plans[j].w[k] * c;
-                    ma.ws[j - j0][k] = plans[j].w[k] * sn;
+                    ma.wc[j - j0][k] = pairs ? (j == j0 ? 1.0 : 0.0) : plans[j].w[k] * c;
+                    ma.ws[j - j0][k] = pairs ? (j == j0 ? 0.0 : -1.0) : plans[j].w[k] * sn;
                 }
             }
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j1 == nsteps ? rho : nullptr);

@@ -262,3 +262,40 @@ def test_timed_call_without_room_for_its_events_changes_nothing(E, torch_cuda, d
     assert torch.allclose(g, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
     ctx.close()
     fresh.close()
+
+
+# meshes below and above 65,536 tets, few and more than few particles
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("side,n,nsteps", [(5, 65, 2), (5, 40_001, 2), (5, 1000, 3), (23, 1000, 3), (23, 32_769, 3),
+                                           (23, 70_001, 2), (5, 1000, 4)])
+def test_short_coarse_calls_equal_single_steps(E, torch_cuda, side, n, nsteps, precision):
+    """Two and three fine steps with three different snapshots against the same
+    call with its slices forced to one, which takes one step per launch."""
+    torch = torch_cuda
+    xyz, tv = synth.kuhn_mesh((side, side, side), (1.0, 1.0, 1.0), 0.1, np.random.default_rng(4))
+    ctx = E.Context(0)
+    ctx.upload_mesh(xyz, tv)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float64, device="cuda", generator=g)
+    b_dc, omega = 1e-4 * rnd(ctx.n_face), 2 * np.pi * 1e9
+    snaps = [E.Fields(10.0 * rnd(ctx.n_edge, 2), 1e-5 * rnd(ctx.n_face, 2), None, b_dc) for _ in range(3)]
+    lam = torch.rand(3, n, dtype=torch.float64, device="cuda", generator=g).sort(dim=0)[0].cpu().numpy()
+    lam = np.stack([lam[0], lam[1] - lam[0], lam[2] - lam[1]], 1)
+    tet = np.sort(np.random.default_rng(9).integers(tv.shape[0], size=n)).astype(np.int32)
+    p1 = E.Particles.from_numpy(tet, lam, 1e6 * rnd(n, 3).cpu().numpy(), np.arange(n), precision=precision)
+    p2 = p1.clone()
+    sp = E.Species(synth.Q_E, synth.M_E, 1.0)
+    g1 = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+    g2 = torch.zeros_like(g1)
+    rho1 = torch.zeros(ctx.n_vert, dtype=torch.float64, device="cuda")
+    rho2 = torch.zeros_like(rho1)
+    dtc = nsteps * 0.05 / side / 1e6
+    for _ in range(2):
+        ctx.coarse_step(p1, sp, snaps, 3 * dtc, dtc, nsteps, omega, g1, rho=rho1)
+        ctx.coarse_step(p2, sp, snaps, 3 * dtc, dtc, nsteps, omega, g2, rho=rho2, flags=E.STEP_XCD_REMAP | E.STEP_SLICES_1)
+    ctx.check()
+    assert (p1.tet.cpu().numpy() != tet).mean() > 0.01
+    same_state(p1.to_numpy(), p2.to_numpy())
+    assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
+    assert torch.allclose(rho1, rho2, rtol=0, atol=1e-13 * rho2.abs().max().item())
+    ctx.close()
