@@ -34,7 +34,8 @@
  *   mesh tables         etpic_mesh_sizes       -> etpic_mesh_upload
  *   field-step solver   etpic_field_bytes      -> etpic_field_setup
  *   Gauss-law solver    etpic_ns_bytes         -> etpic_ns_setup
- *   downshifted rows    etpic_ds_rows_bytes    -> etpic_ds_rows_bind
+ *   wide rows           etpic_ds_rows_bytes    -> etpic_ds_rows_bind
+ *                       (downshifted steps; optional for coarse steps)
  *   projector object    etpic_qh_bytes         -> etpic_qh_bind
  * Each buffer must be 256-byte aligned, at least the queried size, and stay
  * valid (not freed, not written by the caller) while the object that was
@@ -336,7 +337,10 @@ int etpic_run_steps(etpic_ctx *ctx, const etpic_particles *p, int precision, con
  * etpic_gather_push_deposit.  dG accumulates the deposit of all fine steps;
  * rho, if not NULL, receives q w lam_k at the end of the last fine step.
  * flags as for etpic_gather_push_deposit; consecutive fine steps share
- * launches as in etpic_run_steps.  Asynchronous on `stream`.
+ * launches as in etpic_run_steps if wide rows are bound (etpic_ds_rows_bind),
+ * which then hold the three snapshots' parts of each tet's row; without them,
+ * and in calls of two steps, two steps share a launch: the same results.
+ * Asynchronous on `stream`.
  * Errors: EINVAL, ESTATE, EHIP; in-kernel errors via etpic_check. */
 int etpic_coarse_step(etpic_ctx *ctx, const etpic_particles *p, int precision, const etpic_species *sp,
                       const etpic_fields snap[3], double t_coarse, double dt_coarse, int fine_steps, double omega,
@@ -430,10 +434,12 @@ int etpic_gauss_residual_noalloc(etpic_ctx *ctx, const double *dG, const double 
  * velocity update, float64 positions, barycentric increments and deposit,
  * as the mixed fine-step form). */
 
-/* Bytes of the per-tet complex-envelope rows of the downshifted step (72
- * float64 per tet of the uploaded mesh), and binding of the caller's buffer
- * (device, 256-byte aligned) that holds them; etpic_ds_steps needs it (ESTATE
- * otherwise) and rebuilds the rows at each call.  A mesh upload forgets it. */
+/* Bytes of the wide rows (72 float64 per tet of the uploaded mesh), and
+ * binding of the caller's buffer (device, 256-byte aligned) that holds them:
+ * the complex-envelope rows of the downshifted steps (etpic_ds_steps needs the
+ * buffer, ESTATE otherwise; its float64 form does not read it) or the three
+ * snapshots' row parts of etpic_coarse_step (which does without).  Every call
+ * rebuilds its rows.  A mesh upload forgets the buffer. */
 int etpic_ds_rows_bytes(const etpic_ctx *ctx, size_t *bytes);
 int etpic_ds_rows_bind(etpic_ctx *ctx, void *dev_buf, size_t bytes);
 
@@ -454,8 +460,7 @@ int etpic_ds_history_bytes(int64_t n, int precision, size_t *bytes_out);
  * which moves the history with the particles (etpic_sort does not: restart
  * with hist0 = 0 after it).  dG accumulates the deposit of all steps, rho (if not NULL)
  * receives q w lam_k after the last one.  flags as for
- * etpic_gather_push_deposit (XCD_REMAP, TIMING, WALK_BY_SLICE).  The
- * complex-envelope rows go to the buffer of etpic_ds_rows_bind.
+ * etpic_gather_push_deposit (XCD_REMAP, TIMING, WALK_BY_SLICE).
  * Asynchronous on `stream`.  Errors: EINVAL, ESTATE, EHIP; in-kernel errors
  * via etpic_check. */
 int etpic_ds_steps(etpic_ctx *ctx, const etpic_particles *p, int precision, void *hist, size_t hist_bytes,

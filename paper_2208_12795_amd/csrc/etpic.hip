@@ -1695,7 +1695,9 @@ __global__ void __launch_bounds__(kBlock) k_walk(StepArgs<Real> a) {
 // electrons: 7 launches 147, 4 launches 122 us), while of many particles more steps in
 // one launch mean more of them that finish it in the walk.
 constexpr int kMaxFused = 32, kMaxFusedMany = 16;
-constexpr int kCoefDoubles = kRowParts<3> * kRowReals;   // per tet: the largest of the coefficient forms
+// per tet: the largest of the coefficient forms but the parts of three
+// snapshots, which go to the wide rows (etpic_ds_rows_bind) where those are bound
+constexpr int kCoefDoubles = kRowParts<1> * kRowReals;
 
 template <int kSnap>
 struct MultiArgs {
@@ -2239,6 +2241,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_multi(StepArgs<Real> a, MultiAr
 // reals per tet, A_re, A_im, A_dc, C_re, C_im, C_dc, each 4 x 3 (A_k at 3k),
 // built once per call since the fields are fixed within it.
 constexpr int kEnvRow = 72;
+static_assert(kRowParts<3> * kRowReals <= kEnvRow, "the parts of three snapshots fit the wide rows");
 
 __global__ void __launch_bounds__(kBlock) k_tet_coef_env(int64_t nt, const double *__restrict__ prow,
                                                          const int32_t *__restrict__ tetface, FieldPtrs F,
@@ -4813,7 +4816,7 @@ struct etpic_ctx {
     float *d_geo32 = nullptr;         // nt rows of GeoRow<float>
     int32_t *d_tetface = nullptr;     // nt*4 face ids (face k opposite vertex k)
     void *d_coef = nullptr;          // nt*kCoefDoubles doubles: a step's CoefRow rows or a call's row parts
-    double *d_coef_env = nullptr;    // nt*kEnvRow complex-envelope rows (bound by etpic_ds_rows_bind)
+    double *d_coef_env = nullptr;    // nt*kEnvRow: wide rows (bound by etpic_ds_rows_bind)
     int32_t *d_v2e_ptr = nullptr;
     int32_t *d_v2e_code = nullptr;
     int32_t *d_e2s_ptr = nullptr;    // edge -> tet-slot CSR (ne+1)
@@ -5184,9 +5187,11 @@ struct etpic_ctx {
     // On 384,000 tets, mixed, one step per launch / parts / pairs: two steps of
     // 2e5 particles 217 / 228 / 159 us, of 1e7 603 / 576 / 440; three steps of
     // 1,000 156 / 174 / 146, but of 2e5 294 / 229 us by one launch already, as
-    // are all on few tets (750: 72 / 43), where the launches count.
+    // are all on few tets (750: 72 / 43), where the launches count.  Any
+    // number of steps where no wide rows are bound to hold the parts.
     bool in_pairs(const StepPlan &first, int nsteps, int64_t n) const {
-        return first.snap[1] && (nsteps == 2 || (nsteps == 3 && n <= kFewParticles && host.nt >= 65536));
+        return first.snap[1] &&
+               (!d_coef_env || nsteps == 2 || (nsteps == 3 && n <= kFewParticles && host.nt >= 65536));
     }
 
     // Blocks of k_walk_multi.  Few particles: as many as the queue has parts (an
@@ -5198,6 +5203,11 @@ struct etpic_ctx {
         return n <= kFewParticles ? kShards : n < ((int64_t)1 << 26) ? kLeaverBlocks : 2 * kLeaverBlocks;
     }
 
+    template <int kSnap>
+    double *parts_table() const {
+        return kSnap == 3 ? d_coef_env : static_cast<double *>(d_coef);
+    }
+
     // the parts of the 10-real rows, from which multi-step launches form the
     // row of each of their steps
     template <int kSnap>
@@ -5205,7 +5215,7 @@ struct etpic_ctx {
         FieldPtrs F = field_ptrs(snap, w, 1.0, 0.0);
         F.xcd = coef_xcd();
         launch_timed(k_tet_coef<double, kSnap, kCoefParts>, grid_for(2 * host.nt), st, ev_start(ta, 0), ev_stop(ta, 0),
-                     host.nt, d_gpush64, d_tetface, F, static_cast<double *>(d_coef), d_tetG);
+                     host.nt, d_gpush64, d_tetface, F, parts_table<kSnap>(), d_tetG);
         HIP_TRY(hipGetLastError());
         return ETPIC_OK;
     }
@@ -5269,7 +5279,7 @@ struct etpic_ctx {
                 if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, st, ta)) return r;
             }
             MultiArgs<kSnap> ma{};
-            ma.parts = static_cast<const double *>(d_coef);
+            ma.parts = parts_table<kSnap>();
             ma.nsteps = j1 - j0;
             ma.width = width;
             for (int j = j0; j < j1; ++j) {

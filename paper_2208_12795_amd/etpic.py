@@ -550,6 +550,12 @@ class Context:
         d = parts.desc()
         sp = species.c()
         arr = (_Fields * 3)(*[f.desc(self.n_edge, self.n_face) for f in snaps])
+        if fine_steps > 2 and self._ds_rows is None:
+            import torch
+            try:
+                self._bind_wide_rows(stream)
+            except torch.OutOfMemoryError:   # they are not needed, two steps per launch then
+                pass
         _chk(lib().etpic_coarse_step(self._h, C.byref(d), parts.precision, C.byref(sp), arr, float(t_coarse),
                                      float(dt_coarse), int(fine_steps), float(omega), self._dg(dG), self._rho(rho),
                                      int(flags), _stream(stream)))
@@ -570,6 +576,18 @@ class Context:
                                         int(step0), int(nsteps), float(dt), float(omega), self._dg(dG), self._rho(rho),
                                         int(flags), _stream(stream)))
 
+    def _bind_wide_rows(self, stream):
+        """The wide rows (downshifted steps, coarse steps of several fine ones),
+        once per mesh, from the memory of the stream that uses them first."""
+        if self._ds_rows is None:
+            import torch
+            b = C.c_size_t(0)
+            _chk(lib().etpic_ds_rows_bytes(self._h, C.byref(b)))
+            with torch.cuda.stream(stream):   # (None: the current one)
+                buf = _device_buffer(b.value, self.device)
+            _chk(lib().etpic_ds_rows_bind(self._h, C.c_void_p(buf.data_ptr()), buf.numel()))
+            self._ds_rows = buf
+
     # downshifted integrator (float64) --------------------------------------------
     def ds_history(self, parts):
         """A zeroed history buffer for parts ([48, n] of the velocity type on the device)."""
@@ -583,12 +601,7 @@ class Context:
                  flags=STEP_XCD_REMAP, stream=None):
         """nsteps downshifted steps from step0 with hist0 earlier ones in hist."""
         assert hist.is_contiguous() and hist.dtype.is_floating_point
-        if self._ds_rows is None:
-            b = C.c_size_t(0)
-            _chk(lib().etpic_ds_rows_bytes(self._h, C.byref(b)))
-            buf = _device_buffer(b.value, self.device)
-            _chk(lib().etpic_ds_rows_bind(self._h, C.c_void_p(buf.data_ptr()), buf.numel()))
-            self._ds_rows = buf
+        self._bind_wide_rows(stream)
         d = parts.desc()
         sp = species.c()
         fd = fields.desc(self.n_edge, self.n_face)

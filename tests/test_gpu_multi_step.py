@@ -299,3 +299,27 @@ def test_short_coarse_calls_equal_single_steps(E, torch_cuda, side, n, nsteps, p
     assert torch.allclose(g1, g2, rtol=0, atol=1e-13 * g2.abs().max().item())
     assert torch.allclose(rho1, rho2, rtol=0, atol=1e-13 * rho2.abs().max().item())
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("n,ordered,nsteps", [(65, False, 7), (40_001, True, 10)])
+def test_coarse_step_without_wide_rows(E, torch_cuda, n, ordered, nsteps, precision):
+    """A context to which no wide rows were given takes two steps per launch:
+    the results of one that has them."""
+    torch = torch_cuda
+    out = []
+    for bound in (True, False):
+        w, ctx, f, sp, p = problem(E, torch, n, precision, ordered)
+        snaps = [E.Fields.from_numpy(e, b, None, w.b_dc) for e, b in synth.envelope_snapshots(w, seed=3)]
+        if not bound:
+            ctx._bind_wide_rows = lambda stream: None
+        g = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+        dtc = nsteps * 300.0 * w.dt
+        for k in range(2):
+            ctx.coarse_step(p, sp, snaps, (3 + k) * dtc, dtc, nsteps, w.omega, g)
+        ctx.check()
+        assert (ctx._ds_rows is not None) == bound
+        out.append((p.to_numpy(), g))
+        ctx.close()
+    same_state(out[0][0], out[1][0])
+    assert torch.allclose(out[0][1], out[1][1], rtol=0, atol=1e-13 * out[0][1].abs().max().item())
