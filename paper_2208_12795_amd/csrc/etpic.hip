@@ -2332,6 +2332,7 @@ struct DsArgs {
     int phase;                // number of the first step, mod 4
     int hist0;                // downshifted steps taken before it (at most 3 matter)
     int nsteps;
+    int width;                // particles per wavefront (push_width)
     Real P[3], Q[9];          // weights that do not depend on the step's time (3 nodes; Q[3 j + k])
     Real ab[4];               // Adams-Bashforth coefficients times the step
     Real qm;
@@ -2549,6 +2550,31 @@ __device__ __forceinline__ bool ds_step(const DsArgs<Real> &d, int j, const DsRo
     return t[0] >= 0.0 && t[1] >= 0.0 && t[2] >= 0.0 && t[3] >= 0.0;
 }
 
+// kLen reals of each of a wavefront's nr tets, `stride` apart in memory, into
+// its LDS rows, eight loads of a lane in flight together (one after the other
+// they were most of a launch of few particles: one step of 1,000 on 750 tets,
+// mixed, 66 -> 41 us with 16 particles to a wavefront; of 4e6 on 384,000, ten
+// steps, 870 -> 732).
+template <int kLen, int kRow, typename Src, typename Real>
+__device__ __forceinline__ void stage_rows(const Src *__restrict__ src, int stride, const int *tets, int nr, int ln,
+                                           Real *rows) {
+    constexpr int kLoads = 8;
+    const int total = nr * kLen;
+#pragma unroll 1
+    for (int i0 = ln; i0 < total; i0 += 64 * kLoads) {
+        Src x[kLoads];
+        int at[kLoads];
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const int i = min(i0 + 64 * k, total - 1), j = i / kLen, c = i - j * kLen;
+            at[k] = j * kRow + c;
+            x[k] = src[(int64_t)max(tets[j], 0) * stride + c];
+        }
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) rows[at[k]] = (Real)x[k];
+    }
+}
+
 // Real = double: the float64 form.  Real = float: samples, velocities and the
 // velocity update in float32, positions, the barycentric increments and the
 // deposit in float64 (the mixed form of the fine-step kernel).
@@ -2569,13 +2595,13 @@ __global__ void __launch_bounds__(kBlock) k_push_ds(StepArgs<Real> a, DsArgs<Rea
     const unsigned ln = threadIdx.x & 63;
     Real *rows = reinterpret_cast<Real *>(s_lds[wv]);
     int *s_tet = reinterpret_cast<int *>(s_lds[wv] + kRowBytes);
-    const int64_t b0 = ((int64_t)blk * kWaves + wv) * 64;
+    const int64_t b0 = ((int64_t)blk * kWaves + wv) * d.width;
     if (b0 >= a.n) return;   // the whole wavefront; no block barrier below
     const int64_t p = b0 + ln;
     int T = -1;
     double l[4] = {0.0, 0.0, 0.0, 0.0};   // l[0] unused: lam0 is implicit
     DsState<Real> s{};
-    if (p < a.n) {
+    if (p < a.n && (int)ln < d.width) {
         T = __builtin_nontemporal_load(lane_at(a.tet + b0, ln));
         l[1] = __builtin_nontemporal_load(lane_at(a.lam1 + b0, ln));
         l[2] = __builtin_nontemporal_load(lane_at(a.lam2 + b0, ln));
@@ -2603,14 +2629,9 @@ __global__ void __launch_bounds__(kBlock) k_push_ds(StepArgs<Real> a, DsArgs<Rea
         const int nr = min(kRuns, nruns - r0);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        for (int i = ln; i < nr * (kSrc + kGeo + 9); i += 64) {
-            const int j = i / (kSrc + kGeo + 9), c = i - j * (kSrc + kGeo + 9);
-            const int64_t Tj = max(s_tet[r0 + j], 0);
-            rows[j * kRow + c] = c < kSrc ? (Real)d.rows[Tj * kSrc + c]
-                                 : c < kSrc + kGeo
-                                     ? a.geo[Tj * GeoRow<Real>::kStride + c - kSrc]
-                                     : a.gpush[Tj * PushRow<Real>::kStride + c - kSrc - kGeo];
-        }
+        stage_rows<kSrc, kRow>(d.rows, kSrc, s_tet + r0, nr, ln, rows);
+        if (kGeo) stage_rows<9, kRow>(a.geo, GeoRow<Real>::kStride, s_tet + r0, nr, ln, rows + kSrc);
+        stage_rows<9, kRow>(a.gpush, PushRow<Real>::kStride, s_tet + r0, nr, ln, rows + kSrc + kGeo);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         bool live = act && run >= r0 && run < r0 + nr;
@@ -2651,7 +2672,10 @@ __global__ void __launch_bounds__(kBlock) k_push_ds(StepArgs<Real> a, DsArgs<Rea
     double g6[6];
     edge_sums(sum, g6);
     const bool flush = act && runs.lane == runs.run_end;
-    flush_runs_together<Real, true>(a, T, g6, runs, flush, reinterpret_cast<double2 *>(rows));
+    if (a.tetG)
+        flush_runs_together<Real, true>(a, T, g6, runs, flush, reinterpret_cast<double2 *>(rows));
+    else
+        flush_runs_together<Real, false>(a, T, g6, runs, flush, reinterpret_cast<double2 *>(rows));
     if (kRho) {
         double r4[4];
 #pragma unroll
@@ -2703,12 +2727,13 @@ __device__ __forceinline__ void walk_leaver_ds(const StepArgs<Real> &a, const Ds
         if (!some) return;
         double g6[6];
         edge_sums(sum, g6);
-        double *slot = a.tetG + (int64_t)T * 8;
+        const double none[4] = {0.0, 0.0, 0.0, 0.0};
+        if (a.tetG)
+            flush_run<Real, false, true>(a, T, g6, none);
+        else
+            flush_run<Real, false, false>(a, T, g6, none);
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            if (g6[e] != 0.0) unsafeAtomicAdd(&slot[e], a.qw * g6[e]);
-            sum[e] = 0.0;
-        }
+        for (int e = 0; e < 6; ++e) sum[e] = 0.0;
         some = false;
     };
     bool walks = true;
@@ -5181,6 +5206,16 @@ struct etpic_ctx {
                                                            (INT32_MAX - 2) / std::max<int64_t>(host.nt, 1)));
     }
 
+    // Particles per wavefront of a multi-step launch.  Few particles: 16.  A
+    // wavefront is then bound by the latency of its steps, and one whose 64
+    // particles sit in 64 tets takes its steps in four passes one after the
+    // other; up to two wavefronts per SIMD the passes run side by side
+    // instead.  (Not where leavers are queued by 64-particle slice: each slice
+    // has one owner.)
+    static int push_width(int64_t n, uint32_t flags) {
+        return n <= kFewParticles && !(flags & ETPIC_STEP_WALK_BY_SLICE) ? 16 : 64;
+    }
+
     // Steps over three snapshots that go two to a launch, from the two steps'
     // own rows (kCoefPair, 240 B per tet) instead of the parts of three
     // snapshots (560 B per tet, which the particle kernel stages too).
@@ -5211,11 +5246,11 @@ struct etpic_ctx {
     // the parts of the 10-real rows, from which multi-step launches form the
     // row of each of their steps
     template <int kSnap>
-    int launch_parts(const etpic_fields *const snap[3], const double w[3], hipStream_t st, TimingSet *ta) {
+    int launch_parts(const etpic_fields *const snap[3], const double w[3], double *slots, hipStream_t st, TimingSet *ta) {
         FieldPtrs F = field_ptrs(snap, w, 1.0, 0.0);
         F.xcd = coef_xcd();
         launch_timed(k_tet_coef<double, kSnap, kCoefParts>, grid_for(2 * host.nt), st, ev_start(ta, 0), ev_stop(ta, 0),
-                     host.nt, d_gpush64, d_tetface, F, parts_table<kSnap>(), d_tetG);
+                     host.nt, d_gpush64, d_tetface, F, parts_table<kSnap>(), slots);
         HIP_TRY(hipGetLastError());
         return ETPIC_OK;
     }
@@ -5249,12 +5284,7 @@ struct etpic_ctx {
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
         const int launches = (nsteps + most - 1) / most;
         const bool pairs = kSnap == 1 && plans[0].snap[1];
-        // few particles: 16 to a wavefront.  A wavefront is then bound by the
-        // latency of its steps, and one whose 64 particles sit in 64 tets
-        // takes its steps in four passes one after the other; up to two
-        // wavefronts per SIMD the passes run side by side instead.  (Not where
-        // leavers are queued by 64-particle slice: each slice has one owner.)
-        const int width = n <= kFewParticles && !(flags & ETPIC_STEP_WALK_BY_SLICE) ? 16 : 64;
+        const int width = push_width(n, flags);
         const unsigned push_grid = grid_for((n + width - 1) / width * 64);
         TimingSet *ta = nullptr;
         unsigned *ctr = nullptr;
@@ -5276,7 +5306,7 @@ struct etpic_ctx {
                                         i == 0 ? d_tetG : nullptr, st, ta))
                     return r;
             } else if (i == 0) {
-                if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, st, ta)) return r;
+                if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, d_tetG, st, ta)) return r;
             }
             MultiArgs<kSnap> ma{};
             ma.parts = parts_table<kSnap>();
@@ -5393,9 +5423,17 @@ struct etpic_ctx {
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
         const etpic_fields *snap[3] = {f, nullptr, nullptr};
         const double w1[3] = {1.0, 0.0, 0.0};
+        const int width = push_width(n, flags);
+        const unsigned push_grid = grid_for((n + width - 1) / width * 64);
         TimingSet *ta = nullptr;
         unsigned *ctr = nullptr;
         const int alone = std::min(nsteps, std::max(0, 3 - hist0));   // launches of the first three steps
+        // One step of fewer particles than tets: most slots would be cleared and
+        // gathered for nothing, so its currents go straight to the edges
+        // (384,000 tets, mixed: 1,000 particles 182 -> 158 us, 2e5 257 -> 234;
+        // of 4e6 the slots' one line per run is worth the gather, 613 us with
+        // direct atomics, 533 with slots).
+        double *const slots = nsteps == 1 && n < nt ? nullptr : d_tetG;
         if (int r = timing_room(flags, alone + (nsteps - alone + most - 1) / most)) return r;
         for (int j0 = 0, i = 0; j0 < nsteps; ++i) {
             const int H = hist0 + j0;
@@ -5409,16 +5447,16 @@ struct etpic_ctx {
             ta = time_all ? ts : nullptr;
             if (i == 0) {
                 if constexpr (f64) {
-                    if (int r = launch_parts<1>(snap, w1, st, ta)) return r;
+                    if (int r = launch_parts<1>(snap, w1, slots, st, ta)) return r;
                 } else {
                     launch_timed(k_tet_coef_env, dim3(grid_for(nt), 6), st, ev_start(ta, 0), ev_stop(ta, 0), nt,
-                                 d_gpush64, d_tetface, field_ptrs(snap, w1, 1.0, 0.0), d_coef_env, d_tetG);
+                                 d_gpush64, d_tetface, field_ptrs(snap, w1, 1.0, 0.0), d_coef_env, slots);
                     HIP_TRY(hipGetLastError());
                 }
             }
             StepArgs<Real> a = step_args<Real>(p, sp, dt, dG, j0 + len == nsteps ? rho : nullptr);
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
-            a.tetG = d_tetG;
+            a.tetG = slots;
             ctr = d_walk_ctr + (1 + (i & 1)) * kCtrStride;
             unsigned *next = d_walk_ctr + (1 + ((i + 1) & 1)) * kCtrStride;
             a.walk_ctr = ctr;
@@ -5429,6 +5467,7 @@ struct etpic_ctx {
             d.phase = (int)((((step0 + j0) % 4) + 4) % 4);
             d.hist0 = H;
             d.nsteps = len;
+            d.width = width;
             d.qm = (Real)(sp->q / sp->m);
             for (int j = 0; j < len; ++j) {
                 const int K = std::min(H + j, 2) + 1, A = std::min(H + j, 3) + 1;
@@ -5447,15 +5486,18 @@ struct etpic_ctx {
                 for (int k = 0; k < 4; ++k) d.ab[k] = (Real)W.ab[k];
             }
             if (a.rho)
-                launch_timed(k_push_ds<Real, true, kEdc>, grid_for(n), st, ev_start(ts, 1), ev_stop(ts, 1), a, d, remap);
+                launch_timed(k_push_ds<Real, true, kEdc>, push_grid, st, ev_start(ts, 1), ev_stop(ts, 1), a, d, remap);
             else
-                launch_timed(k_push_ds<Real, false, kEdc>, grid_for(n), st, ev_start(ts, 1), ev_stop(ts, 1), a, d, remap);
+                launch_timed(k_push_ds<Real, false, kEdc>, push_grid, st, ev_start(ts, 1), ev_stop(ts, 1), a, d, remap);
             HIP_TRY(hipGetLastError());
             launch_timed(k_walk_ds<Real, kEdc>, kLeaverBlocks, st, ev_start(ta, 2), ev_stop(ta, 2), a, d, next);
             HIP_TRY(hipGetLastError());
             j0 += len;
         }
-        return launch_edges(dG, st, ta, ctr);
+        if (slots) return launch_edges(dG, st, ta, ctr);
+        k_fill_u32<<<grid_for(kCtrStride), kBlock, 0, st>>>(ctr, kCtrStride, 0u);
+        HIP_TRY(hipGetLastError());
+        return ETPIC_OK;
     }
 
     // Weights of one downshifted step [t0, t0 + h] with K Lagrange nodes at
@@ -6245,7 +6287,7 @@ int etpic_backward(etpic_ctx *ctx, int64_t n, const etpic_species *sp, const etp
     {
         const etpic_fields *snap[3] = {f, nullptr, nullptr};
         const double w1[3] = {1.0, 0.0, 0.0};
-        if (int r = ctx->launch_parts<1>(snap, w1, st, nullptr)) return r;
+        if (int r = ctx->launch_parts<1>(snap, w1, nullptr, st, nullptr)) return r;
     }
     // both counter sets of the sweep, all parts of each: a launch's leavers
     // kernel clears the other set only

@@ -323,3 +323,13 @@ def test_coarse_step_without_wide_rows(E, torch_cuda, n, ordered, nsteps, precis
         ctx.close()
     same_state(out[0][0], out[1][0])
     assert torch.allclose(out[0][1], out[1][1], rtol=0, atol=1e-13 * out[0][1].abs().max().item())
+
+
+# 32768 and 32769: 16 and 64 particles to a wavefront; 749 and 750 on 750 tets: the
+# currents of one step straight to the edges and by the tets' slots
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,calls,edc", [(1, 3, False), (749, 6, True), (750, 6, False), (32768, 5, False), (32769, 5, True)])
+def test_one_step_downshifted_calls_equal_one_call(E, torch_cuda, n, calls, edc, precision):
+    """As test_downshifted_launch_split_changes_nothing."""
+    test_downshifted_launch_split_changes_nothing(E, torch_cuda, n, n > 1000, calls, 100.0 if n > 1000 else 1.0, edc, False,
+                                                  precision)
