@@ -837,8 +837,10 @@ int etpic_cotree_step(etpic_cotree *z, etpic_qh *qh, double dt, double omega, do
  * launch that takes several steps books its time evenly over them):
  * ms_out[0] = particle kernel (gather, push, in-tet deposit) of the steps
  * that update the particles in place, ms_out[1] = per-tet coefficient kernel
- * (once per multi-step call), ms_out[2] = walk kernel (with the gather of the
- * per-tet current sums onto the edges at the end of a call), ms_out[3] =
+ * (once per multi-step call, or per two steps where those share a launch),
+ * ms_out[2] = walk kernel (with the gather of the per-tet current sums onto
+ * the edges at the end of a call, and with the next step's coefficient pass
+ * where a flag forces the slices of a call of several steps), ms_out[3] =
  * particle kernel of the steps that also sort (the first step of
  * etpic_sort_run_steps); [1] and [2] only for steps run with
  * ETPIC_STEP_TIMING_ALL (0 otherwise).  launches_out (may be NULL) = number of timed steps
