@@ -1538,9 +1538,10 @@ k_push_sort_slices(StepArgs<Real> a, int remap) {
 // VGPRs, six wavefronts per SIMD, and measured no gain worth it).  Chosen where
 // the mesh's float rows outgrow the Infinity Cache, so that a wavefront's row
 // reads are HBM round trips: there the state loads of one slice overlap the
-// row round trip of the other.
+// row round trip of the other.  (At most 7 wavefronts: 8 leave the compact
+// form too few registers, 1683 -> 1800 us for ten steps of 1e7.)
 template <bool kFixed>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7)))
 k_push_pipe(StepArgs<float> a, int remap) {
     push_slices<float, 2, false, false, kFixed, true>(a, remap);
 }
