@@ -62,6 +62,7 @@
 #include "etpic.h"
 #include "field_host.hpp"
 #include "mesh_host.hpp"
+#include "solve_host.hpp"
 #include "checkpoint_host.hpp"
 
 using etpic::TetTopo;
@@ -3952,13 +3953,7 @@ __device__ __forceinline__ void all_sum4(double v[4], double tot[4]) {
     for (int k = 0; k < 4; ++k) tot[k] = res[k];
 }
 
-// What the host follows a solve by: three words of pinned memory.  word holds
-// (k + 1) << 1 | done of the last product launch that ran; r2 and b2 are read
-// once the stream has drained.
-struct SolveWatch {
-    unsigned long long word;
-    double r2, b2;
-};
+using etpic::SolveWatch;
 
 // Every kSolveReport-th launch reports, and the last: a store to host memory
 // keeps its kernel from ending for 1-2 us.
@@ -4484,6 +4479,12 @@ __device__ __forceinline__ bool res_exchange(ResShared &sh, unsigned long long *
     return sh.ok != 0;
 }
 
+// A block whose wait ran out leaves without its rows of the result: the host
+// must not take block 0's report for the whole.
+__device__ __forceinline__ void give_up(SolveWatch *watch) {
+    if (threadIdx.x == 0) __hip_atomic_store(&watch->gave_up, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ double quad_sum(double x) {   // over the kResLanes lanes of a row
     x += dpp_get<0xb1, 0xf>(x);   // quad_perm 1, 0, 3, 2
     x += dpp_get<0x4e, 0xf>(x);   // quad_perm 2, 3, 0, 1
@@ -4557,7 +4558,7 @@ __global__ void __launch_bounds__(kResThreads) k_ns_resident(NsCsr S, double *sc
             qi = az + be * qi;
             w[0] = pi * qi;
         }
-        if (!res_exchange<1>(sh, slots, s, w)) return;
+        if (!res_exchange<1>(sh, slots, s, w)) return give_up(watch);
         const double al = w[0] != 0.0 ? rn / w[0] : 0.0;
         w[0] = w[1] = 0.0;
         if (owner) {
@@ -4568,7 +4569,7 @@ __global__ void __launch_bounds__(kResThreads) k_ns_resident(NsCsr S, double *sc
             w[0] = ri * zi;
             w[1] = ri * ri;
         }
-        if (!res_exchange<2>(sh, slots, s + 1, w)) return;
+        if (!res_exchange<2>(sh, slots, s + 1, w)) return give_up(watch);
         ro = rn;
         rn = w[0];
         r2 = w[1];
@@ -4656,7 +4657,7 @@ __global__ void __launch_bounds__(kResThreads) k_cocg_resident(FieldCsr S, doubl
             w[0] = pq.x;
             w[1] = pq.y;
         }
-        if (!res_exchange<2>(sh, slots, s, w)) return;
+        if (!res_exchange<2>(sh, slots, s, w)) return give_up(watch);
         const double2 pq = make_double2(w[0], w[1]);
         const double2 al = (pq.x == 0.0 && pq.y == 0.0) ? zero : cdiv(rn, pq);
         w[0] = w[1] = w[2] = 0.0;
@@ -4671,7 +4672,7 @@ __global__ void __launch_bounds__(kResThreads) k_cocg_resident(FieldCsr S, doubl
             w[1] = rz.y;
             w[2] = ri.x * ri.x + ri.y * ri.y;
         }
-        if (!res_exchange<3>(sh, slots, s + 1, w)) return;
+        if (!res_exchange<3>(sh, slots, s + 1, w)) return give_up(watch);
         ro = rn;
         rn = make_double2(w[0], w[1]);
         r2 = w[2];
@@ -6657,18 +6658,20 @@ int watch_solve(SolveWatch &W, hipStream_t st, int max_iter, Launch &&launch) {
 
 // A solve in one launch: launch(blocks) enqueues it for `rows` rows.  False in
 // `took` if there are more rows than one block per CU takes (kResMaxBlocks x
-// kResRows = 65,536: their vectors and matrix entries fill the registers) or if
-// the blocks did not meet; the start has to be enqueued again then.
+// kResRows = 65,536: their vectors and matrix entries fill the registers), if
+// the blocks did not meet or if one left a wait; the start has to be enqueued
+// again then.
 template <typename Launch>
 int resident_solve(SolveWatch &W, hipStream_t st, int64_t rows, bool &took, Launch &&launch) {
     took = false;
     const int64_t blocks = (rows + kResRows - 1) / kResRows;
     if (blocks > kResMaxBlocks) return ETPIC_OK;
     __atomic_store_n(&W.word, 0ull, __ATOMIC_RELAXED);
+    __atomic_store_n(&W.gave_up, 0ull, __ATOMIC_RELAXED);
     launch((unsigned)blocks);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));
-    took = __atomic_load_n(&W.word, __ATOMIC_RELAXED) != 0;
+    took = etpic::one_launch_took(W);
     return ETPIC_OK;
 }
 
