@@ -4351,7 +4351,7 @@ constexpr int kResVals = 4;
 constexpr int kResStride = 8;                   // words from block to block
 constexpr size_t kResSlots = (size_t)3 * kResMaxBlocks * kResStride;
 constexpr unsigned kMeetClosed = 0x80000000u;
-constexpr long long kMeetTicks = 50000;        // 0.5 ms of the 100 MHz counter
+constexpr long long kMeetTicks = 50000;        // 0.5 ms of the 100 MHz counter (OneLaunchTrials: what follows it)
 constexpr unsigned kSlotSpins = 1u << 22;
 constexpr unsigned long long kSlotEmpty = 0xfff8c0de00000001ull;
 
@@ -4884,6 +4884,7 @@ struct etpic_ctx {
     unsigned long long *d_runstat = nullptr;
     unsigned long long *h_runstat = nullptr;   // (and two words the residual's maxima are written into)
     SolveWatch *h_watch = nullptr;             // pinned, behind those
+    etpic::OneLaunchTrials field_trials, ns_trials;   // (their solves take different numbers of blocks)
     hipEvent_t runstat_ev = nullptr;
     bool runstat_pending = false;
     int64_t runstat_n = 0;
@@ -6656,22 +6657,26 @@ int watch_solve(SolveWatch &W, hipStream_t st, int max_iter, Launch &&launch) {
     return ETPIC_OK;
 }
 
-// A solve in one launch: launch(blocks) enqueues it for `rows` rows.  False in
-// `took` if there are more rows than one block per CU takes (kResMaxBlocks x
-// kResRows = 65,536: their vectors and matrix entries fill the registers), if
-// the blocks did not meet or if one left a wait; the start has to be enqueued
-// again then.
+// A solve in one launch: launch(blocks) enqueues it for `rows` rows.  Not
+// tried (kNotTried) if there are more rows than one block per CU takes
+// (kResMaxBlocks x kResRows = 65,536: their vectors and matrix entries fill the
+// registers) or if the last trials say so; kFailed if the blocks did
+// not meet or one left a wait: the start has to be enqueued again then.
+enum OneLaunch { kNotTried, kTook, kFailed };
+
 template <typename Launch>
-int resident_solve(SolveWatch &W, hipStream_t st, int64_t rows, bool &took, Launch &&launch) {
-    took = false;
+int resident_solve(SolveWatch &W, etpic::OneLaunchTrials &trials, hipStream_t st, int64_t rows, OneLaunch &way,
+                   Launch &&launch) {
+    way = kNotTried;
     const int64_t blocks = (rows + kResRows - 1) / kResRows;
-    if (blocks > kResMaxBlocks) return ETPIC_OK;
+    if (blocks > kResMaxBlocks || !trials.tries()) return ETPIC_OK;
     __atomic_store_n(&W.word, 0ull, __ATOMIC_RELAXED);
     __atomic_store_n(&W.gave_up, 0ull, __ATOMIC_RELAXED);
     launch((unsigned)blocks);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));
-    took = etpic::one_launch_took(W);
+    way = etpic::one_launch_took(W) ? kTook : kFailed;
+    trials.ended(way == kTook);
     return ETPIC_OK;
 }
 
@@ -6846,15 +6851,14 @@ int etpic_field_step(etpic_ctx *ctx, double t_next, double *u, double *v, double
     start();
     HIP_TRY(hipGetLastError());
     unsigned long long *slots = reinterpret_cast<unsigned long long *>(F.partial + 4 * (F.nb + kNsBlocks));
-    bool took = false;
-    if (int rc = resident_solve(W, st, ne, took, [&](unsigned blocks) {
+    OneLaunch way;
+    if (int rc = resident_solve(W, ctx->field_trials, st, ne, way, [&](unsigned blocks) {
             k_cocg_resident<<<blocks, kResThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, F.dinv, x, r, z, pa, ge, slots,
                                                             tol2, max_iter, &W);
         }))
         return rc;
-    if (!took && ne <= (int64_t)kResMaxBlocks * kResRows) start();
-    // (else: too many rows, or other work held the CUs)
-    if (!took) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
+    if (way == kFailed) start();
+    if (way != kTook) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
             k_cocg_apply<<<ga, kNsThreads, 0, st>>>(F.csr(), alpha, beta, F.sc, z, p, q, pa, k == 0 ? (int64_t)ge : gu,
                                                     pb, k, tol2, check_only ? 1 : 0, &W);
             if (!check_only)
@@ -7025,14 +7029,14 @@ int ns_solve_impl(etpic_ctx *ctx, const NsRhs &R, double *x, double c, double s,
     const double tol2 = tol * tol;
     SolveWatch &W = *ctx->h_watch;
     unsigned long long *slots = reinterpret_cast<unsigned long long *>(N.partial + 8 * kNsBlocks);
-    bool took = false;
-    if (int rc = resident_solve(W, st, nv, took, [&](unsigned blocks) {
+    OneLaunch way;
+    if (int rc = resident_solve(W, ctx->ns_trials, st, nv, way, [&](unsigned blocks) {
             k_ns_resident<<<blocks, kResThreads, 0, st>>>(N.csr(), N.sc, N.dinv, x, r, z, pb, nb, slots, tol2, max_iter,
                                                           &W);
         }))
         return rc;
-    if (!took && nv <= (int64_t)kResMaxBlocks * kResRows) start();
-    if (!took) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
+    if (way == kFailed) start();
+    if (way != kTook) if (int rc = watch_solve(W, st, max_iter, [&](int k, bool check_only) {
             k_ns_apply<<<gr, kNsThreads, 0, st>>>(N.csr(), N.sc, z, p, q, pb, k == 0 ? nb : (int64_t)gv, pa, k, tol2,
                                                   check_only ? 1 : 0, &W);
             if (!check_only)
