@@ -201,14 +201,15 @@ def _dptr(t):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
-_torch = _dtypes = None
+_torch = _dtypes = _raw_stream = None
 
 
 def _load_torch():
     """torch (imported on first use) and the dtypes the library takes, by name."""
-    global _torch, _dtypes
+    global _torch, _dtypes, _raw_stream
     if _torch is None:
         import torch
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
         _dtypes = {k: getattr(torch, k) for k in ("float64", "float32", "int32", "int64")}
         _torch = torch
     return _torch
@@ -249,8 +250,10 @@ def _stream(stream):
     if stream is not None:
         return stream.cuda_stream
     torch = _torch or _load_torch()
-    # (the handle alone: building torch's Stream object around it costs 2.4 us)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    # (the handle alone, where this torch gives it: building its Stream object costs 2.4 us)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def mesh_canonical(xyz, tet_vert):
