@@ -333,3 +333,49 @@ def test_one_step_downshifted_calls_equal_one_call(E, torch_cuda, n, calls, edc,
     """As test_downshifted_launch_split_changes_nothing."""
     test_downshifted_launch_split_changes_nothing(E, torch_cuda, n, n > 1000, calls, 100.0 if n > 1000 else 1.0, edc, False,
                                                   precision)
+
+
+@pytest.mark.parametrize("precision", [0, 2])
+@pytest.mark.parametrize("sorting", [False, True])
+def test_more_leavers_than_the_queue_holds(E, torch_cuda, sorting, precision):
+    """Twelve million particles, most of which leave their tet in the first
+    step: each of the queue's 64 parts (131,072 entries) runs over, so leavers
+    go by their slice or, in a sorting launch, by a scan of all particles; two
+    steps in one launch against one step per launch.  Identical particles; an
+    edge sums about 1e5 terms in another order (3e-14 of them by chance): 1e-12."""
+    torch = torch_cuda
+    n, side = 12_000_000, 5
+    xyz, tv = synth.kuhn_mesh((side, side, side), (1.0, 1.0, 1.0), 0.1, np.random.default_rng(4))
+    ctx = E.Context(0)
+    ctx.upload_mesh(xyz, tv)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    rnd = lambda *shape: torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen)
+    f = E.Fields(0.1 * rnd(ctx.n_edge, 2), 1e-5 * rnd(ctx.n_face, 2), None, 1e-4 * rnd(ctx.n_face))
+    sp = E.Species(synth.Q_E, synth.M_E, 1.0)
+    lam = torch.rand(3, n, dtype=torch.float64, device="cuda", generator=gen).sort(dim=0)[0]
+    lam = torch.stack([lam[0], lam[1] - lam[0], lam[2] - lam[1]])
+    v = rnd(3, n)
+    v *= 1e6 / v.norm(dim=0)
+    tet = torch.randint(tv.shape[0], (n,), device="cuda", generator=gen, dtype=torch.int32).sort()[0]
+    if precision == 2:
+        u = (lam * (1.0 - 2e-9) * 4294967296.0).long()
+        lam, v = torch.where(u >= 1 << 31, u - (1 << 32), u).int(), v.float()
+    src = E.Particles(lam.contiguous(), v.contiguous(), tet, torch.arange(n, device="cuda"))
+    dt, omega, out = 0.3 / 1e6, 2 * np.pi * 1e9, []
+    for flags in (E.STEP_XCD_REMAP, E.STEP_XCD_REMAP | E.STEP_SLICES_1):
+        g = torch.zeros(ctx.n_edge, dtype=torch.float64, device="cuda")
+        p = src.empty_like() if sorting else src.clone()
+        if sorting:
+            ctx.sort_run_steps(src, p, sp, f, 0, 2, dt, omega, g, flags=flags)
+        else:
+            ctx.run_steps(p, sp, f, 0, 2, dt, omega, g, flags=flags)
+        ctx.check()
+        o = p.ids.argsort()
+        out.append((p.tet[o], p.lam[:, o], p.vel[:, o], g))
+    moved = (out[0][0] != tet).double().mean().item()
+    print(f"[multi] moved to another tet: {moved:.3f}", flush=True)
+    assert moved * n > 64 * 131072
+    for a, b in zip(out[0][:3], out[1][:3]):
+        assert torch.equal(a, b)
+    assert torch.allclose(out[0][3], out[1][3], rtol=0, atol=1e-12 * out[1][3].abs().max().item())
+    ctx.close()
