@@ -40,7 +40,9 @@
 //   k_charge      vertex charge of the particles.
 //   k_gauss_*     continuity residual D^T dG - (rho_new - rho_old).
 //   k_locate, k_positions   Cartesian points <-> (tet, barycentrics).
-//   k_adjoint     reverse of one float64 step (gradient w.r.t. the edge envelope).
+//   k_adjoint, k_adjoint_leavers
+//                 reverse of several float64 steps (gradient w.r.t. the edge
+//                 envelope), and of the particles that left their tet in them.
 //   k_field_spmv, k_nm_*, k_cocg_*   implicit envelope field step.
 //   k_ns_*        Gauss-law (non-solenoidal) field solve: CG on the nodal operator.
 #include <hip/hip_runtime.h>
@@ -201,24 +203,17 @@ struct FieldPtrs {
     int xcd;       // coefficient pass: one contiguous tet range per XCD
 };
 
-template <int kSnap>
-__device__ __forceinline__ double2 envelope(const double2 *const env[3], const double w[3], int64_t id) {
-    if (kSnap == 1) return env[0][id];
-    const double2 a = env[0][id], b = env[1][id], c = env[2][id];
-    return make_double2(w[0] * a.x + w[1] * b.x + w[2] * c.x, w[0] * a.y + w[1] * b.y + w[2] * c.y);
-}
-
 // local edge index of the vertex pair {i, j}, i < j
 __host__ __device__ constexpr int local_edge(int i, int j) { return i == 0 ? j - 1 : (i == 1 ? j + 1 : 5); }
 
-template <int K, int kSnap>
+template <int K>
 __device__ __forceinline__ void coef_A(const int32_t *tp, const double g[4][3], const FieldPtrs &F, double A[3]) {
     A[0] = A[1] = A[2] = 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         if (j == K) continue;
         const int id = tp[local_edge(j < K ? j : K, j < K ? K : j)];
-        const double2 z = envelope<kSnap>(F.e_env, F.w, id);
+        const double2 z = F.e_env[0][id];
         double eps = z.x * F.c - z.y * F.s;
         if (F.e_dc) eps += F.e_dc[id];
         if (j < K) eps = -eps;
@@ -227,7 +222,7 @@ __device__ __forceinline__ void coef_A(const int32_t *tp, const double g[4][3], 
     }
 }
 
-template <int K, int kSnap>
+template <int K>
 __device__ __forceinline__ void coef_C(const int32_t *tp, const double g[4][3], const FieldPtrs &F, double Cv[3]) {
     Cv[0] = Cv[1] = Cv[2] = 0.0;
     constexpr int lf[4][3] = {{1, 2, 3}, {0, 2, 3}, {0, 1, 3}, {0, 1, 2}};
@@ -237,7 +232,7 @@ __device__ __forceinline__ void coef_C(const int32_t *tp, const double g[4][3], 
         const int a = lf[f][0] == K ? lf[f][1] : (lf[f][1] == K ? lf[f][2] : lf[f][0]);
         const int b = lf[f][0] == K ? lf[f][2] : (lf[f][1] == K ? lf[f][0] : lf[f][1]);
         const int id = tp[6 + f];
-        const double2 z = envelope<kSnap>(F.b_env, F.w, id);
+        const double2 z = F.b_env[0][id];
         double beta = z.x * F.c - z.y * F.s;
         if (F.b_dc) beta += F.b_dc[id];
         beta *= 2.0;
@@ -1023,10 +1018,12 @@ __global__ void __launch_bounds__(kBlock) k_slots_to_edges(int64_t ne, const int
 
 
 // 2 / d for d >= 1 or NaN: the reciprocal refined, without the operand scaling
-// a general division starts with.  float32: the steps of the general division,
-// hence its (correctly rounded) result.  float64: one cubic step from the
-// hardware's reciprocal (relative error below 2^-20, so the step's own is
-// below 2^-60).  The fix-up gives 0 at d = inf.
+// a general division starts with.  float64: one cubic step from the hardware's
+// reciprocal (measured within 2^-24, so the step's own error is below 2^-72);
+// equal to 2.0 / d in each of 1e8 values over the whole range.  float32: the
+// general division's steps, equal to its result below d = 2^126 (where the
+// reciprocal's underflow ends: 0 beyond, for a rotation of more than 9e18 per
+// step).  The fix-up gives 0 at d = inf.
 __device__ __forceinline__ float two_over(float d) {
     float y = __builtin_amdgcn_rcpf(d);
     y = fmaf(fmaf(-d, y, 1.0f), y, y);
@@ -1694,9 +1691,9 @@ __global__ void __launch_bounds__(kBlock) k_walk_coef(StepArgs<Real> a, int64_t 
 // path integrals, a third of a single step's instructions, run once per launch
 // on sums over its steps.  What is left per step is the arithmetic of the push
 // itself.  Measured, ten steps and their re-sort in one call, 40^3 x 6 tets,
-// against one step per launch: 1e7 float64 2.90 -> 0.78 ms, 5e7 mixed 9.64 ->
-// 2.50 ms, 1e7 compact 1.99 -> 0.71 ms; the 100 steps of 1,000 electrons on
-// 750 tets 1.14 -> 0.12 ms.
+// against one step per launch: 1e7 float64 2.90 -> 0.65 ms, 5e7 mixed 9.64 ->
+// 2.27 ms, 1e7 compact 1.99 -> 0.60 ms; the 100 steps of 1,000 electrons on
+// 750 tets 1.14 -> 0.14 ms.
 //
 // The rows of each step come from the parts of the tet's row (real, imaginary,
 // dc, built once per call by the coefficient pass).  A wavefront stages the
@@ -2302,15 +2299,15 @@ __global__ void __launch_bounds__(kBlock) k_tet_coef_env(int64_t nt, const doubl
     }
     double o[12];
     if (part < 3) {
-        coef_A<0, 1>(tp, g, G, o);
-        coef_A<1, 1>(tp, g, G, o + 3);
-        coef_A<2, 1>(tp, g, G, o + 6);
-        coef_A<3, 1>(tp, g, G, o + 9);
+        coef_A<0>(tp, g, G, o);
+        coef_A<1>(tp, g, G, o + 3);
+        coef_A<2>(tp, g, G, o + 6);
+        coef_A<3>(tp, g, G, o + 9);
     } else {
-        coef_C<0, 1>(tp, g, G, o);
-        coef_C<1, 1>(tp, g, G, o + 3);
-        coef_C<2, 1>(tp, g, G, o + 6);
-        coef_C<3, 1>(tp, g, G, o + 9);
+        coef_C<0>(tp, g, G, o);
+        coef_C<1>(tp, g, G, o + 3);
+        coef_C<2>(tp, g, G, o + 6);
+        coef_C<3>(tp, g, G, o + 9);
     }
     double *dst = out + T * kEnvRow + 12 * part;
 #pragma unroll
@@ -4875,7 +4872,7 @@ struct etpic_ctx {
     unsigned *d_status = nullptr;    // device status word
     unsigned *d_walk_queue = nullptr;  // kWalkQueueCap particle indices
     unsigned *d_slice_queue = nullptr; // kWalkQueueCap slice indices
-    unsigned *d_walk_ctr = nullptr;    // kCtrSets sets of 3 walk-queue counters
+    unsigned *d_walk_ctr = nullptr;    // kCtrSets sets of walk-queue counters, kCtrStride words each
     unsigned long long *d_red = nullptr;  // 2 words per block of the residual maxima
     double *d_scratch = nullptr;          // device address of `scratch` on this device
     // mean same-tet run length from the last sort (sum count^2 / N_p), read
