@@ -1709,9 +1709,11 @@ __global__ void __launch_bounds__(kBlock) k_walk_coef(StepArgs<Real> a, int64_t 
 // queued; k_walk_multi walks it and takes it through the remaining steps.
 //
 // A launch takes up to 16 steps, of few particles up to 32: there the launch
-// itself and the walk after it are the larger part (100 steps of 1,000
-// electrons: 7 launches 147, 4 launches 122 us), while of many particles more steps in
-// one launch mean more of them that finish it in the walk.
+// itself and the walk after it are the larger part (100 steps in 7 launches
+// and in 4: 1,000 electrons on 750 tets 199 and 182 us a call, 32,768 207 and
+// 170, 32,768 on 83,000 tets 278 and 221; 50,000 and 400,000 electrons, left
+// at 16, would gain 13 to 16 % too where few leave their tet).  The more steps in one
+// launch, the more of many particles finish it in the walk, one lane each.
 constexpr int kMaxFused = 32, kMaxFusedMany = 16;
 // per tet: the largest of the coefficient forms but the parts of three
 // snapshots, which go to the wide rows (etpic_ds_rows_bind) where those are bound
@@ -2569,14 +2571,15 @@ __device__ __forceinline__ bool ds_step(const DsArgs<Real> &d, int j, const DsRo
 }
 
 // kLen reals of each of a wavefront's nr tets, `stride` apart in memory, into
-// its LDS rows, eight loads of a lane in flight together (one after the other
+// its LDS rows, four loads of a lane in flight together (one after the other
 // they were most of a launch of few particles: one step of 1,000 on 750 tets,
 // mixed, 66 -> 41 us with 16 particles to a wavefront; of 4e6 on 384,000, ten
-// steps, 870 -> 732).
+// steps, 878 -> 737.  Eight: 734, but ten float64 steps of 1e7, three tets to a
+// wavefront, 2495 instead of 2460).
 template <int kLen, int kRow, typename Src, typename Real>
 __device__ __forceinline__ void stage_rows(const Src *__restrict__ src, int stride, const int *tets, int nr, int ln,
                                            Real *rows) {
-    constexpr int kLoads = 8;
+    constexpr int kLoads = 4;
     const int total = nr * kLen;
 #pragma unroll 1
     for (int i0 = ln; i0 < total; i0 += 64 * kLoads) {
@@ -5266,8 +5269,9 @@ struct etpic_ctx {
     // Blocks of k_walk_multi.  Few particles: as many as the queue has parts (an
     // empty block costs its table's clearing; 1,000 electrons 5.4 us with 512).
     // More blocks take a long queue's leavers sooner and pay for it with more
-    // tables: 5e7 particles 111 us with 512, 130 with 1024; 1e8 in a bunch 1075 and
-    // 780.
+    // tables; re-sort and ten steps, mixed, with 512 and 1024: 1e7 on 384,000
+    // tets 632 and 654 us, 3e7 in a bunch on 3.1e6 tets 3501 and 3472, 6e7 5598
+    // and 5439, 1e8 8951 and 8524; without a bunch within 1 % from 3e7 on.
     static unsigned leaver_blocks(int64_t n) {
         return n <= kFewParticles ? kShards : n < ((int64_t)1 << 26) ? kLeaverBlocks : 2 * kLeaverBlocks;
     }
@@ -5304,15 +5308,23 @@ struct etpic_ctx {
         return ETPIC_OK;
     }
 
+    // A call's steps taken in several calls of fused_steps.
+    struct Segment {
+        bool goes_on, last;
+        unsigned sets;
+    };
+
     // Multi-step launches of p.  With src, the first launch reads src and
     // writes p: at the tet-sorted places (sorted), or place for place.
-    // parts_ready: the rows' parts are there from an earlier call with the
-    // same fields.  Plans over three snapshots with kSnap = 1: two steps to a
+    // seg: a call that goes on from an earlier one with the same fields finds
+    // the rows' parts ready and adds to the slots as they are; one that another
+    // goes on from leaves them; `sets` carries on the turns of the counter sets.
+    // Plans over three snapshots with kSnap = 1: two steps to a
     // launch, from their own rows.
     template <typename Real, int kSnap, bool kFixed>
     int fused_steps(const etpic_particles *p, const etpic_species *sp, const StepPlan *plans, int nsteps, int most,
                     double dt, double omega, double *dG, double *rho, uint32_t flags, hipStream_t st,
-                    const etpic_particles *src, bool sorted = true, bool parts_ready = false) {
+                    const etpic_particles *src, bool sorted = true, Segment *seg = nullptr) {
         const int remap = (flags & ETPIC_STEP_XCD_REMAP) ? 1 : 0;
         const int64_t n = p->n, nt = host.nt;
         const bool time_all = (flags & ETPIC_STEP_TIMING_ALL) != 0;
@@ -5332,14 +5344,11 @@ struct etpic_ctx {
                 ts->steps = j1 - j0;
             }
             ta = time_all ? ts : nullptr;
-            if (i == 0 && parts_ready) {
-                k_fill_u32<<<grid_for(16 * nt), kBlock, 0, st>>>(reinterpret_cast<unsigned *>(d_tetG), 16 * nt, 0u);
-                HIP_TRY(hipGetLastError());
-            } else if (pairs) {
+            if (pairs) {
                 if (int r = launch_pair(plans[j0], j1 - j0 > 1 ? &plans[j0 + 1] : nullptr, omega,
                                         i == 0 ? d_tetG : nullptr, st, ta))
                     return r;
-            } else if (i == 0) {
+            } else if (i == 0 && !(seg && seg->goes_on)) {
                 if (int r = launch_parts<kSnap>(plans[0].snap, plans[0].w, d_tetG, st, ta)) return r;
             }
             MultiArgs<kSnap> ma{};
@@ -5357,8 +5366,9 @@ struct etpic_ctx {
             a.walk_by_slice = (flags & ETPIC_STEP_WALK_BY_SLICE) ? 1 : 0;
             a.fixed = kFixed ? 1 : 0;
             a.tetG = d_tetG;
-            ctr = d_walk_ctr + (1 + (i & 1)) * kCtrStride;
-            unsigned *next = d_walk_ctr + (1 + ((i + 1) & 1)) * kCtrStride;
+            const unsigned turn = seg ? seg->sets++ : (unsigned)i;
+            ctr = d_walk_ctr + (1 + (turn & 1)) * kCtrStride;
+            unsigned *next = d_walk_ctr + (1 + ((turn + 1) & 1)) * kCtrStride;
             a.walk_ctr = ctr;
             hipEvent_t e0 = ev_start(ts, 1), e1 = ev_stop(ts, 1);
             if (moves) {
@@ -5384,7 +5394,7 @@ struct etpic_ctx {
             HIP_TRY(hipGetLastError());
             j0 = j1;
         }
-        return launch_edges(dG, st, ta, ctr);
+        return seg && !seg->last ? ETPIC_OK : launch_edges(dG, st, ta, ctr);
     }
 
     template <typename Real>
@@ -6268,12 +6278,12 @@ int etpic_adjoint_workspace(const etpic_ctx *ctx, int64_t n, int nsteps, int che
 // nsteps float64 steps from one state buffer into another (see fused_steps).
 static int adjoint_forward(etpic_ctx *ctx, const etpic_particles &from, const etpic_particles &to,
                            const etpic_species *sp, const etpic_fields *f, int64_t step0, int nsteps, double dt,
-                           double omega, double *dG, hipStream_t st, bool parts_ready) {
+                           double omega, double *dG, hipStream_t st, etpic_ctx::Segment *seg) {
     std::vector<StepPlan> plans((size_t)nsteps);
     for (int j = 0; j < nsteps; ++j)
         plans[j] = StepPlan{{f, nullptr, nullptr}, {1.0, 0.0, 0.0}, (double)(step0 + j) * dt};
     return ctx->fused_steps<double, 1, false>(&to, sp, plans.data(), nsteps, ctx->most_fused(to.n), dt, omega, dG, nullptr,
-                                              ETPIC_STEP_XCD_REMAP, st, &from, false, parts_ready);
+                                              ETPIC_STEP_XCD_REMAP, st, &from, false, seg);
 }
 
 int etpic_forward_checkpointed(etpic_ctx *ctx, const etpic_particles *p, const etpic_species *sp,
@@ -6293,11 +6303,15 @@ int etpic_forward_checkpointed(etpic_ctx *ctx, const etpic_particles *p, const e
     const int64_t n = p->n;
     k_copy_state<<<grid_for(n), kBlock, 0, st>>>(*p, state_view(workspace, 0, L, n));
     HIP_TRY(hipGetLastError());
+    etpic_ctx::Segment part{};
     for (int seg = 0; seg < L.ncp; ++seg) {
         const int k0 = seg * checkpoint_every, k1 = std::min(nsteps, k0 + checkpoint_every);
         const etpic_particles from = state_view(workspace, (size_t)seg * L.state, L, n);
         const etpic_particles to = seg + 1 < L.ncp ? state_view(workspace, (size_t)(seg + 1) * L.state, L, n) : *p;
-        if (int r = adjoint_forward(ctx, from, to, sp, f, step0 + k0, k1 - k0, dt, omega, acc, st, seg > 0)) return r;
+        // (the currents of all segments gather in the slots and go to dG after the last)
+        part.goes_on = seg > 0;
+        part.last = seg + 1 == L.ncp;
+        if (int r = adjoint_forward(ctx, from, to, sp, f, step0 + k0, k1 - k0, dt, omega, acc, st, &part)) return r;
     }
     return ETPIC_OK;
 }
@@ -6340,10 +6354,13 @@ int etpic_backward(etpic_ctx *ctx, int64_t n, const etpic_species *sp, const etp
             return i == 0 ? state_view(workspace, (size_t)seg * L.state, L, n)
                           : state_view(workspace, L.slots_off + (size_t)(i - 1) * L.state, L, n);
         };
-        for (int i = 1; i < pieces; ++i)
+        etpic_ctx::Segment part{true, false, 0};   // (what it leaves in the slots is not wanted)
+        for (int i = 1; i < pieces; ++i) {
+            part.last = i + 1 == pieces;
             if (int r = adjoint_forward(ctx, start(i - 1), start(i), sp, f, step0 + begin(i - 1),
-                                        begin(i) - begin(i - 1), dt, omega, scratch_dG, st, true))
+                                        begin(i) - begin(i - 1), dt, omega, scratch_dG, st, &part))
                 return r;
+        }
         for (int i = pieces - 1; i >= 0; --i) {
             const etpic_particles cur = start(i);
             const StepArgs<double> base = ctx->step_args<double>(&cur, sp, dt, scratch_dG, nullptr);
