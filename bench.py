@@ -712,12 +712,14 @@ def roofline(res, form, n_p, n_t, n_e, sort_every, copy_gbs, traffic_path=None, 
     elif sort_every:
         step_bytes += SORT_BYTES_PER_PARTICLE[form] * n_p / sort_every
     step_gbs = step_bytes / (r["ms_per_step"] * 1e-3) / 1e9
-    return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    alu = alu_roofline(valu_path, name, launch_ms)
+    nearer = "alu" if alu is not None and alu["frac"] > ach / HBM_PEAK_GBS else "hbm"   # the ceiling it is nearer to
+    return {"bound": "hbm", "limited_by": nearer, "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": name,
             "bytes_per_launch": bytes_launch, "kernel_ms": round(launch_ms, 5), "steps_per_launch": per,
             "stream_GBs": round(stream_gbs, 1), "frac_of_stream": round(ach / stream_gbs, 4),
             "copy_GBs": round(copy_gbs, 1), "frac_of_copy": round(ach / copy_gbs, 4),
-            "alu": alu_roofline(valu_path, name, launch_ms),
+            "alu": alu,
             "whole_step": {"bytes_per_step": int(step_bytes), "ms_per_step": round(r["ms_per_step"], 5),
                            "achieved": round(step_gbs, 1), "frac": round(step_gbs / HBM_PEAK_GBS, 4),
                            "note": "algorithmic bytes of the whole step (state %d B per particle, %d B per "
