@@ -7,8 +7,8 @@
 //                 in lam), where A_i, C_i fold the real parts Re{dof e^{jwt}} + dc
 //                 of the 6 edge and 4 face DoFs into the gradients; the envelope
 //                 may be interpolated in time between three snapshots.  Per
-//                 step, or once per multi-step call as the parts the steps'
-//                 rows are formed from.
+//                 step, per two steps, or once per multi-step call as the
+//                 parts the steps' rows are formed from.
 //   k_push_multi  several steps of a multi-step call per launch: per particle,
 //                 tet-sorted, gather, Boris push and in-tet path integrals of
 //                 each step from the staged row parts, the state in registers
@@ -5872,7 +5872,7 @@ int check_buffer(const void *buf, size_t bytes, size_t need, const char *what) {
 // float32 push rows, float64 and float32 geometry rows, tet-face ids, the
 // coefficient table, vertex coordinates,
 // point-location start grid, vertex -> edge CSR, sort counters and tile sums,
-// edge -> tet-slot CSR, two per-tet current slot buffers.
+// edge -> tet-slot CSR, per-tet current slots.
 struct MeshPtrs {
     TetTopo *topo;
     double *grad64, *gpush64, *geo64;
