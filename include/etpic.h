@@ -44,10 +44,10 @@
  * downshifted buffers must then be given again), or destruction.  Particle
  * arrays, field DoFs, outputs, the adjoint workspace and the downshifted
  * history are caller-owned too and must stay valid until the work queued on
- * `stream` has finished.  Host resources taken by etpic_create: one pinned
- * 8-byte word (the sort's run-length statistic is read into it without
- * blocking) and a fixed pool of HIP events for ETPIC_STEP_TIMING; none
- * afterwards.
+ * `stream` has finished.  Host resources taken by etpic_create: eight pinned
+ * words (the sort's run-length statistic, read without blocking; a residual's
+ * two maxima; what the host follows an iterative solve by) and a fixed pool
+ * of HIP events for ETPIC_STEP_TIMING; none afterwards.
  *
  * Errors: every entry point returns an etpic status (0 = OK).  On failure the
  * message is available from etpic_last_error() (thread-local).  Errors found
@@ -113,7 +113,8 @@ enum etpic_device_flags {
 /* flags of etpic_gather_push_deposit */
 enum etpic_step_flags {
     ETPIC_STEP_XCD_REMAP = 1u, /* map consecutive particle blocks to one XCD (default on) */
-    ETPIC_STEP_TIMING = 2u,    /* time the particle kernel of each step with HIP events (etpic_kernel_time) */
+    ETPIC_STEP_TIMING = 2u,    /* time the particle kernel of each step with HIP events (etpic_kernel_time);
+                                  EINVAL, before anything is launched, when their pool runs out */
     /* slices of 64 particles per wavefront of the particle kernel; without one
      * of these the library picks 1, 4 or 16 from the last sort's (etpic_sort,
      * etpic_sort_run_steps, etpic_ds_sort) mean, over particles, of the number
