@@ -379,7 +379,8 @@ __device__ __forceinline__ void half_row(int face, const double z[6], const doub
 
 // Clears the current slots of tets [T0, T0 + nloc) (by one block; null: none).
 // A call clears the slots it is about to use in its first kernel, the
-// coefficient pass, whose stores these join: so a call recorded into a graph
+// coefficient pass, beside whose gathers these stores run (behind its own
+// stores they cost small calls up to 1 %): so a call recorded into a graph
 // may be replayed, and one that stopped short leaves nothing for the next.
 // (Each slot cleared by the edge that read it: 8-byte stores out of order,
 // 35 instead of 19 us on 384,000 tets; a fill of its own: one launch more.)
@@ -435,6 +436,7 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
         for (int i = threadIdx.x; i < nloc; i += kBlock) sface[i] = tf[i];
     }
     __syncthreads();
+    clear_slots(slots, T0, nloc);
     const int part = (int)(threadIdx.x >= kTets);
     const int t = threadIdx.x & (kTets - 1);
     const bool act = t < nloc;
@@ -580,7 +582,6 @@ __device__ __forceinline__ void tet_coef(int64_t nt, const double *__restrict__ 
             }
         }
     }
-    clear_slots(slots, T0, nloc);
 }
 
 template <typename Real, int kSnap, int kMode>
